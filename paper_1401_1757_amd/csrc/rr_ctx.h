@@ -137,6 +137,7 @@ struct rr_ctx {
     std::vector<double> vas_r0_host;     // their values (the last generation's)
     int n_ages_stage = 0;
     std::vector<double> shock_host;
+    double curve_log_span = 0.0;         // bound on |log| of any product of one scenario's factors
 
     // portfolio
     bool has_pf = false;
@@ -157,6 +158,8 @@ struct rr_ctx {
     DevBuf<double> cf_t;                  // [cf_steps][cf_cols] (table tiles)
     int cf_cols = 0;
     bool has_flow = false;                // some tile is not FLOW_LEVEL
+    bool has_frac = false;                // some tile is FLOW_FRAC
+    int max_term = 0;                     // longest remaining term at node 0
 
     // uploaded Markov models
     bool has_markov = false;
@@ -176,6 +179,7 @@ struct rr_ctx {
     DevBuf<int> counters;
     DevBuf<double> partial;
     DevBuf<double> totals_tmp;
+    DevBuf<double> flow_work;             // rows and sums of the summed-cash-flow totals
     DevBuf<long long> path_off;
     int path_off_node = -1, path_off_step = -1, path_off_gen = -1;
     std::map<PlanKey, std::unique_ptr<Plan>> plans;

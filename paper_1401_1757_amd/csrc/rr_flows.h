@@ -1,0 +1,509 @@
+// Expected cash flows of the policies, walked forward in time (device
+// templates, FP64).
+//
+// The reserve of Eq. (3.1) is linear in the discount products D_t = v_0 ...
+// v_{t-1} (Eq. (3.5)): r_0 = sum_t f_t D_t, where f_t is the cash flow expected
+// at time t.  f_t comes from the forward recurrence of the state occupancy
+// (a row vector times W_t per step), the adjoint of the backward recurrence:
+// the same products of survival probabilities, taken once per policy instead
+// of once per policy and scenario.  What then remains per scenario is one
+// multiply-add per month, and nothing per policy where only totals are asked
+// for (the flows add up over the policies first).
+//
+// A walker holds one policy per lane.  load(t) fetches what step t needs
+// (issued ahead of its use), step(t, ..) returns f_t and advances the lane
+// through step t.  Steps are taken in increasing t; a lane past its term has
+// flow 0.  MASK = false is the form for steps that every lane of the tile
+// takes (t < the tile's smallest remaining term, no expired or padding lane).
+#pragma once
+
+#include "rr_recurrence.h"
+
+namespace rr {
+
+// The table values of one step; unused members cost nothing after inlining.
+struct FlowIn {
+    double x1, x2, x3;   // one-step survival probabilities of the lives
+    double cv;           // table tiles: cash flow of the step
+};
+
+template <bool LDSQ>
+__device__ __forceinline__ double flow_q(const RecParams &P, const double *__restrict__ lq, int idx)
+{
+    return qload<LDSQ>(lq, P.q, idx);
+}
+
+// The node's mortality shock on a survival probability (m != 1).
+__device__ __forceinline__ double shocked(double p, double m) { return 1.0 - fmin(1.0, m * (1.0 - p)); }
+
+// Payment factor F(T) of a pattern tile (PatLane in rr_recurrence.h), walked
+// forward: the position in the policy year counts up, and the level follows by
+// one multiplication by 1 + e at each anniversary passed.
+struct PatWalk {
+    double g, lev;
+    int pos, n, annual;   // months since the last anniversary (0 at one), anniversaries so far
+
+    __device__ __forceinline__ void init(const RecParams &P, int slot, int shift, int t0)
+    {
+        const int code = P.pat_code[slot];
+        g = P.pat_g[slot];
+        annual = code & PAT_ANNUAL;
+        const unsigned w = (unsigned)(shift + ((code & PAT_ARREARS) ? 1 : 0) + t0 + 12 - (code & 255));
+        n = (int)(w / 12u);
+        pos = (int)(w % 12u);
+        double l = 1.0, x = g;
+        for (int k = n; k > 0; k >>= 1) {
+            if (k & 1) l *= x;
+            x *= x;
+        }
+        lev = l;
+    }
+    // F at the current step; moves on to the next one.
+    __device__ __forceinline__ double next()
+    {
+        const double f = annual ? (pos == 0 && n > 0 ? 12.0 * lev : 0.0) : lev;
+        ++pos;
+        const bool ann = pos == 12;
+        pos = ann ? 0 : pos;
+        n += ann ? 1 : 0;
+        lev = ann ? lev * g : lev;
+        return f;
+    }
+};
+
+// What every walker knows of its lane.
+struct FlowLane {
+    int slot, uid, S;    // sorted slot, upload index (-1: padding), remaining term
+    bool live;
+    __device__ __forceinline__ void init(const RecParams &P, const Tile &T, int shift, int lane)
+    {
+        slot = T.first + lane;
+        S = P.term[slot] - shift;
+        uid = P.uidx[slot];
+        live = uid >= 0 && S > 0;
+    }
+};
+
+// Scalar-reserve models (one life, or two lives with the reserve in state 00):
+// occupancy P, flow f_t = c_{t-1} + P_t a0 (at t = S: the boundary reserve in
+// place of a0), c_t = P_t (p a1 + (1 - p) b1), P_{t+1} = P_t p.
+template <bool LDSQ, bool TWO, int FLOW>
+struct FlowScalar {
+    int S, qa, qb;
+    double occ, carry, a0, a1, b1, a1mb1, rS;
+    const double *cfb;
+    int cfs;
+    PatWalk pat;
+
+    __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int shift, int t0)
+    {
+        S = L.S;
+        qa = P.qoff1[L.slot] + P.age1[L.slot] + shift;
+        qb = TWO ? P.qoff2[L.slot] + P.age2[L.slot] + shift : 0;
+        a0 = P.coef[L.slot];
+        a1 = P.coef[P.n_pad + L.slot];
+        b1 = P.coef[2 * P.n_pad + L.slot];
+        rS = P.coef[3 * P.n_pad + L.slot];
+        a1mb1 = a1 - b1;
+        occ = L.live ? 1.0 : 0.0;
+        carry = 0.0;
+        if constexpr (FLOW == FLOW_TABLE) {
+            cfb = P.cf_t + P.pat_code[L.slot] + (ptrdiff_t)shift * P.cf_cols;
+            cfs = P.cf_cols;
+        }
+        if constexpr (FLOW == FLOW_PATTERN) pat.init(P, L.slot, shift, t0);
+    }
+    __device__ __forceinline__ FlowIn load(const RecParams &P, const double *__restrict__ lq, int t) const
+    {
+        FlowIn in{};
+        in.x1 = flow_q<LDSQ>(P, lq, qa + t);
+        if constexpr (TWO) in.x2 = flow_q<LDSQ>(P, lq, qb + t);
+        if constexpr (FLOW == FLOW_TABLE) in.cv = cfb[(ptrdiff_t)t * cfs];
+        return in;
+    }
+    __device__ __forceinline__ void shock(FlowIn &in, double m) const
+    {
+        in.x1 = shocked(in.x1, m);
+        if constexpr (TWO) in.x2 = shocked(in.x2, m);
+    }
+    template <bool MASK>
+    __device__ __forceinline__ double step(int t, const FlowIn &in)
+    {
+        const double p = TWO ? in.x1 * in.x2 : in.x1;
+        double c, adv = a0;
+        if constexpr (FLOW == FLOW_PATTERN) {
+            const double f = pat.next();
+            c = p * (f * a1);
+            adv = f * a0;
+        } else if constexpr (FLOW == FLOW_TABLE) {
+            c = p * in.cv;
+        } else {
+            c = fma(p, a1mb1, b1);
+        }
+        const bool on = !MASK || t < S;
+        const double out = fma(occ, on ? adv : rS, carry);
+        carry = on ? occ * c : 0.0;
+        occ = on ? occ * p : 0.0;
+        return out;
+    }
+};
+
+// Two lives with a vector reserve: occupancy of states 00, 10 and (LAST) 01.
+// ESC: every amount times the payment factor.
+template <bool LDSQ, bool LAST, bool ESC>
+struct FlowVector {
+    int S, qa, qb;
+    double o00, o01, o10, carry, cf[6], d;
+    PatWalk pat;
+
+    __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int shift, int t0)
+    {
+        S = L.S;
+        qa = P.qoff1[L.slot] + P.age1[L.slot] + shift;
+        qb = P.qoff2[L.slot] + P.age2[L.slot] + shift;
+#pragma unroll
+        for (int j = 0; j < 6; ++j) cf[j] = P.coef[j * P.n_pad + L.slot];
+        d = LAST ? P.coef[6 * P.n_pad + L.slot] : 0.0;
+        o00 = L.live ? 1.0 : 0.0;
+        o01 = o10 = carry = 0.0;
+        if constexpr (ESC) pat.init(P, L.slot, shift, t0);
+    }
+    __device__ __forceinline__ FlowIn load(const RecParams &P, const double *__restrict__ lq, int t) const
+    {
+        FlowIn in{};
+        in.x1 = flow_q<LDSQ>(P, lq, qa + t);
+        in.x2 = flow_q<LDSQ>(P, lq, qb + t);
+        return in;
+    }
+    __device__ __forceinline__ void shock(FlowIn &in, double m) const
+    {
+        in.x1 = shocked(in.x1, m);
+        in.x2 = shocked(in.x2, m);
+    }
+    template <bool MASK>
+    __device__ __forceinline__ double step(int t, const FlowIn &in)
+    {
+        if (MASK && t >= S) o00 = o01 = o10 = 0.0;
+        const double px = in.x1, py = in.x2, qx = 1.0 - px, qy = 1.0 - py;
+        double f = 1.0;
+        if constexpr (ESC) f = pat.next();
+        double adv = fma(o10, cf[4], o00 * cf[0]);
+        if constexpr (LAST) adv = fma(o01, cf[2], adv);
+        const double out = ESC ? fma(f, adv, carry) : carry + adv;
+        const double n00 = o00 * (px * py);
+        const double n10 = fma(o10, py, o00 * (qx * py));
+        double arr = fma(n10, cf[5], n00 * cf[1]);
+        if constexpr (LAST) {
+            const double n01 = fma(o01, px, o00 * (px * qy));
+            arr = fma(n01, cf[3], arr);
+            // benefit on the second death: from 00 both die, from 01 and 10 the survivor
+            arr = fma(fma(o10, qy, fma(o01, qx, o00 * (qx * qy))), d, arr);
+            o01 = n01;
+        }
+        o00 = n00;
+        o10 = n10;
+        carry = ESC ? f * arr : arr;
+        return out;
+    }
+};
+
+// Three independent lives: the occupancy of every state is a product of the
+// lives' survival probabilities, and "some life alive" is the sum of positive
+// terms X1 + (1 - X1)(X2 + (1 - X2) X3).
+template <bool LDSQ>
+struct FlowThree {
+    int S, qa, qb, qc;
+    bool last;
+    double l1, l2, l3, carry, a0all, a0, a1;
+
+    __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int shift, bool is_last)
+    {
+        S = L.S;
+        last = is_last;
+        qa = P.qoff1[L.slot] + P.age1[L.slot] + shift;
+        qb = P.qoff2[L.slot] + P.age2[L.slot] + shift;
+        qc = P.qoff3[L.slot] + P.age3[L.slot] + shift;
+        a0all = P.coef[L.slot];
+        a1 = P.coef[P.n_pad + L.slot];
+        a0 = last ? P.coef[2 * P.n_pad + L.slot] : 0.0;
+        l1 = l2 = l3 = L.live ? 1.0 : 0.0;
+        carry = 0.0;
+    }
+    __device__ __forceinline__ FlowIn load(const RecParams &P, const double *__restrict__ lq, int t) const
+    {
+        FlowIn in{};
+        in.x1 = flow_q<LDSQ>(P, lq, qa + t);
+        in.x2 = flow_q<LDSQ>(P, lq, qb + t);
+        in.x3 = flow_q<LDSQ>(P, lq, qc + t);
+        return in;
+    }
+    __device__ __forceinline__ void shock(FlowIn &in, double m) const
+    {
+        in.x1 = shocked(in.x1, m);
+        in.x2 = shocked(in.x2, m);
+        in.x3 = shocked(in.x3, m);
+    }
+    template <bool MASK>
+    __device__ __forceinline__ double step(int t, const FlowIn &in)
+    {
+        if (MASK && t >= S) l1 = l2 = l3 = 0.0;
+        // all alive: a0all; some alive but not all: a0 (the last survivor's)
+        const double all = l1 * l2 * l3;
+        const double some = fma(1.0 - l1, fma(1.0 - l2, l3, l2), l1);
+        const double out = carry + fma(all, a0all - a0, some * a0);
+        l1 *= in.x1;
+        l2 *= in.x2;
+        l3 *= in.x3;
+        const double nsome = fma(1.0 - l1, fma(1.0 - l2, l3, l2), l1);
+        carry = (last ? nsome : l1 * l2 * l3) * a1;
+        return out;
+    }
+};
+
+// One life on an uploaded Markov model of M states (4: the padded small form,
+// MAX_MK_STATES: the large one): occupancy row vector times the matrix at the
+// attained age; benefits at the end of a month, premium in state 0.
+template <int M>
+struct FlowMarkov {
+    int S;
+    const double *wb;
+    double occ[M], c[M], carry, a0;
+
+    __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int shift)
+    {
+        S = L.S;
+        a0 = P.coef[L.slot];
+        const int model = L.live ? P.pat_code[L.slot] : 0;
+        const int age0 = L.live ? P.age1[L.slot] + shift : 0;
+        wb = P.mk_w + ((size_t)model * P.mk_ages + age0) * (M * M);
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            c[j] = M <= 4 ? P.coef[(1 + (j & 3)) * P.n_pad + L.slot]
+                          : P.coef[P.n_pad + L.slot] * P.mk_c[model * M + j];
+            occ[j] = 0.0;
+        }
+        occ[0] = L.live ? 1.0 : 0.0;
+        carry = 0.0;
+    }
+    // f_t; the lane's matrix is read here (rows of the last month again past the term).
+    __device__ __forceinline__ double step(int t)
+    {
+        const bool on = t < S;
+        if (!on) {
+#pragma unroll
+            for (int j = 0; j < M; ++j) occ[j] = 0.0;
+        }
+        const double *w = wb + (size_t)max(min(t, S - 1), 0) * (M * M);
+        const double out = fma(occ[0], a0, carry);
+        double n[M];
+#pragma unroll
+        for (int j = 0; j < M; ++j) n[j] = occ[0] * w[j];
+#pragma unroll
+        for (int i = 1; i < M; ++i)
+#pragma unroll
+            for (int j = 0; j < M; ++j) n[j] = fma(occ[i], w[i * M + j], n[j]);
+        double arr = 0.0;
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            arr = fma(n[j], c[j], arr);
+            occ[j] = n[j];
+        }
+        carry = arr;
+        return out;
+    }
+};
+
+// Annuity paid at the fraction f of the month: a second flow, discounted by
+// D_t v_t^f, beside the premium's.
+template <bool LDSQ, bool TWO>
+struct FlowFrac {
+    int S, qa, qb;
+    double occ, a0, pay, f, g;
+
+    __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int shift)
+    {
+        S = L.S;
+        qa = P.qoff1[L.slot] + P.age1[L.slot] + shift;
+        qb = TWO ? P.qoff2[L.slot] + P.age2[L.slot] + shift : 0;
+        a0 = P.coef[L.slot];
+        pay = P.coef[P.n_pad + L.slot];
+        f = P.frac;
+        g = 1.0 - P.frac;
+        occ = L.live ? 1.0 : 0.0;
+    }
+    __device__ __forceinline__ FlowIn load(const RecParams &P, const double *__restrict__ lq, int t) const
+    {
+        FlowIn in{};
+        in.x1 = flow_q<LDSQ>(P, lq, qa + t);
+        if constexpr (TWO) in.x2 = flow_q<LDSQ>(P, lq, qb + t);
+        return in;
+    }
+    __device__ __forceinline__ void shock(FlowIn &in, double m) const
+    {
+        in.x1 = shocked(in.x1, m);
+        if constexpr (TWO) in.x2 = shocked(in.x2, m);
+    }
+    // f_t; the flow within the month goes to *mid.
+    __device__ __forceinline__ double step(int t, const FlowIn &in, double *mid)
+    {
+        if (t >= S) occ = 0.0;
+        const double pf = TWO ? fma(f, in.x1, g) * fma(f, in.x2, g) : fma(f, in.x1, g);
+        *mid = occ * (pf * pay);
+        const double out = occ * a0;
+        occ *= TWO ? in.x1 * in.x2 : in.x1;
+        return out;
+    }
+};
+
+// Walk of one tile at one node from t = 0 to its last flow (t = smax): emit(u,
+// flow) for each step of a block of U consecutive steps starting at t, then
+// done(t) once per block.  The table values of a block are all loaded before
+// its first step.  Steps past the tile's last load its last month's values
+// again and return 0.
+template <int U, class W, class Emit, class Done>
+__device__ __forceinline__ void flow_walk(const RecParams &P, const double *__restrict__ lq, W &w, double m,
+                                          int smax, int smin, Emit emit, Done done)
+{
+    const bool shock = m != 1.0;
+    FlowIn a[U];
+    auto fetch = [&](int t) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) a[u] = w.load(P, lq, min(t + u, smax - 1));
+    };
+    fetch(0);
+    for (int t = 0; t <= smax; t += U) {
+        FlowIn b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) b[u] = a[u];
+        if (t + U <= smax) fetch(t + U);
+        if (shock) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) w.shock(b[u], m);
+        }
+        if (t + U <= smin) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) emit(u, w.template step<false>(t + u, b[u]));
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) emit(u, w.template step<true>(t + u, b[u]));
+        }
+        done(t);
+    }
+}
+
+// Dispatch of a tile's model: emit(u, flow) and done(t) as for flow_walk;
+// emit_mid(u, flow) receives the second flow of fractional tiles (before done).
+// SPECIAL: the portfolio has tiles other than level ones.  VEC: it has vector
+// models.  smin is 0 where some lane of the tile is padding or expired.
+template <int U, bool LDSQ, bool VEC, bool SPECIAL, class Emit, class EmitMid, class Done>
+__device__ __forceinline__ void flow_tile(const RecParams &P, const double *__restrict__ lq, const Tile &T,
+                                          int shift, double m, int lane, Emit emit, EmitMid emit_mid,
+                                          Done done)
+{
+    FlowLane L;
+    L.init(P, T, shift, lane);
+    const int smax = T.smax - shift;
+    const int smin = __ballot(!L.live) ? 0 : T.smin - shift;
+    auto walk = [&](auto &w) { flow_walk<U>(P, lq, w, m, smax, smin, emit, done); };
+    if constexpr (SPECIAL) {
+        if (T.flow == FLOW_PATTERN) {
+            if (T.kind == KIND_SINGLE) {
+                FlowScalar<LDSQ, false, FLOW_PATTERN> w;
+                w.init(P, L, shift, 0);
+                walk(w);
+            } else if (T.kind == KIND_JOINT) {
+                FlowScalar<LDSQ, true, FLOW_PATTERN> w;
+                w.init(P, L, shift, 0);
+                walk(w);
+            } else if (T.kind == KIND_REV) {
+                FlowVector<LDSQ, false, true> w;
+                w.init(P, L, shift, 0);
+                walk(w);
+            } else {
+                FlowVector<LDSQ, true, true> w;
+                w.init(P, L, shift, 0);
+                walk(w);
+            }
+            return;
+        }
+        if (T.flow == FLOW_TABLE) {
+            FlowScalar<LDSQ, false, FLOW_TABLE> w;
+            w.init(P, L, shift, 0);
+            walk(w);
+            return;
+        }
+        if (T.flow == FLOW_THREE) {
+            FlowThree<LDSQ> w;
+            w.init(P, L, shift, T.kind == KIND_LAST);
+            walk(w);
+            return;
+        }
+        if (T.flow == FLOW_MARKOV) {
+            auto run = [&](auto &w) {
+                w.init(P, L, shift);
+                for (int t = 0; t <= smax; t += U) {
+#pragma unroll 1
+                    for (int u = 0; u < U; ++u) emit(u, w.step(t + u));
+                    done(t);
+                }
+            };
+            if (P.mk_states > 4) {
+                FlowMarkov<MAX_MK_STATES> w;
+                run(w);
+            } else {
+                FlowMarkov<4> w;
+                run(w);
+            }
+            return;
+        }
+        if (T.flow == FLOW_FRAC) {
+            auto run = [&](auto &w) {
+                w.init(P, L, shift);
+                for (int t = 0; t <= smax; t += U) {
+                    FlowIn a[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        a[u] = w.load(P, lq, min(t + u, smax - 1));
+                        if (m != 1.0) w.shock(a[u], m);
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        double mid;
+                        emit(u, w.step(t + u, a[u], &mid));
+                        emit_mid(u, mid);
+                    }
+                    done(t);
+                }
+            };
+            if (T.kind == KIND_JOINT) {
+                FlowFrac<LDSQ, true> w;
+                run(w);
+            } else {
+                FlowFrac<LDSQ, false> w;
+                run(w);
+            }
+            return;
+        }
+    }
+    if (T.kind == KIND_SINGLE) {
+        FlowScalar<LDSQ, false, FLOW_LEVEL> w;
+        w.init(P, L, shift, 0);
+        walk(w);
+    } else if (T.kind == KIND_JOINT) {
+        FlowScalar<LDSQ, true, FLOW_LEVEL> w;
+        w.init(P, L, shift, 0);
+        walk(w);
+    } else if constexpr (VEC) {
+        if (T.kind == KIND_REV) {
+            FlowVector<LDSQ, false, false> w;
+            w.init(P, L, shift, 0);
+            walk(w);
+        } else {
+            FlowVector<LDSQ, true, false> w;
+            w.init(P, L, shift, 0);
+            walk(w);
+        }
+    }
+}
+
+}  // namespace rr
