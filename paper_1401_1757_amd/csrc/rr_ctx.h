@@ -159,6 +159,7 @@ struct rr_ctx {
     int cf_cols = 0;
     bool has_flow = false;                // some tile is not FLOW_LEVEL
     bool has_frac = false;                // some tile is FLOW_FRAC
+    int flow_set = 0;                     // 0: level tiles only, 1: payment patterns too, 2: other kinds
     int max_term = 0;                     // longest remaining term at node 0
 
     // uploaded Markov models

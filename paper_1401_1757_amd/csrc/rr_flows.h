@@ -36,6 +36,21 @@ __device__ __forceinline__ double flow_q(const RecParams &P, const double *__res
 // The node's mortality shock on a survival probability (m != 1).
 __device__ __forceinline__ double shocked(double p, double m) { return 1.0 - fmin(1.0, m * (1.0 - p)); }
 
+// Stage the survival tables in LDS with the node's shock applied (n threads;
+// the caller synchronises): per-step loads then need no shock.
+__device__ __forceinline__ void flow_stage_tables(const RecParams &P, double *dst, double m, int n)
+{
+    constexpr int B = 4;
+    for (int base = threadIdx.x; base < P.n_q; base += B * n) {
+        double x[B];
+#pragma unroll
+        for (int i = 0; i < B; ++i) x[i] = P.q[min(base + i * n, P.n_q - 1)];
+#pragma unroll
+        for (int i = 0; i < B; ++i)
+            if (base + i * n < P.n_q) dst[base + i * n] = m == 1.0 ? x[i] : shocked(x[i], m);
+    }
+}
+
 // Payment factor F(T) of a pattern tile (PatLane in rr_recurrence.h), walked
 // forward: the position in the policy year counts up, and the level follows by
 // one multiplication by 1 + e at each anniversary passed.
@@ -71,13 +86,18 @@ struct PatWalk {
     }
 };
 
+// A walk may be cut in time: the walker's transfer over steps [t0, t1) is
+// accumulated by tr_step from tr_init, and start(k transfers in order) sets the
+// state they lead to.  Up to FLOW_TR doubles a lane.
+constexpr int FLOW_TR = 4;
+
 // What every walker knows of its lane.
 struct FlowLane {
     int slot, uid, S;    // sorted slot, upload index (-1: padding), remaining term
     bool live;
-    __device__ __forceinline__ void init(const RecParams &P, const Tile &T, int shift, int lane)
+    __device__ __forceinline__ void init(const RecParams &P, int at, int shift)
     {
-        slot = T.first + lane;
+        slot = at;
         S = P.term[slot] - shift;
         uid = P.uidx[slot];
         live = uid >= 0 && S > 0;
@@ -95,7 +115,7 @@ struct FlowScalar {
     int cfs;
     PatWalk pat;
 
-    __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int shift, int t0)
+    __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int, int shift, int t0)
     {
         S = L.S;
         qa = P.qoff1[L.slot] + P.age1[L.slot] + shift;
@@ -125,6 +145,18 @@ struct FlowScalar {
     {
         in.x1 = shocked(in.x1, m);
         if constexpr (TWO) in.x2 = shocked(in.x2, m);
+    }
+    __device__ __forceinline__ static void tr_init(double (&x)[FLOW_TR]) { x[0] = 1.0; }
+    __device__ __forceinline__ static void tr_step(double (&x)[FLOW_TR], const FlowIn &in)
+    {
+        x[0] *= TWO ? in.x1 * in.x2 : in.x1;
+    }
+    static constexpr int TR = 1;
+    // State after the transfer x; past the term the occupancy is 0.
+    __device__ __forceinline__ void advance(const double (&x)[FLOW_TR]) { occ *= x[0]; }
+    __device__ __forceinline__ void past(int t)
+    {
+        if (t > S) occ = 0.0;
     }
     template <bool MASK>
     __device__ __forceinline__ double step(int t, const FlowIn &in)
@@ -156,7 +188,7 @@ struct FlowVector {
     double o00, o01, o10, carry, cf[6], d;
     PatWalk pat;
 
-    __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int shift, int t0)
+    __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int, int shift, int t0)
     {
         S = L.S;
         qa = P.qoff1[L.slot] + P.age1[L.slot] + shift;
@@ -179,6 +211,31 @@ struct FlowVector {
     {
         in.x1 = shocked(in.x1, m);
         in.x2 = shocked(in.x2, m);
+    }
+    // Transfer from state 00: survival of each life, then the arrivals in 10 and 01.
+    static constexpr int TR = LAST ? 4 : 3;
+    __device__ __forceinline__ static void tr_init(double (&x)[FLOW_TR])
+    {
+        x[0] = x[1] = 1.0;
+        x[2] = x[3] = 0.0;
+    }
+    __device__ __forceinline__ static void tr_step(double (&x)[FLOW_TR], const FlowIn &in)
+    {
+        const double w = x[0] * x[1];
+        x[2] = fma(x[2], in.x2, w * ((1.0 - in.x1) * in.x2));
+        if constexpr (LAST) x[3] = fma(x[3], in.x1, w * (in.x1 * (1.0 - in.x2)));
+        x[0] *= in.x1;
+        x[1] *= in.x2;
+    }
+    __device__ __forceinline__ void advance(const double (&x)[FLOW_TR])
+    {
+        o10 = fma(o10, x[1], o00 * x[2]);
+        if constexpr (LAST) o01 = fma(o01, x[0], o00 * x[3]);
+        o00 *= x[0] * x[1];
+    }
+    __device__ __forceinline__ void past(int t)
+    {
+        if (t > S) o00 = o01 = o10 = 0.0;
     }
     template <bool MASK>
     __device__ __forceinline__ double step(int t, const FlowIn &in)
@@ -216,10 +273,10 @@ struct FlowThree {
     bool last;
     double l1, l2, l3, carry, a0all, a0, a1;
 
-    __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int shift, bool is_last)
+    __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int kind, int shift, int)
     {
         S = L.S;
-        last = is_last;
+        last = kind == KIND_LAST;
         qa = P.qoff1[L.slot] + P.age1[L.slot] + shift;
         qb = P.qoff2[L.slot] + P.age2[L.slot] + shift;
         qc = P.qoff3[L.slot] + P.age3[L.slot] + shift;
@@ -242,6 +299,24 @@ struct FlowThree {
         in.x1 = shocked(in.x1, m);
         in.x2 = shocked(in.x2, m);
         in.x3 = shocked(in.x3, m);
+    }
+    static constexpr int TR = 3;
+    __device__ __forceinline__ static void tr_init(double (&x)[FLOW_TR]) { x[0] = x[1] = x[2] = 1.0; }
+    __device__ __forceinline__ static void tr_step(double (&x)[FLOW_TR], const FlowIn &in)
+    {
+        x[0] *= in.x1;
+        x[1] *= in.x2;
+        x[2] *= in.x3;
+    }
+    __device__ __forceinline__ void advance(const double (&x)[FLOW_TR])
+    {
+        l1 *= x[0];
+        l2 *= x[1];
+        l3 *= x[2];
+    }
+    __device__ __forceinline__ void past(int t)
+    {
+        if (t > S) l1 = l2 = l3 = 0.0;
     }
     template <bool MASK>
     __device__ __forceinline__ double step(int t, const FlowIn &in)
@@ -269,7 +344,7 @@ struct FlowMarkov {
     const double *wb;
     double occ[M], c[M], carry, a0;
 
-    __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int shift)
+    __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int, int shift, int)
     {
         S = L.S;
         a0 = P.coef[L.slot];
@@ -298,10 +373,20 @@ struct FlowMarkov {
         double n[M];
 #pragma unroll
         for (int j = 0; j < M; ++j) n[j] = occ[0] * w[j];
+        if constexpr (M <= 4) {
 #pragma unroll
-        for (int i = 1; i < M; ++i)
+            for (int i = 1; i < M; ++i)
 #pragma unroll
-            for (int j = 0; j < M; ++j) n[j] = fma(occ[i], w[i * M + j], n[j]);
+                for (int j = 0; j < M; ++j) n[j] = fma(occ[i], w[i * M + j], n[j]);
+        } else {   // a row at a time (the occupancies move down one place per row): few registers
+#pragma unroll 1
+            for (int i = 1; i < M; ++i) {
+#pragma unroll
+                for (int j = 0; j + 1 < M; ++j) occ[j] = occ[j + 1];
+#pragma unroll
+                for (int j = 0; j < M; ++j) n[j] = fma(occ[0], w[i * M + j], n[j]);
+            }
+        }
         double arr = 0.0;
 #pragma unroll
         for (int j = 0; j < M; ++j) {
@@ -318,9 +403,9 @@ struct FlowMarkov {
 template <bool LDSQ, bool TWO>
 struct FlowFrac {
     int S, qa, qb;
-    double occ, a0, pay, f, g;
+    double occ, a0, pay, f, g, mid;
 
-    __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int shift)
+    __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int, int shift, int)
     {
         S = L.S;
         qa = P.qoff1[L.slot] + P.age1[L.slot] + shift;
@@ -343,167 +428,177 @@ struct FlowFrac {
         in.x1 = shocked(in.x1, m);
         if constexpr (TWO) in.x2 = shocked(in.x2, m);
     }
-    // f_t; the flow within the month goes to *mid.
-    __device__ __forceinline__ double step(int t, const FlowIn &in, double *mid)
+    static constexpr int TR = 1;
+    __device__ __forceinline__ static void tr_init(double (&x)[FLOW_TR]) { x[0] = 1.0; }
+    __device__ __forceinline__ static void tr_step(double (&x)[FLOW_TR], const FlowIn &in)
     {
-        if (t >= S) occ = 0.0;
+        x[0] *= TWO ? in.x1 * in.x2 : in.x1;
+    }
+    __device__ __forceinline__ void advance(const double (&x)[FLOW_TR]) { occ *= x[0]; }
+    __device__ __forceinline__ void past(int t)
+    {
+        if (t > S) occ = 0.0;
+    }
+    // f_t; the flow within the month goes to mid.
+    template <bool MASK>
+    __device__ __forceinline__ double step(int t, const FlowIn &in)
+    {
+        if (MASK && t >= S) occ = 0.0;
         const double pf = TWO ? fma(f, in.x1, g) * fma(f, in.x2, g) : fma(f, in.x1, g);
-        *mid = occ * (pf * pay);
+        mid = occ * (pf * pay);
         const double out = occ * a0;
         occ *= TWO ? in.x1 * in.x2 : in.x1;
         return out;
     }
 };
 
-// Walk of one tile at one node from t = 0 to its last flow (t = smax): emit(u,
-// flow) for each step of a block of U consecutive steps starting at t, then
-// done(t) once per block.  The table values of a block are all loaded before
-// its first step.  Steps past the tile's last load its last month's values
-// again and return 0.
-template <int U, class W, class Emit, class Done>
-__device__ __forceinline__ void flow_walk(const RecParams &P, const double *__restrict__ lq, W &w, double m,
-                                          int smax, int smin, Emit emit, Done done)
+// Walk of J tiles of one model (64 slots apart) at one node over the steps
+// [t0, t1), t0 a multiple of U: emit(t, flow) for each step of a block of U
+// consecutive steps, the flows of the J tiles added in order, then done(t + U)
+// once per block.  Blocks are whole: steps past the last flow give
+// 0.  The walkers stand at step t0 (or, `lead`, at t0 - 1: that step is taken
+// first and its flow dropped, so that the amounts it leaves for t0 are there).
+// smax: the last flow's time; every lane of every tile lives past smin.
+template <int U, int J, class W, class Emit, class Done>
+__device__ __forceinline__ void flow_walk(const RecParams &P, const double *__restrict__ lq, W (&w)[J], double m,
+                                          int smax, int smin, int t0, int t1, bool lead, Emit emit, Done done)
 {
     const bool shock = m != 1.0;
-    FlowIn a[U];
-    auto fetch = [&](int t) {
+    if (lead) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) a[u] = w.load(P, lq, min(t + u, smax - 1));
-    };
-    fetch(0);
-    for (int t = 0; t <= smax; t += U) {
-        FlowIn b[U];
+        for (int j = 0; j < J; ++j) {
+            FlowIn a = w[j].load(P, lq, min(t0 - 1, smax - 1));
+            if (shock) w[j].shock(a, m);
+            (void)w[j].template step<true>(t0 - 1, a);
+        }
+    }
+    int t = t0;
+    for (; t + U <= min(smin, t1); t += U) {
+        FlowIn a[J][U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) b[u] = a[u];
-        if (t + U <= smax) fetch(t + U);
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+            for (int u = 0; u < U; ++u) a[j][u] = w[j].load(P, lq, t + u);
         if (shock) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) w.shock(b[u], m);
-        }
-        if (t + U <= smin) {
+            for (int j = 0; j < J; ++j)
 #pragma unroll
-            for (int u = 0; u < U; ++u) emit(u, w.template step<false>(t + u, b[u]));
-        } else {
-#pragma unroll
-            for (int u = 0; u < U; ++u) emit(u, w.template step<true>(t + u, b[u]));
+                for (int u = 0; u < U; ++u) w[j].shock(a[j][u], m);
         }
-        done(t);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            double f = w[0].template step<false>(t + u, a[0][u]);
+#pragma unroll
+            for (int j = 1; j < J; ++j) f += w[j].template step<false>(t + u, a[j][u]);
+            emit(t + u, f);
+        }
+        done(t + U);
     }
-}
-
-// Dispatch of a tile's model: emit(u, flow) and done(t) as for flow_walk;
-// emit_mid(u, flow) receives the second flow of fractional tiles (before done).
-// SPECIAL: the portfolio has tiles other than level ones.  VEC: it has vector
-// models.  smin is 0 where some lane of the tile is padding or expired.
-template <int U, bool LDSQ, bool VEC, bool SPECIAL, class Emit, class EmitMid, class Done>
-__device__ __forceinline__ void flow_tile(const RecParams &P, const double *__restrict__ lq, const Tile &T,
-                                          int shift, double m, int lane, Emit emit, EmitMid emit_mid,
-                                          Done done)
-{
-    FlowLane L;
-    L.init(P, T, shift, lane);
-    const int smax = T.smax - shift;
-    const int smin = __ballot(!L.live) ? 0 : T.smin - shift;
-    auto walk = [&](auto &w) { flow_walk<U>(P, lq, w, m, smax, smin, emit, done); };
-    if constexpr (SPECIAL) {
-        if (T.flow == FLOW_PATTERN) {
-            if (T.kind == KIND_SINGLE) {
-                FlowScalar<LDSQ, false, FLOW_PATTERN> w;
-                w.init(P, L, shift, 0);
-                walk(w);
-            } else if (T.kind == KIND_JOINT) {
-                FlowScalar<LDSQ, true, FLOW_PATTERN> w;
-                w.init(P, L, shift, 0);
-                walk(w);
-            } else if (T.kind == KIND_REV) {
-                FlowVector<LDSQ, false, true> w;
-                w.init(P, L, shift, 0);
-                walk(w);
-            } else {
-                FlowVector<LDSQ, true, true> w;
-                w.init(P, L, shift, 0);
-                walk(w);
-            }
-            return;
-        }
-        if (T.flow == FLOW_TABLE) {
-            FlowScalar<LDSQ, false, FLOW_TABLE> w;
-            w.init(P, L, shift, 0);
-            walk(w);
-            return;
-        }
-        if (T.flow == FLOW_THREE) {
-            FlowThree<LDSQ> w;
-            w.init(P, L, shift, T.kind == KIND_LAST);
-            walk(w);
-            return;
-        }
-        if (T.flow == FLOW_MARKOV) {
-            auto run = [&](auto &w) {
-                w.init(P, L, shift);
-                for (int t = 0; t <= smax; t += U) {
 #pragma unroll 1
-                    for (int u = 0; u < U; ++u) emit(u, w.step(t + u));
-                    done(t);
-                }
-            };
-            if (P.mk_states > 4) {
-                FlowMarkov<MAX_MK_STATES> w;
-                run(w);
-            } else {
-                FlowMarkov<4> w;
-                run(w);
-            }
-            return;
-        }
-        if (T.flow == FLOW_FRAC) {
-            auto run = [&](auto &w) {
-                w.init(P, L, shift);
-                for (int t = 0; t <= smax; t += U) {
-                    FlowIn a[U];
+    for (; t < t1; t += U) {
+        FlowIn a[J][U];
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        a[u] = w.load(P, lq, min(t + u, smax - 1));
-                        if (m != 1.0) w.shock(a[u], m);
-                    }
+        for (int j = 0; j < J; ++j)
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        double mid;
-                        emit(u, w.step(t + u, a[u], &mid));
-                        emit_mid(u, mid);
-                    }
-                    done(t);
-                }
-            };
-            if (T.kind == KIND_JOINT) {
-                FlowFrac<LDSQ, true> w;
-                run(w);
-            } else {
-                FlowFrac<LDSQ, false> w;
-                run(w);
-            }
-            return;
+            for (int u = 0; u < U; ++u) a[j][u] = w[j].load(P, lq, min(t + u, smax - 1));
+        if (shock) {
+#pragma unroll
+            for (int j = 0; j < J; ++j)
+#pragma unroll
+                for (int u = 0; u < U; ++u) w[j].shock(a[j][u], m);
         }
-    }
-    if (T.kind == KIND_SINGLE) {
-        FlowScalar<LDSQ, false, FLOW_LEVEL> w;
-        w.init(P, L, shift, 0);
-        walk(w);
-    } else if (T.kind == KIND_JOINT) {
-        FlowScalar<LDSQ, true, FLOW_LEVEL> w;
-        w.init(P, L, shift, 0);
-        walk(w);
-    } else if constexpr (VEC) {
-        if (T.kind == KIND_REV) {
-            FlowVector<LDSQ, false, false> w;
-            w.init(P, L, shift, 0);
-            walk(w);
-        } else {
-            FlowVector<LDSQ, true, false> w;
-            w.init(P, L, shift, 0);
-            walk(w);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            double f = w[0].template step<true>(t + u, a[0][u]);
+#pragma unroll
+            for (int j = 1; j < J; ++j) f += w[j].template step<true>(t + u, a[j][u]);
+            emit(t + u, f);
         }
+        done(t + U);
     }
 }
 
+// The transfer of a walker over the steps [t0, t1).
+template <class W>
+__device__ __forceinline__ void flow_transfer(const RecParams &P, const double *__restrict__ lq, const W &w, double m,
+                                              int smax, int t0, int t1, double (&x)[FLOW_TR])
+{
+    constexpr int U = 8;
+    W::tr_init(x);
+    for (int t = t0; t < t1; t += U) {
+        FlowIn a[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) a[u] = w.load(P, lq, min(t + u, smax - 1));
+        if (m != 1.0) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) w.shock(a[u], m);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (t + u < t1) W::tr_step(x, a[u]);
+    }
+}
+
+// Calls visit(walker type tag) for the tile's model, where the tag's type W is
+// tag.w's.  Markov tiles are visited with FlowMarkov.
+template <class W>
+struct FlowTag {
+    typedef W type;
+};
+
+// Tiles a kernel instance can hold: level ones only; payment patterns too; every kind.
+enum FlowSet : int { FLOWS_LEVEL = 0, FLOWS_PATTERN = 1, FLOWS_ALL = 2 };
+
+template <bool LDSQ, bool VEC, int SET, class Visit>
+__device__ __forceinline__ void flow_model(const RecParams &P, int kind, int flow, Visit visit)
+{
+    if constexpr (SET >= FLOWS_PATTERN) {
+        if (flow == FLOW_PATTERN) {
+            if (kind == KIND_SINGLE) visit(FlowTag<FlowScalar<LDSQ, false, FLOW_PATTERN>>{});
+            else if (kind == KIND_JOINT) visit(FlowTag<FlowScalar<LDSQ, true, FLOW_PATTERN>>{});
+            else if (kind == KIND_REV) visit(FlowTag<FlowVector<LDSQ, false, true>>{});
+            else visit(FlowTag<FlowVector<LDSQ, true, true>>{});
+            return;
+        }
+    }
+    if constexpr (SET >= FLOWS_ALL) {
+        if (flow == FLOW_TABLE) {
+            visit(FlowTag<FlowScalar<LDSQ, false, FLOW_TABLE>>{});
+            return;
+        }
+        if (flow == FLOW_THREE) {
+            visit(FlowTag<FlowThree<LDSQ>>{});
+            return;
+        }
+        if (flow == FLOW_MARKOV) {
+            if (P.mk_states > 4) visit(FlowTag<FlowMarkov<MAX_MK_STATES>>{});
+            else visit(FlowTag<FlowMarkov<4>>{});
+            return;
+        }
+        if (flow == FLOW_FRAC) {
+            if (kind == KIND_JOINT) visit(FlowTag<FlowFrac<LDSQ, true>>{});
+            else visit(FlowTag<FlowFrac<LDSQ, false>>{});
+            return;
+        }
+    }
+    if (kind == KIND_SINGLE) visit(FlowTag<FlowScalar<LDSQ, false, FLOW_LEVEL>>{});
+    else if (kind == KIND_JOINT) visit(FlowTag<FlowScalar<LDSQ, true, FLOW_LEVEL>>{});
+    else if constexpr (VEC) {
+        if (kind == KIND_REV) visit(FlowTag<FlowVector<LDSQ, false, false>>{});
+        else visit(FlowTag<FlowVector<LDSQ, true, false>>{});
+    }
+}
+
+template <class W>
+struct FlowTraits {
+    static constexpr bool markov = false, frac = false;
+};
+template <int M>
+struct FlowTraits<FlowMarkov<M>> {
+    static constexpr bool markov = true, frac = false;
+};
+template <bool LDSQ, bool TWO>
+struct FlowTraits<FlowFrac<LDSQ, TWO>> {
+    static constexpr bool markov = false, frac = true;
+};
 }  // namespace rr

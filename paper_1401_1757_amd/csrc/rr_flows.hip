@@ -3,79 +3,174 @@
 // R_t = F_t + v_t R_{t+1} of that one sequence per scenario.
 #include "rr_flows.h"
 
+#include <algorithm>
+#include <type_traits>
+
 namespace rr {
 
-constexpr int FLOW_U = 8;                  // steps per block of a walk
+constexpr int FLOW_U = 4;                  // steps loaded together
+constexpr int FLOW_BLK = 8;                // steps per row reduction; rows are whole blocks
 constexpr int FLOW_WAVES = 8;              // wavefronts per workgroup
 constexpr int FLOW_ROW = 65;               // stage rows: 65 doubles apart, 8 columns per lane on distinct banks
-constexpr int FLOW_STAGE = FLOW_U * FLOW_ROW;
+constexpr int FLOW_STAGE = FLOW_BLK * FLOW_ROW;
 constexpr int FLOW_RED = 64;               // rows per workgroup of the row reduction
 
-// Sums over the policies of the tiles g, g + R, ... of a node, one row of
-// row_len doubles per wavefront (unit = node * R + g).  A block of eight steps
-// passes through the wavefront's LDS stage: lane l adds eight lanes' flows of
-// step l % 8, three exchanges add the eight parts, in a fixed order.  A later
-// tile of the wavefront adds to the row it wrote before.
+// x + the value of the lane 16 (32) away, by the row-swap instructions: both
+// outputs of a swap of x with itself, added.
+__device__ __forceinline__ double add_across_16(double x)
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(x), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(x), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ double add_across_32(double x)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(x), __double2loint(x), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(x), __double2hiint(x), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
+// A wavefront's row: flows of the 64 lanes pass through its LDS stage in
+// blocks of eight steps; lane l adds eight lanes' flows of step l % 8, three
+// exchanges add the eight parts, in a fixed order.  A later walk adds to what
+// an earlier one wrote.  Only that branch waits for memory: a wait for the old
+// values of every block would also wait for the store of the block before
+// (four times the walk's time).
+struct FlowRow {
+    double *stage, *dst;
+    int have;   // length written so far
+
+    __device__ __forceinline__ void put(int t, double x, int lane) { stage[(t & (FLOW_BLK - 1)) * FLOW_ROW + lane] = x; }
+    // After the last step of the block that ends before t.
+    __device__ __forceinline__ void flush(int t, int lane)
+    {
+        __builtin_amdgcn_wave_barrier();
+        const double *p = stage + (lane & 7) * FLOW_ROW + (lane >> 3) * 8;
+        double s = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+        s += dpp_f64<0x128>(s);   // row_ror:8: the lane 8 away
+        s = add_across_32(add_across_16(s));
+        if (lane < FLOW_BLK) {
+            double *o = dst + (t - FLOW_BLK) + lane;
+            if (t <= have) s += *o;
+            *o = s;
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+};
+
+// Rows of summed flows, row_len doubles each: row g of a node (grid: rows x
+// nodes) takes the tiles g, g + R, ...  CHUNKS wavefronts share a row, a time
+// chunk each, since the serial walk over hundreds of months is what a run waits
+// for: they exchange their chunks' transfers first and then walk from the state
+// these lead to.  A workgroup holds FLOW_WAVES / CHUNKS rows and one copy of the
+// survival tables.  Every wavefront passes the same barriers whatever its tile's model.
 //
-// Bound by vector issue and LDS: per policy-month one or two table reads, one
-// stage write and read and about ten FP64 operations.
-template <bool LDSQ, bool VEC, bool SPECIAL>
-__global__ void __launch_bounds__(64 * FLOW_WAVES, 2)
-k_flow_sums(RecParams P, int node_begin, int node_count, int R, int row_len, int table_doubles,
-            double *__restrict__ rows, double *__restrict__ rows_mid)
+// Bound by vector issue: per policy-month the table reads, about ten FP64
+// operations and two multiplications for the transfer.  See flow_shape for the
+// split and its figures.
+template <bool LDSQ, bool VEC, int SET, int CHUNKS>
+__global__ void __launch_bounds__(64 * FLOW_WAVES, 4)
+k_flow_sums(RecParams P, int node_begin, int R, int row_len, int table_doubles, double *__restrict__ rows,
+            double *__restrict__ rows_mid)
 {
     extern __shared__ double s_mem[];
+    const int node = node_begin + blockIdx.y;
+    double m = P.shock[node];
     if constexpr (LDSQ) {
-        for (int i = threadIdx.x; i < P.n_q; i += 64 * FLOW_WAVES) s_mem[i] = P.q[i];
+        flow_stage_tables(P, s_mem, m, 64 * FLOW_WAVES);
+        m = 1.0;   // the staged values are the node's own
         __syncthreads();
     }
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int unit = wave_uniform(blockIdx.x * FLOW_WAVES + wave);
-    if (unit >= node_count * R) return;
-    double *stage = s_mem + table_doubles + wave * FLOW_STAGE * (SPECIAL ? 2 : 1);
-    double *stage_mid = stage + FLOW_STAGE;
-    const int node = node_begin + unit / R, g = unit % R;
+    const int wave = wave_uniform(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    constexpr int SUB = FLOW_WAVES / CHUNKS;
+    const int chunk = wave % CHUNKS, wave0 = wave - chunk;
+    const int g = blockIdx.x * SUB + wave / CHUNKS;
+    const size_t unit = (size_t)blockIdx.y * R + min(g, R - 1);
     const int shift = node * P.node_step;
-    const double m = P.shock[node];
-    double *row = rows + (size_t)unit * row_len;
-    double *row_mid = SPECIAL && rows_mid ? rows_mid + (size_t)unit * row_len : nullptr;
-    int have = 0, have_mid = 0;   // length written so far
-    const int u = lane & 7, j = lane >> 3;
-    auto flush = [&](const double *st, double *dst, int t, int got) {
-        __builtin_amdgcn_wave_barrier();
-        double s = 0.0;
+    double *stage0 = s_mem + table_doubles;
+    double (*s_tr)[FLOW_TR][64] = reinterpret_cast<double (*)[FLOW_TR][64]>(stage0);   // before the stages' use
+    FlowRow row, mid;
+    row.stage = stage0 + wave * FLOW_STAGE * (SET == FLOWS_ALL ? 2 : 1);
+    row.dst = rows + unit * row_len;
+    mid.stage = row.stage + FLOW_STAGE;
+    mid.dst = rows_mid + unit * row_len;
+    row.have = mid.have = 0;
+    int done = 0, done_mid = 0;   // length of the row's longest tile so far
+    for (int tile0 = 0; tile0 < P.n_tiles; tile0 += R) {
+        const int tile = tile0 + g;
+        const bool any = g < R && tile < P.n_tiles;
+        const int at = any ? tile : 0;
+        const int smax = wave_uniform(P.tiles[at].smax) - shift;
+        // Between a row's tiles: the stages are free again, and the next tile adds
+        // to what the row's wavefronts wrote.
+        if (tile0 > 0) __syncthreads();
+        if (!any || smax <= 0) {   // nothing to walk: only the two barriers
+            __syncthreads();
+            __syncthreads();
+            continue;
+        }
+        const int kind = wave_uniform(P.tiles[at].kind), flow = wave_uniform(P.tiles[at].flow);
+        int smin = wave_uniform(P.tiles[at].smin) - shift;
+        FlowLane L;
+        L.init(P, wave_uniform(P.tiles[at].first) + lane, shift);
+        if (__ballot(!L.live)) smin = 0;
+        const int len = (smax / FLOW_BLK + 1) * FLOW_BLK;
+        const int per = ((len / FLOW_BLK + CHUNKS - 1) / CHUNKS) * FLOW_BLK;
+        flow_model<LDSQ, VEC, SET>(P, kind, flow, [&](auto tag) {
+            typedef typename decltype(tag)::type W;
+            typedef FlowTraits<W> X;
+            // Markov tiles: one wavefront walks all of it
+            const int t0 = X::markov ? (chunk == 0 ? 0 : len) : min(chunk * per, len);
+            const int t1 = X::markov ? len : min(t0 + per, len);
+            const bool lead = t0 > 0;
+            const int s0 = lead ? t0 - 1 : t0;   // first step walked
+            W w[1];
+            w[0].init(P, L, kind, shift, s0);
+            if constexpr (!X::markov) {
+                double x[FLOW_TR];
+                flow_transfer(P, s_mem, w[0], m, smax, s0, t1 > t0 && t1 < len ? t1 - 1 : s0, x);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) s += st[u * FLOW_ROW + j * 8 + i];
-        s += __shfl_xor(s, 8);
-        s += __shfl_xor(s, 16);
-        s += __shfl_xor(s, 32);
-        if (lane < FLOW_U) dst[t + lane] = t < got ? dst[t + lane] + s : s;
-        __builtin_amdgcn_wave_barrier();
-    };
-    for (int tile = g; tile < P.n_tiles; tile += R) {
-        Tile T = P.tiles[tile];
-        T.kind = wave_uniform(T.kind);
-        T.first = wave_uniform(T.first);
-        T.smax = wave_uniform(T.smax);
-        T.smin = wave_uniform(T.smin);
-        T.flow = wave_uniform(T.flow);
-        const int smax = T.smax - shift;
-        if (smax <= 0) continue;
-        const bool mid = SPECIAL && row_mid != nullptr && T.flow == FLOW_FRAC;
-        flow_tile<FLOW_U, LDSQ, VEC, SPECIAL>(
-            P, s_mem, T, shift, m, lane, [&](int k, double x) { stage[k * FLOW_ROW + lane] = x; },
-            [&](int k, double x) { if (SPECIAL) stage_mid[k * FLOW_ROW + lane] = x; },
-            [&](int t) {
-                flush(stage, row, t, have);
-                if (mid) flush(stage_mid, row_mid, t, have_mid);
-            });
-        const int len = (smax / FLOW_U + 1) * FLOW_U;
-        have = max(have, len);
-        if (mid) have_mid = max(have_mid, len);
+                for (int i = 0; i < W::TR; ++i) s_tr[wave][i][lane] = x[i];
+                __syncthreads();
+                for (int c = 0; c < chunk; ++c) {
+#pragma unroll
+                    for (int i = 0; i < W::TR; ++i) x[i] = s_tr[wave0 + c][i][lane];
+                    w[0].advance(x);
+                }
+                w[0].past(s0);
+            } else {
+                __syncthreads();
+            }
+            __syncthreads();   // transfers read: the stages may be written
+            row.have = done;
+            mid.have = done_mid;
+            if (t0 >= t1) return;
+            if constexpr (X::markov) {
+                for (int t = t0; t < t1; ++t) {
+                    row.put(t, w[0].step(t), lane);
+                    if ((t & (FLOW_BLK - 1)) == FLOW_BLK - 1) row.flush(t + 1, lane);
+                }
+            } else {
+                flow_walk<FLOW_U, 1>(
+                    P, s_mem, w, m, smax, smin, t0, t1, lead,
+                    [&](int t, double f) {
+                        row.put(t, f, lane);
+                        if constexpr (X::frac) mid.put(t, w[0].mid, lane);
+                    },
+                    [&](int t) {
+                        if (t & (FLOW_BLK - 1)) return;
+                        row.flush(t, lane);
+                        if constexpr (X::frac) mid.flush(t, lane);
+                    });
+            }
+        });
+        done = max(done, len);
+        if (flow == FLOW_FRAC) done_mid = max(done_mid, len);
     }
-    for (int t = have + lane; t < row_len; t += 64) row[t] = 0.0;
-    if (row_mid)
-        for (int t = have_mid + lane; t < row_len; t += 64) row_mid[t] = 0.0;
+    if (g >= R || chunk > 0) return;
+    for (int t = done + lane; t < row_len; t += 64) row.dst[t] = 0.0;
+    if (SET == FLOWS_ALL && rows_mid != nullptr)
+        for (int t = done_mid + lane; t < row_len; t += 64) mid.dst[t] = 0.0;
 }
 
 // out[node][chunk][t] = sum of the node's rows of the chunk, in a fixed order.
@@ -187,22 +282,26 @@ k_flow_totals(RecParams P, const double *__restrict__ sums, const double *__rest
 // ---------------------------------------------------------------------------
 // Sizes and launches
 // ---------------------------------------------------------------------------
-// Rows of a launch: enough wavefronts for four per SIMD, and at most 24 MiB of
-// rows whatever the portfolio's size (a wavefront then takes several tiles).
+// Rows of a launch: one per tile, at most 48 MiB of them (past that a row takes
+// several tiles; less where the scratch also holds the totals, at 8 bytes each).
 // Sizes follow from the run alone, so every entry point adds in the same order.
-constexpr int FLOW_MAX_ROWS = 4096;
-constexpr size_t FLOW_ROW_BYTES = (size_t)24 << 20;
+constexpr size_t FLOW_ROW_BYTES = (size_t)48 << 20;
+// Up to this many (node, tile) pairs a tile's months are cut in eight, past it
+// in four (fewer transfers).
+constexpr int FLOW_SPLIT_TILES = 1024;
 
-FlowShape flow_shape(int node_count, int n_tiles, int max_term, bool has_mid)
+FlowShape flow_shape(int node_count, int n_tiles, int max_term, bool has_mid, size_t own_totals)
 {
     FlowShape f;
-    f.row_len = (max_term / FLOW_U + 1) * FLOW_U;
-    const size_t cap = FLOW_ROW_BYTES / ((size_t)f.row_len * 8 * (has_mid ? 2 : 1));
-    const int rows = (int)(cap < (size_t)FLOW_MAX_ROWS ? cap : (size_t)FLOW_MAX_ROWS);
-    f.nodes = node_count < rows ? node_count : (rows > 0 ? rows : 1);
-    const int most = rows / f.nodes > 0 ? rows / f.nodes : 1;
-    const int per = (n_tiles + most - 1) / most;   // tiles per wavefront
+    f.row_len = (max_term / FLOW_BLK + 1) * FLOW_BLK;
+    const size_t taken = std::min(own_totals * sizeof(double), (size_t)36 << 20);
+    const size_t cap = (FLOW_ROW_BYTES - taken) / ((size_t)f.row_len * 8 * (has_mid ? 2 : 1));
+    const int rows = (int)std::max<size_t>(1, std::min<size_t>(cap, 1 << 20));
+    f.nodes = std::min({node_count, rows, 65535});
+    const int most = rows / f.nodes;
+    const int per = (n_tiles + most - 1) / most;   // tiles per row
     f.R = (n_tiles + per - 1) / per;
+    f.chunks = (long long)node_count * n_tiles <= FLOW_SPLIT_TILES ? 8 : 4;
     f.chunk_rows = f.R > 16 * FLOW_RED ? (f.R + 15) / 16 : FLOW_RED;
     f.n_chunks = f.R <= 8 ? 0 : (f.R + f.chunk_rows - 1) / f.chunk_rows;
     const size_t rows_d = (size_t)f.nodes * f.R * f.row_len;
@@ -212,35 +311,38 @@ FlowShape flow_shape(int node_count, int n_tiles, int max_term, bool has_mid)
 }
 
 // LDS of the sums kernel and of the totals kernel, in bytes.
-static size_t sums_lds(const RecParams &p, bool special)
+static size_t sums_lds(const RecParams &p, int set)
 {
     return ((p.q_in_lds ? (size_t)(p.n_q + 1) / 2 * 2 : 0) +
-            (size_t)FLOW_WAVES * FLOW_STAGE * (special ? 2 : 1)) * sizeof(double);
+            (size_t)FLOW_WAVES * FLOW_STAGE * (set == FLOWS_ALL ? 2 : 1)) * sizeof(double);
 }
 
-bool flow_fits(const FlowShape &f, const RecParams &p, bool special, bool has_mid, size_t lds_per_block)
+bool flow_fits(const FlowShape &f, const RecParams &p, int set, bool has_mid, size_t lds_per_block)
 {
-    // 16 KiB of the totals kernel's LDS is its static part
-    return sums_lds(p, special) <= lds_per_block &&
+    // 16 KiB of the totals kernel's LDS are its static part
+    return sums_lds(p, set) <= lds_per_block &&
            (size_t)f.row_len * 8 * (has_mid ? 2 : 1) + (size_t)(16 << 10) <= lds_per_block;
 }
 
-template <bool LDSQ>
-static void launch_sums(const RecParams &p, const FlowShape &f, bool special, int node_begin, int nodes,
+template <bool LDSQ, int CHUNKS>
+static void launch_sums(const RecParams &p, const FlowShape &f, int set, int node_begin, int nodes,
                         double *rows, double *rows_mid, hipStream_t s)
 {
-    const dim3 g((nodes * f.R + FLOW_WAVES - 1) / FLOW_WAVES), b(64 * FLOW_WAVES);
-    const size_t lds = sums_lds(p, special);
+    constexpr int SUB = FLOW_WAVES / CHUNKS;   // rows per workgroup
+    const dim3 g((f.R + SUB - 1) / SUB, nodes), b(64 * FLOW_WAVES);
+    const size_t lds = sums_lds(p, set);
     const int td = p.q_in_lds ? (p.n_q + 1) / 2 * 2 : 0;
-    if (special)
-        hipLaunchKernelGGL((k_flow_sums<LDSQ, true, true>), g, b, lds, s, p, node_begin, nodes, f.R, f.row_len, td, rows, rows_mid);
-    else if (p.has_vector)
-        hipLaunchKernelGGL((k_flow_sums<LDSQ, true, false>), g, b, lds, s, p, node_begin, nodes, f.R, f.row_len, td, rows, rows_mid);
-    else
-        hipLaunchKernelGGL((k_flow_sums<LDSQ, false, false>), g, b, lds, s, p, node_begin, nodes, f.R, f.row_len, td, rows, rows_mid);
+#define RR_SUMS(VEC, SET) \
+    hipLaunchKernelGGL((k_flow_sums<LDSQ, VEC, SET, CHUNKS>), g, b, lds, s, p, node_begin, f.R, \
+                       f.row_len, td, rows, rows_mid)
+    if (set == FLOWS_ALL) RR_SUMS(true, FLOWS_ALL);
+    else if (set == FLOWS_PATTERN) RR_SUMS(true, FLOWS_PATTERN);
+    else if (p.has_vector) RR_SUMS(true, FLOWS_LEVEL);
+    else RR_SUMS(false, FLOWS_LEVEL);
+#undef RR_SUMS
 }
 
-hipError_t launch_flow_totals(const RecParams &p, int node_count, const FlowShape &f, bool special, bool has_mid,
+hipError_t launch_flow_totals(const RecParams &p, int node_count, const FlowShape &f, int set, bool has_mid,
                               bool safe_curves, int max_term, double *scratch, double *totals, hipStream_t s)
 {
     const size_t rows_d = (size_t)f.nodes * f.R * f.row_len;
@@ -251,8 +353,13 @@ hipError_t launch_flow_totals(const RecParams &p, int node_count, const FlowShap
     for (int k = 0; k < node_count; k += f.nodes) {
         const int nodes = node_count - k < f.nodes ? node_count - k : f.nodes;
         const int nb = p.node_begin + k;
-        if (p.q_in_lds) launch_sums<true>(p, f, special, nb, nodes, rows, rows_mid, s);
-        else launch_sums<false>(p, f, special, nb, nodes, rows, rows_mid, s);
+        auto launch = [&](auto ldsq) {
+            constexpr bool L = decltype(ldsq)::value;
+            if (f.chunks == 8) launch_sums<L, 8>(p, f, set, nb, nodes, rows, rows_mid, s);
+            else launch_sums<L, 4>(p, f, set, nb, nodes, rows, rows_mid, s);
+        };
+        if (p.q_in_lds) launch(std::true_type{});
+        else launch(std::false_type{});
         const double *src = rows, *src_mid = rows_mid;
         int n_sums = f.R;
         if (f.n_chunks > 0) {

@@ -1029,8 +1029,9 @@ extern "C" int rr_portfolio_upload(rr_ctx *c, const rr_portfolio *p)
     // the cash flows of table slots, amount x table value, month-major over
     // the table tiles' slots (padding slots: 0).
     c->has_flow = c->has_frac = false;
-    c->max_term = 0;
+    c->max_term = c->flow_set = 0;
     for (const Tile &T : tiles) {
+        c->flow_set = std::max(c->flow_set, T.flow == FLOW_LEVEL ? 0 : (T.flow == FLOW_PATTERN ? 1 : 2));
         c->has_flow |= T.flow != FLOW_LEVEL;
         c->has_frac |= T.flow == FLOW_FRAC;
         c->max_term = std::max(c->max_term, T.smax);
@@ -1469,6 +1470,13 @@ static bool unpinned(const rr_ctx *c)
     return !c->opt_k && !c->opt_j && !c->opt_wg && c->opt_xcd == 1 && c->opt_ring == 0 && c->opt_curve_share == -1;
 }
 
+static FlowShape run_flow_shape(const rr_ctx *c, const rr_run *run)
+{
+    const bool own = (run->out_mask & (RR_OUT_TOTALS | RR_OUT_STATS)) == RR_OUT_STATS;
+    return flow_shape(run->node_count, c->n_tiles, c->max_term, c->has_frac,
+                      own ? (size_t)run->node_count * run->scen_count : 0);
+}
+
 // The cash-flow kernels' LDS holds the run's tables and rows.
 static bool flow_ok(rr_ctx *c, const rr_run *run)
 {
@@ -1477,8 +1485,8 @@ static bool flow_ok(rr_ctx *c, const rr_run *run)
     memset(&none, 0, sizeof none);
     rr_run r = *run;
     r.out_mask = 0;
-    return flow_fits(flow_shape(run->node_count, c->n_tiles, c->max_term, c->has_frac),
-                     make_params(c, &r, &none, &pl, nullptr), c->has_flow, c->has_frac, c->lds_per_block);
+    return flow_fits(run_flow_shape(c, run),
+                     make_params(c, &r, &none, &pl, nullptr), c->flow_set, c->has_frac, c->lds_per_block);
 }
 
 static int enqueue_run(rr_ctx *c, const rr_run *run, const rr_outputs *out, Plan *pl,
@@ -1510,14 +1518,18 @@ static int enqueue_run(rr_ctx *c, const rr_run *run, const rr_outputs *out, Plan
 // Whether the run's totals come from the policies' summed cash flows instead
 // of the per-policy chains: runs that ask for no per-policy output.  The sum
 // costs one policy-month of work per policy and month whatever the number of
-// scenarios; the chains cost that per scenario, and win nowhere: one scenario
-// 100,000 policies 0.031 against 0.055 ms, 500 scenarios x 60 nodes x 10,000
-// policies 0.12 against 2.56 ms.  A pinned launch shape or queue mode asks for
-// the recurrence kernel itself.
+// scenarios, the chains cost that per scenario.  Chains against sums: 10,000
+// policies x 60 nodes x 500 scenarios 2.49 / 0.115 ms, 1,000 x 1,000 scenarios
+// 0.090 / 0.040 ms, 5,003 x 13 0.063 / 0.034 ms, 1,000 x 1 0.021 / 0.020 ms; a
+// large book on one scenario has the same number of policy-months either way
+// and pays for the rows (100,000 x 1: 0.054 / 0.073 ms), so one scenario of more
+// than 512 tiles keeps the chains.  A pinned launch shape or queue mode asks
+// for the recurrence kernel itself.
 static bool flow_totals_run(rr_ctx *c, const rr_run *run)
 {
     if (run->out_mask & (RR_OUT_R0 | RR_OUT_PATH)) return false;
     if (!(run->out_mask & (RR_OUT_TOTALS | RR_OUT_STATS)) || c->n_user == 0) return false;
+    if (run->scen_count == 1 && (long long)c->n_tiles * run->node_count > 512) return false;
     return unpinned(c) && flow_ok(c, run);
 }
 
@@ -1529,8 +1541,8 @@ static int enqueue_flow_totals(rr_ctx *c, const rr_run *run, const rr_outputs *o
     std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
     int rc;
     if (timed && (rc = begin_timed(c, s, &ev))) return rc;
-    HIPCHK(c, launch_flow_totals(P, run->node_count, flow_shape(run->node_count, c->n_tiles, c->max_term, c->has_frac),
-                                 c->has_flow, c->has_frac, c->curve_log_span <= kSafeLogSpan, c->max_term, work,
+    HIPCHK(c, launch_flow_totals(P, run->node_count, run_flow_shape(c, run),
+                                 c->flow_set, c->has_frac, c->curve_log_span <= kSafeLogSpan, c->max_term, work,
                                  totals, s));
     if (timed && (rc = end_timed(c, s, ev))) return rc;
     return enqueue_stats(c, run, out, totals, s);
@@ -1842,7 +1854,7 @@ extern "C" int rr_reserve_recurrence(rr_ctx *c, const rr_run *run, const rr_outp
     }
     int rc;
     if (flow_totals_run(c, run)) {
-        const size_t need = flow_shape(run->node_count, c->n_tiles, c->max_term, c->has_frac).scratch_doubles;
+        const size_t need = run_flow_shape(c, run).scratch_doubles;
         if (need > c->flow_work.n) drop_graphs(c);
         HIPCHK(c, c->flow_work.alloc(need));
         note_flow_launch(c);
@@ -1954,8 +1966,8 @@ extern "C" int rr_reserve_recurrence_noalloc(rr_ctx *c, const rr_run *run, const
     }
     if (flow_totals_run(c, run)) {
         // Totals (if they are not the caller's) first, then the cash-flow rows:
-        // at most 59 of the 64 MiB for any run that the limit above admits.
-        const FlowShape f = flow_shape(run->node_count, c->n_tiles, c->max_term, c->has_frac);
+        // together within the 64 MiB for any run that the limit above admits.
+        const FlowShape f = run_flow_shape(c, run);
         const long long o_work = own_tot ? (ns + 31) / 32 * 32 : 0;
         if (own_tot) totals = S;
         if (o_work + (long long)f.scratch_doubles <= cap) {

@@ -165,17 +165,20 @@ struct FlowShape {
     int row_len;        // doubles per row: times 0 .. longest term, whole blocks
     int R;              // rows (wavefronts) per node
     int nodes;          // nodes per launch
+    int chunks;         // wavefronts per row, a time chunk each
     int chunk_rows, n_chunks;   // row reduction (n_chunks 0: the totals kernel adds the rows)
     size_t scratch_doubles;
 };
 // max_term: longest remaining term of the portfolio at node 0; has_mid: some
-// tile is fractional (a second flow per month).
-FlowShape flow_shape(int node_count, int n_tiles, int max_term, bool has_mid);
-// special: some tile is not a level one.  Whether the kernels' LDS suffices.
-bool flow_fits(const FlowShape &f, const RecParams &p, bool special, bool has_mid, size_t lds_per_block);
+// tile is fractional (a second flow per month); own_totals: totals that need
+// scratch too (the caller asks for statistics only).
+FlowShape flow_shape(int node_count, int n_tiles, int max_term, bool has_mid, size_t own_totals);
+// set: the kinds of tiles the portfolio has (0 level ones only, 1 payment
+// patterns too, 2 others).  Whether the kernels' LDS suffices.
+bool flow_fits(const FlowShape &f, const RecParams &p, int set, bool has_mid, size_t lds_per_block);
 // totals[node][scen] of the run in p (its node_begin, scen_begin, scen_count);
 // safe_curves: no product of a run's discount factors leaves the FP64 range.
-hipError_t launch_flow_totals(const RecParams &p, int node_count, const FlowShape &f, bool special, bool has_mid,
+hipError_t launch_flow_totals(const RecParams &p, int node_count, const FlowShape &f, int set, bool has_mid,
                               bool safe_curves, int max_term, double *scratch, double *totals, hipStream_t s);
 hipError_t launch_fill(double *dst, long long n, double value, hipStream_t stream);
 hipError_t launch_fill_int(int *dst, int n, int value, hipStream_t stream);
