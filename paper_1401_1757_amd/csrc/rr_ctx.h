@@ -137,6 +137,8 @@ struct rr_ctx {
     std::vector<double> vas_r0_host;     // their values (the last generation's)
     int n_ages_stage = 0;
     std::vector<double> shock_host;
+    DevBuf<double> disc;                 // [n_nodes][disc_rows][scen_pad] discount products of v
+    bool has_disc = false;               // disc holds the present curves' products
     double curve_log_span = 0.0;         // bound on |log| of any product of one scenario's factors
 
     // portfolio
@@ -169,6 +171,9 @@ struct rr_ctx {
     DevBuf<double> mk_w;                  // [model][mk_ages][4][4] ([9][9] above 4 states)
     DevBuf<double> mk_c;                  // [model][9] benefits per unit amount
     DevBuf<Tile> tiles;
+    DevBuf<int> tile_order;               // tiles, longest remaining term first
+    DevBuf<int> tile_base;                // [n_tiles + 1] first month of each tile's kept flows
+    std::vector<int> tile_base_host;
     int gen = 0;                          // bumps on every upload
     long long curve_gen = 0;              // bumps whenever the curve values change (uploads
                                           // and in-place regeneration)
@@ -180,7 +185,7 @@ struct rr_ctx {
     DevBuf<int> counters;
     DevBuf<double> partial;
     DevBuf<double> totals_tmp;
-    DevBuf<double> flow_work;             // rows and sums of the summed-cash-flow totals
+    DevBuf<double> flow_work;             // rows and sums of the summed cash flows, kept flows
     DevBuf<long long> path_off;
     int path_off_node = -1, path_off_step = -1, path_off_gen = -1;
     std::map<PlanKey, std::unique_ptr<Plan>> plans;

@@ -65,13 +65,16 @@ struct FlowRow {
 // these lead to.  A workgroup holds FLOW_WAVES / CHUNKS rows and one copy of the
 // survival tables.  Every wavefront passes the same barriers whatever its tile's model.
 //
+// With `st` the flows themselves are kept too (or, without rows, only), for
+// k_reserve_mm: one line of 64 policies a month.
+//
 // Bound by vector issue: per policy-month the table reads, about ten FP64
 // operations and two multiplications for the transfer.  See flow_shape for the
 // split and its figures.
 template <bool LDSQ, bool VEC, int SET, int CHUNKS>
 __global__ void __launch_bounds__(64 * FLOW_WAVES, 4)
 k_flow_sums(RecParams P, int node_begin, int R, int row_len, int table_doubles, double *__restrict__ rows,
-            double *__restrict__ rows_mid)
+            double *__restrict__ rows_mid, FlowStore st)
 {
     extern __shared__ double s_mem[];
     const int node = node_begin + blockIdx.y;
@@ -96,14 +99,14 @@ k_flow_sums(RecParams P, int node_begin, int R, int row_len, int table_doubles, 
     mid.dst = rows_mid + unit * row_len;
     row.have = mid.have = 0;
     int done = 0, done_mid = 0;   // length of the row's longest tile so far
-    for (int tile0 = 0; tile0 < P.n_tiles; tile0 += R) {
+    for (int tile0 = st.tile_begin; tile0 < st.tile_end; tile0 += R) {
         const int tile = tile0 + g;
-        const bool any = g < R && tile < P.n_tiles;
+        const bool any = g < R && tile < st.tile_end;
         const int at = any ? tile : 0;
         const int smax = wave_uniform(P.tiles[at].smax) - shift;
         // Between a row's tiles: the stages are free again, and the next tile adds
         // to what the row's wavefronts wrote.
-        if (tile0 > 0) __syncthreads();
+        if (tile0 > st.tile_begin) __syncthreads();
         if (!any || smax <= 0) {   // nothing to walk: only the two barriers
             __syncthreads();
             __syncthreads();
@@ -116,6 +119,8 @@ k_flow_sums(RecParams P, int node_begin, int R, int row_len, int table_doubles, 
         if (__ballot(!L.live)) smin = 0;
         const int len = (smax / FLOW_BLK + 1) * FLOW_BLK;
         const int per = ((len / FLOW_BLK + CHUNKS - 1) / CHUNKS) * FLOW_BLK;
+        double *keep = nullptr;   // the lane's kept flows, month t at keep[64 t]
+        if (st.flows) keep = st.flows + ((size_t)blockIdx.y * st.node_months + (P.tile_base[tile] - st.month_begin)) * 64 + lane;
         flow_model<LDSQ, VEC, SET>(P, kind, flow, [&](auto tag) {
             typedef typename decltype(tag)::type W;
             typedef FlowTraits<W> X;
@@ -147,18 +152,25 @@ k_flow_sums(RecParams P, int node_begin, int R, int row_len, int table_doubles, 
             if (t0 >= t1) return;
             if constexpr (X::markov) {
                 for (int t = t0; t < t1; ++t) {
-                    row.put(t, w[0].step(t), lane);
+                    const double f = w[0].step(t);
+                    if (keep) keep[(size_t)t * 64] = f;
+                    if (!rows) continue;
+                    row.put(t, f, lane);
                     if ((t & (FLOW_BLK - 1)) == FLOW_BLK - 1) row.flush(t + 1, lane);
                 }
             } else {
                 flow_walk<FLOW_U, 1>(
                     P, s_mem, w, m, smax, smin, t0, t1, lead,
                     [&](int t, double f) {
-                        row.put(t, f, lane);
-                        if constexpr (X::frac) mid.put(t, w[0].mid, lane);
+                        if (keep) keep[(size_t)t * 64] = f;
+                        if (rows) row.put(t, f, lane);
+                        if constexpr (X::frac) {
+                            if (keep) keep[(size_t)t * 64 + st.mid] = w[0].mid;
+                            if (rows) mid.put(t, w[0].mid, lane);
+                        }
                     },
                     [&](int t) {
-                        if (t & (FLOW_BLK - 1)) return;
+                        if ((t & (FLOW_BLK - 1)) || !rows) return;
                         row.flush(t, lane);
                         if constexpr (X::frac) mid.flush(t, lane);
                     });
@@ -167,7 +179,7 @@ k_flow_sums(RecParams P, int node_begin, int R, int row_len, int table_doubles, 
         done = max(done, len);
         if (flow == FLOW_FRAC) done_mid = max(done_mid, len);
     }
-    if (g >= R || chunk > 0) return;
+    if (g >= R || chunk > 0 || !rows) return;
     for (int t = done + lane; t < row_len; t += 64) row.dst[t] = 0.0;
     if (SET == FLOWS_ALL && rows_mid != nullptr)
         for (int t = done_mid + lane; t < row_len; t += 64) mid.dst[t] = 0.0;
@@ -325,16 +337,16 @@ bool flow_fits(const FlowShape &f, const RecParams &p, int set, bool has_mid, si
 }
 
 template <bool LDSQ, int CHUNKS>
-static void launch_sums(const RecParams &p, const FlowShape &f, int set, int node_begin, int nodes,
-                        double *rows, double *rows_mid, hipStream_t s)
+static void launch_sums(const RecParams &p, int R, int row_len, int set, int node_begin, int nodes,
+                        double *rows, double *rows_mid, const FlowStore &st, hipStream_t s)
 {
     constexpr int SUB = FLOW_WAVES / CHUNKS;   // rows per workgroup
-    const dim3 g((f.R + SUB - 1) / SUB, nodes), b(64 * FLOW_WAVES);
+    const dim3 g((R + SUB - 1) / SUB, nodes), b(64 * FLOW_WAVES);
     const size_t lds = sums_lds(p, set);
     const int td = p.q_in_lds ? (p.n_q + 1) / 2 * 2 : 0;
 #define RR_SUMS(VEC, SET) \
-    hipLaunchKernelGGL((k_flow_sums<LDSQ, VEC, SET, CHUNKS>), g, b, lds, s, p, node_begin, f.R, \
-                       f.row_len, td, rows, rows_mid)
+    hipLaunchKernelGGL((k_flow_sums<LDSQ, VEC, SET, CHUNKS>), g, b, lds, s, p, node_begin, R, row_len, td, rows, \
+                       rows_mid, st)
     if (set == FLOWS_ALL) RR_SUMS(true, FLOWS_ALL);
     else if (set == FLOWS_PATTERN) RR_SUMS(true, FLOWS_PATTERN);
     else if (p.has_vector) RR_SUMS(true, FLOWS_LEVEL);
@@ -342,9 +354,33 @@ static void launch_sums(const RecParams &p, const FlowShape &f, int set, int nod
 #undef RR_SUMS
 }
 
-hipError_t launch_flow_totals(const RecParams &p, int node_count, const FlowShape &f, int set, bool has_mid,
-                              bool safe_curves, int max_term, double *scratch, double *totals, hipStream_t s)
+// The walk over the tiles of st (all of them for rows) at `nodes` nodes.
+static void launch_flow_walk(const RecParams &p, const FlowShape &f, int set, int node_begin, int nodes, double *rows,
+                             double *rows_mid, const FlowStore &st, hipStream_t s)
 {
+    const int R = rows ? f.R : st.tile_end - st.tile_begin;
+    auto launch = [&](auto ldsq) {
+        constexpr bool L = decltype(ldsq)::value;
+        if (f.chunks == 8) launch_sums<L, 8>(p, R, f.row_len, set, node_begin, nodes, rows, rows_mid, st, s);
+        else launch_sums<L, 4>(p, R, f.row_len, set, node_begin, nodes, rows, rows_mid, st, s);
+    };
+    if (p.q_in_lds) launch(std::true_type{});
+    else launch(std::false_type{});
+}
+
+hipError_t launch_flow_store(const RecParams &p, const FlowShape &f, int set, bool has_mid, int node_begin, int nodes,
+                             const FlowStore &st, double *totals_scratch, hipStream_t s)
+{
+    double *rows = totals_scratch, *mid = nullptr;
+    if (rows && has_mid) mid = rows + (size_t)f.nodes * (f.R + f.n_chunks) * f.row_len;
+    launch_flow_walk(p, f, set, node_begin, nodes, rows, mid, st, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_flow_totals(const RecParams &p, int node_count, const FlowShape &f, int set, bool has_mid,
+                              bool safe_curves, bool kept, int max_term, double *scratch, double *totals, hipStream_t s)
+{
+    const FlowStore none{nullptr, 0, 0, 0, 0, p.n_tiles};
     const size_t rows_d = (size_t)f.nodes * f.R * f.row_len;
     const size_t sums_d = (size_t)f.nodes * f.n_chunks * f.row_len;
     double *rows = scratch, *sums = rows + rows_d;
@@ -353,13 +389,7 @@ hipError_t launch_flow_totals(const RecParams &p, int node_count, const FlowShap
     for (int k = 0; k < node_count; k += f.nodes) {
         const int nodes = node_count - k < f.nodes ? node_count - k : f.nodes;
         const int nb = p.node_begin + k;
-        auto launch = [&](auto ldsq) {
-            constexpr bool L = decltype(ldsq)::value;
-            if (f.chunks == 8) launch_sums<L, 8>(p, f, set, nb, nodes, rows, rows_mid, s);
-            else launch_sums<L, 4>(p, f, set, nb, nodes, rows, rows_mid, s);
-        };
-        if (p.q_in_lds) launch(std::true_type{});
-        else launch(std::false_type{});
+        if (!kept) launch_flow_walk(p, f, set, nb, nodes, rows, rows_mid, none, s);
         const double *src = rows, *src_mid = rows_mid;
         int n_sums = f.R;
         if (f.n_chunks > 0) {

@@ -562,6 +562,22 @@ static int enqueue_vasicek(rr_ctx *c, const VasParams &P, const std::vector<doub
     return RR_OK;
 }
 
+// Discount products of the installed curves, kept beside them (8 bytes per
+// curve value): formed where no product can leave the FP64 range and the
+// memory is there; without them runs take the recurrence kernel.
+static int enqueue_discounts(rr_ctx *c)
+{
+    c->has_disc = false;
+    if (!(c->curve_log_span <= kSafeLogSpan)) return RR_OK;
+    if (c->disc.alloc((size_t)c->n_nodes * disc_rows(c->n_steps) * c->scen_pad) != hipSuccess) {
+        (void)hipGetLastError();
+        return RR_OK;
+    }
+    HIPCHK(c, launch_discounts(c->v.p, c->n_nodes, c->n_steps, c->scen_pad, c->disc.p, c->stream));
+    c->has_disc = true;
+    return RR_OK;
+}
+
 // Shared tail of rr_basis_upload and rr_basis_generate_vasicek: install the
 // checked mortality part and the sizes, then the curves from the host copy
 // `v` (scenario-major) or from the generator.
@@ -626,6 +642,7 @@ static int install_basis(rr_ctx *c, const rr_basis *b, std::vector<double> &q,
         HIPCHK(c, c->vf.alloc((size_t)nvv));
         HIPCHK(c, launch_pow_curves(c->v.p, c->vf.p, nvv, c->frac, c->stream));
     }
+    if ((rc = enqueue_discounts(c))) return rc;
     HIPCHK(c, c->shock.alloc((size_t)b->n_nodes));
     HIPCHK(c, hipMemcpy(c->shock.p, c->shock_host.data(), sizeof(double) * b->n_nodes,
                         hipMemcpyHostToDevice));
@@ -696,7 +713,8 @@ extern "C" int rr_curves_generate_vasicek(rr_ctx *c, const rr_vasicek *vs)
     const double span = vasicek_log_span(P, r0);
     if ((span <= kSafeLogSpan) != (c->curve_log_span <= kSafeLogSpan)) drop_graphs(c);   // other kernels
     c->curve_log_span = span;
-    return enqueue_vasicek(c, P, r0, c->v.p, 1, nullptr);
+    if ((rc = enqueue_vasicek(c, P, r0, c->v.p, 1, nullptr))) return rc;
+    return enqueue_discounts(c);
 }
 
 extern "C" int rr_vasicek_curves(rr_ctx *c, const rr_vasicek *vs, int32_t n_nodes, int32_t n_scen,
@@ -1025,6 +1043,17 @@ extern "C" int rr_portfolio_upload(rr_ctx *c, const rr_portfolio *p)
     if ((rc = upload_vec(c, c->uidx, s_uidx))) return rc;
     if ((rc = upload_vec(c, c->coef, coef))) return rc;
     if ((rc = upload_vec(c, c->tiles, tiles))) return rc;
+    std::vector<int> by_term(tiles.size());
+    std::iota(by_term.begin(), by_term.end(), 0);
+    std::stable_sort(by_term.begin(), by_term.end(), [&](int a, int b) { return tiles[a].smax > tiles[b].smax; });
+    if ((rc = upload_vec(c, c->tile_order, by_term))) return rc;
+    c->tile_base_host.assign(1, 0);
+    long long months = 0;
+    for (const Tile &T : tiles) {
+        months += (T.smax / DISC_BLOCK + 1) * DISC_BLOCK;
+        c->tile_base_host.push_back((int)std::min<long long>(months, 1 << 30));   // (then no flows are kept)
+    }
+    if ((rc = upload_vec(c, c->tile_base, c->tile_base_host))) return rc;
     // Payment patterns of the slots (level slots: g = 1, anniversary 12) and
     // the cash flows of table slots, amount x table value, month-major over
     // the table tiles' slots (padding slots: 0).
@@ -1389,6 +1418,9 @@ static RecParams make_params(rr_ctx *c, const rr_run *run, const rr_outputs *out
     P.n_pad = c->n_pad;
     P.n_user = c->n_user;
     P.tiles = c->tiles.p;
+    P.tile_order = c->tile_order.p;
+    P.tile_base = c->tile_base.p;
+    P.disc = !c->v_override && c->has_disc ? c->disc.p : nullptr;
     P.n_tiles = c->n_tiles;
     P.has_vector = 0;
     for (const Tile &T : c->tiles_host) P.has_vector |= (T.kind == KIND_REV || T.kind == KIND_LAST);
@@ -1533,17 +1565,85 @@ static bool flow_totals_run(rr_ctx *c, const rr_run *run)
     return unpinned(c) && flow_ok(c, run);
 }
 
-static int enqueue_flow_totals(rr_ctx *c, const rr_run *run, const rr_outputs *out, double *work,
-                               double *totals, hipStream_t s, bool timed)
+// Largest share of a tile's kept flows: sixteen thousand months.
+constexpr long long kFlowTileDoubles = 1LL << 21;
+
+// Whether the run's per-policy reserves come from the matrix product of the
+// policies' flows and the discount products: state-0 reserves of two scenarios
+// or more.
+static bool flow_reserves_run(rr_ctx *c, const rr_run *run)
+{
+    if (!(run->out_mask & RR_OUT_R0) || (run->out_mask & (RR_OUT_PATH | RR_OUT_ALL_STATES))) return false;
+    if (c->n_user == 0 || !c->has_disc || c->v_override) return false;
+    if (run->scen_count < 2) return false;
+    if ((long long)(c->max_term + DISC_BLOCK) * 128 > kFlowTileDoubles || c->tile_base_host.back() >= (1 << 30)) return false;
+    return unpinned(c) && flow_ok(c, run);
+}
+
+static bool flow_run(rr_ctx *c, const rr_run *run) { return flow_totals_run(c, run) || flow_reserves_run(c, run); }
+
+// Scratch of a run by cash flows, in doubles: the totals' rows, then room for
+// kept flows (the whole run's or, past `most`, a batch of it).
+static void flow_work(const rr_ctx *c, const rr_run *run, long long most, long long *totals, long long *kept)
+{
+    *totals = run->out_mask & (RR_OUT_TOTALS | RR_OUT_STATS) ? (long long)run_flow_shape(c, run).scratch_doubles : 0;
+    *kept = 0;
+    if (!(run->out_mask & RR_OUT_R0)) return;
+    const long long node = (long long)c->tile_base_host.back() * 64 * (c->has_frac ? 2 : 1);
+    *kept = std::min(node * run->node_count, std::max(most - *totals, kFlowTileDoubles));
+}
+
+// The run by cash flows: reserves (if asked for), totals, statistics.  work:
+// flow_work's two parts, one after the other.
+static int enqueue_flow_run(rr_ctx *c, const rr_run *run, const rr_outputs *out, double *work, long long kept,
+                            double *totals, hipStream_t s, bool timed)
 {
     Plan pl;   // no work lists
     const RecParams P = make_params(c, run, out, &pl, nullptr);
+    const FlowShape f = run_flow_shape(c, run);
     std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
     int rc;
     if (timed && (rc = begin_timed(c, s, &ev))) return rc;
-    HIPCHK(c, launch_flow_totals(P, run->node_count, run_flow_shape(c, run),
-                                 c->flow_set, c->has_frac, c->curve_log_span <= kSafeLogSpan, c->max_term, work,
-                                 totals, s));
+    bool have_rows = false;
+    if (P.r0) {
+        const int streams = c->has_frac ? 2 : 1;
+        const int months = c->tile_base_host.back();
+        FlowStore st;
+        st.flows = work + (totals ? f.scratch_doubles : 0);
+        const long long room = kept / (64 * streams);   // months
+        if (months <= room) {
+            // Whole nodes; where all of them fit, one walk serves the totals too.
+            const int per = (int)std::min<long long>({room / months, run->node_count, 65535});
+            st.node_months = months;
+            st.month_begin = st.tile_begin = 0;
+            st.tile_end = c->n_tiles;
+            st.mid = (long long)per * months * 64;
+            have_rows = totals && per == run->node_count && f.nodes == per && f.R == c->n_tiles;
+            for (int k = 0; k < run->node_count; k += per) {
+                const int nodes = std::min(per, run->node_count - k);
+                HIPCHK(c, launch_flow_store(P, f, c->flow_set, c->has_frac, P.node_begin + k, nodes, st,
+                                            have_rows ? work : nullptr, s));
+                HIPCHK(c, launch_reserve_mm(P, P.node_begin + k, nodes, c->has_frac, st, s));
+            }
+        } else {
+            for (int k = 0; k < run->node_count; ++k)
+                for (int t0 = 0; t0 < c->n_tiles;) {
+                    int t1 = t0 + 1;
+                    while (t1 < c->n_tiles && c->tile_base_host[t1 + 1] - c->tile_base_host[t0] <= room) ++t1;
+                    st.tile_begin = t0;
+                    st.tile_end = t1;
+                    st.month_begin = c->tile_base_host[t0];
+                    st.node_months = c->tile_base_host[t1] - c->tile_base_host[t0];
+                    st.mid = (long long)st.node_months * 64;
+                    HIPCHK(c, launch_flow_store(P, f, c->flow_set, c->has_frac, P.node_begin + k, 1, st, nullptr, s));
+                    HIPCHK(c, launch_reserve_mm(P, P.node_begin + k, 1, c->has_frac, st, s));
+                    t0 = t1;
+                }
+        }
+    }
+    if (totals)
+        HIPCHK(c, launch_flow_totals(P, run->node_count, f, c->flow_set, c->has_frac,
+                                     c->curve_log_span <= kSafeLogSpan, have_rows, c->max_term, work, totals, s));
     if (timed && (rc = end_timed(c, s, ev))) return rc;
     return enqueue_stats(c, run, out, totals, s);
 }
@@ -1853,14 +1953,16 @@ extern "C" int rr_reserve_recurrence(rr_ctx *c, const rr_run *run, const rr_outp
         return RR_OK;
     }
     int rc;
-    if (flow_totals_run(c, run)) {
-        const size_t need = run_flow_shape(c, run).scratch_doubles;
-        if (need > c->flow_work.n) drop_graphs(c);
-        HIPCHK(c, c->flow_work.alloc(need));
+    if (flow_run(c, run)) {
+        long long need, kept;
+        flow_work(c, run, 1LL << 25, &need, &kept);   // flows of 256 MiB at a time
+        need += kept;
+        if ((size_t)need > c->flow_work.n) drop_graphs(c);
+        HIPCHK(c, c->flow_work.alloc((size_t)need));
         note_flow_launch(c);
         return launch_graphed(c, run_key(c, run, out, {1, (uint64_t)(uintptr_t)c->flow_work.p, (uint64_t)(uintptr_t)totals}),
                               [&](hipStream_t s, bool timed) {
-                                  return enqueue_flow_totals(c, run, out, c->flow_work.p, totals, s, timed);
+                                  return enqueue_flow_run(c, run, out, c->flow_work.p, kept, totals, s, timed);
                               });
     }
     double *partial = nullptr;
@@ -1964,15 +2066,16 @@ extern "C" int rr_reserve_recurrence_noalloc(rr_ctx *c, const rr_run *run, const
         if (mask & RR_OUT_STATS) HIPCHK(c, launch_fill(out->stats, 2LL * run->node_count, 0.0, st));
         return RR_OK;
     }
-    if (flow_totals_run(c, run)) {
+    if (flow_run(c, run)) {
         // Totals (if they are not the caller's) first, then the cash-flow rows:
         // together within the 64 MiB for any run that the limit above admits.
-        const FlowShape f = run_flow_shape(c, run);
         const long long o_work = own_tot ? (ns + 31) / 32 * 32 : 0;
+        long long need, kept;
+        flow_work(c, run, cap - o_work, &need, &kept);
         if (own_tot) totals = S;
-        if (o_work + (long long)f.scratch_doubles <= cap) {
+        if (o_work + need + kept <= cap) {
             note_flow_launch(c);
-            return enqueue_flow_totals(c, run, out, S + o_work, totals, st, false);
+            return enqueue_flow_run(c, run, out, S + o_work, kept, totals, st, false);
         }
         if (own_tot) totals = S + o_tot;
     }

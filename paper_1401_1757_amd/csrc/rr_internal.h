@@ -77,6 +77,10 @@ struct Item {
     int count;     // consecutive tiles of one model in the item (1..J)
 };
 
+// Rows per node of the discount products: months 0 .. n_steps in whole blocks.
+constexpr int DISC_BLOCK = 8;
+__host__ __device__ constexpr int disc_rows(int n_steps) { return (n_steps / DISC_BLOCK + 1) * DISC_BLOCK; }
+
 struct RecParams {
     // basis
     const double *q;          // [n_tables][n_ages_stage] one-step survival p = 1 - q
@@ -88,6 +92,7 @@ struct RecParams {
     int n_steps;
     int scen_pad;
     const double *shock;      // [n_nodes]: multiplier on q (1.0 when none)
+    const double *disc;       // [n_nodes][disc_rows(n_steps)][scen_pad] discount products, or null
     // portfolio, sorted and padded to whole tiles
     const int *age1;          // attained age at node 0 (padding: 0)
     const int *age2;
@@ -114,6 +119,8 @@ struct RecParams {
     int ring_off;             // curve-ring launches: first double of the rings in LDS
     int path_lds;             // path output: first double of the wavefronts' stages in LDS
     const Tile *tiles;
+    const int *tile_order;    // [n_tiles] tiles, longest remaining term first
+    const int *tile_base;     // [n_tiles + 1] first month of a tile's kept flows (whole blocks of 8)
     int n_tiles;
     // work
     const Item *items;
@@ -178,8 +185,29 @@ FlowShape flow_shape(int node_count, int n_tiles, int max_term, bool has_mid, si
 bool flow_fits(const FlowShape &f, const RecParams &p, int set, bool has_mid, size_t lds_per_block);
 // totals[node][scen] of the run in p (its node_begin, scen_begin, scen_count);
 // safe_curves: no product of a run's discount factors leaves the FP64 range.
+// kept: the rows are there already (launch_flow_store with the same scratch).
 hipError_t launch_flow_totals(const RecParams &p, int node_count, const FlowShape &f, int set, bool has_mid,
-                              bool safe_curves, int max_term, double *scratch, double *totals, hipStream_t s);
+                              bool safe_curves, bool kept, int max_term, double *scratch, double *totals,
+                              hipStream_t s);
+// Kept cash flows of tiles [tile_begin, tile_end) at some nodes: 64 doubles a
+// month, node k's from month k * node_months, a tile's from tile_base[tile] -
+// month_begin; flows within the month `mid` doubles further on.
+struct FlowStore {
+    double *flows;
+    long long mid;
+    int node_months, month_begin, tile_begin, tile_end;
+};
+// Fill st; with totals_scratch (all tiles and f.nodes nodes) the rows of
+// launch_flow_totals as well.
+hipError_t launch_flow_store(const RecParams &p, const FlowShape &f, int set, bool has_mid, int node_begin, int nodes,
+                             const FlowStore &st, double *totals_scratch, hipStream_t s);
+// Discount products of the curves (rr_reserve_mm.hip): D[node][t][scen_pad], t =
+// 0 .. n_steps, then zeros to a whole block of months.
+hipError_t launch_discounts(const double *v, int n_nodes, int n_steps, int scen_pad, double *D, hipStream_t s);
+// r0[node][policy][scen] (state 0) of st's tiles at nodes node_begin .. + nodes - 1
+// as a matrix product of their kept flows and p.disc.
+hipError_t launch_reserve_mm(const RecParams &p, int node_begin, int nodes, bool has_mid, const FlowStore &st,
+                             hipStream_t s);
 hipError_t launch_fill(double *dst, long long n, double value, hipStream_t stream);
 hipError_t launch_fill_int(int *dst, int n, int value, hipStream_t stream);
 hipError_t launch_transpose_curves(const double *src, double *dst, int n_nodes, int n_scen,

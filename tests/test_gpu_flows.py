@@ -168,3 +168,81 @@ def test_totals_on_curves_whose_products_leave_the_range(ctx, big):
     upload(ctx, w)
     _say(f"totals, factors {big}")
     check_totals(ctx, w)
+
+
+def check_reserves(ctx, w, node0=0, nnode=None, scen0=0, nscen=None, noalloc=False, totals=True):
+    b = w.basis
+    nnode = b.n_nodes - node0 if nnode is None else nnode
+    nscen = b.n_scen - scen0 if nscen is None else nscen
+    out = ctx.alloc_outputs(nnode, nscen, totals=totals, stats=True)
+    for x in out.values():
+        x.fill_(float("nan"))
+    call = ctx.reserve_recurrence_noalloc if noalloc else ctx.reserve_recurrence
+    call(node0, nnode, scen0, nscen, w.node_step_m, out)
+    torch.cuda.synchronize()
+    ref = oracle.reserves(b, w.portfolio, node0, nnode, scen0, nscen, w.node_step_m)
+    assert_reserves_close(to_np(out["r0"]), ref["r_all"][..., 0], ref["gross"])
+    if totals:
+        err = np.abs(to_np(out["totals"]) - ref["totals"])
+        assert np.all(err <= RTOL * np.maximum(ref["gross_totals"], 1e-300)), err.max()
+    return out
+
+
+@pytest.mark.parametrize("n,steps,scen,nodes", [(1, 1, 2, 1), (63, 31, 16, 1), (64, 32, 17, 2), (65, 33, 32, 3),
+                                                (200, 64, 33, 1), (700, 16, 130, 2), (450, 90, 64, 3),
+                                                (300, 140, 65, 2), (900, 260, 5, 2), (130, 100, 129, 1)])
+@pytest.mark.parametrize("special", [False, True])
+def test_reserves_every_kind(ctx, n, steps, scen, nodes, special):
+    w = every_kind(3 * n + steps + scen, n, steps, scen, nodes, special=special)
+    upload(ctx, w)
+    _say(f"reserves {n} policies x {nodes} x {scen}, {steps} steps, special={special}")
+    a = check_reserves(ctx, w)
+    b = check_reserves(ctx, w, noalloc=True)
+    assert all(torch.equal(a[k], b[k]) for k in a)
+    if nodes > 1:
+        check_reserves(ctx, w, node0=1, scen0=scen // 2, totals=False)
+
+
+@pytest.mark.parametrize("products", [(0,), (1, 8, 9), (2,), (3, 10), (12,), (13,)])
+def test_reserves_of_one_model(ctx, products):
+    w = every_kind(70 + products[0], 200, 100, 70, 2, products=products, special=False)
+    upload(ctx, w)
+    _say(f"reserves, products {products}")
+    check_reserves(ctx, w)
+
+
+def test_reserves_large_markov_and_device_tables(ctx):
+    w = every_kind(78, 600, 80, 70, 2, n_tables=12, states=9)
+    upload(ctx, w)
+    _say("reserves, nine-state models, tables in device memory")
+    check_reserves(ctx, w)
+
+
+def test_reserves_follow_regenerated_curves(ctx):
+    """The discount products kept beside the curves are those of the last
+    generation, through graph replays and a change of the start rates."""
+    rng = np.random.default_rng(12)
+    w = synth.random_small(rng, n=300, n_steps=120, n_scen=1, n_nodes=1)
+    vas = dict(a=synth.VAS_A, b=synth.VAS_B, sigma=synth.VAS_SIGMA, dt=1.0 / 12.0)
+    ctx.basis_generate_vasicek(w.basis.q, 70, 120, [0.03], key=(5, 6), **vas)
+    ctx.portfolio_upload(w.portfolio)
+    out = ctx.alloc_outputs(1, 70)
+    for r0, key in ((0.03, (5, 6)), (0.03, (5, 7)), (0.01, (9, 7)), (0.03, (5, 6))):
+        _say(f"generation {r0} {key}")
+        ctx.curves_generate_vasicek([r0], key=key, **vas)
+        ctx.reserve_recurrence(0, 1, 0, 70, 12, out)
+        torch.cuda.synchronize()
+        v, _ = oracle.vasicek_curves(r0=[r0], n_scen=70, n_steps=120, key=key, **vas)
+        ref = oracle.reserves(synth.Basis(q=w.basis.q, v=np.asarray(v).reshape(1, 70, 120)), w.portfolio, 0, 1, 0, 70)
+        assert_reserves_close(to_np(out["r0"]), ref["r_all"][..., 0], ref["gross"])
+
+
+@pytest.mark.parametrize("big", [1.0e4, 1.0e-4])
+def test_reserves_on_curves_whose_products_leave_the_range(ctx, big):
+    w = every_kind(32, 300, 160, 66, 1, special=False, shock=False)
+    v = w.basis.v
+    v[:, :, :60] = np.where(np.arange(60) % 2 == 0, big, 1.0 / big)
+    v[:, :, 60:] = 1.0 / big if big > 1 else big
+    upload(ctx, w)
+    _say(f"reserves, factors {big}")
+    check_reserves(ctx, w)
