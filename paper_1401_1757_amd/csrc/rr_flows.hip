@@ -119,8 +119,8 @@ k_flow_sums(RecParams P, int node_begin, int R, int row_len, int table_doubles, 
         if (__ballot(!L.live)) smin = 0;
         const int len = (smax / FLOW_BLK + 1) * FLOW_BLK;
         const int per = ((len / FLOW_BLK + CHUNKS - 1) / CHUNKS) * FLOW_BLK;
-        double *keep = nullptr;   // the lane's kept flows, month t at keep[64 t]
-        if (st.flows) keep = st.flows + ((size_t)blockIdx.y * st.node_months + (P.tile_base[tile] - st.month_begin)) * 64 + lane;
+        double *keep = nullptr;   // the lane's kept flows, month t at keep[64 t] (order: see FlowStore)
+        if (st.flows) keep = st.flows + ((size_t)blockIdx.y * st.node_months + (P.tile_base[tile] - st.month_begin)) * 64 + (lane & 15) * 4 + (lane >> 4);
         flow_model<LDSQ, VEC, SET>(P, kind, flow, [&](auto tag) {
             typedef typename decltype(tag)::type W;
             typedef FlowTraits<W> X;

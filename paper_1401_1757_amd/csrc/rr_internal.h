@@ -191,7 +191,8 @@ hipError_t launch_flow_totals(const RecParams &p, int node_count, const FlowShap
                               hipStream_t s);
 // Kept cash flows of tiles [tile_begin, tile_end) at some nodes: 64 doubles a
 // month, node k's from month k * node_months, a tile's from tile_base[tile] -
-// month_begin; flows within the month `mid` doubles further on.
+// month_begin; flows within the month `mid` doubles further on.  Lane l of the
+// tile is at (l % 16) * 4 + l / 16 of a month's 64.
 struct FlowStore {
     double *flows;
     long long mid;

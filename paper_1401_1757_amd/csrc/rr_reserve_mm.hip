@@ -8,6 +8,24 @@
 namespace rr {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
+// Two doubles moved by one 16-byte access, at 8-byte alignment.
+typedef double f64x2 __attribute__((ext_vector_type(2), aligned(8)));
+
+// N consecutive doubles, in 16-byte accesses where there are two or more.
+template <int N>
+__device__ __forceinline__ void load_run(double (&x)[N], const double *__restrict__ p)
+{
+    if constexpr (N == 1) {
+        x[0] = p[0];
+    } else {
+#pragma unroll
+        for (int i = 0; i < N; i += 2) {
+            const f64x2 v = *reinterpret_cast<const f64x2 *>(p + i);
+            x[i] = v[0];
+            x[i + 1] = v[1];
+        }
+    }
+}
 
 // ---------------------------------------------------------------------------
 // Discount products D[node][t][scen_pad], t = 0 .. n_steps, from the curves
@@ -92,7 +110,11 @@ __device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 c)
 // with its part of the reserves in accumulators.  Flows (one line of 64 a month)
 // and discount products (one line of scenarios a month) go straight from memory
 // into fragments, eight months ahead of their use; the workgroup's wavefronts
-// share their lines in the L1.  No LDS, no barriers.
+// share their lines in the L1.  No LDS, no barriers.  A lane's policies of all
+// fragments lie side by side in the kept flows, and its NB scenarios are
+// neighbours, so that every access is 16 bytes a lane: the L1 takes 16 cycles
+// for a wavefront's access of 8 bytes a lane as for one of 16, and with 8-byte
+// ones it, not the matrix pipe, was the limit (53 against 77 TFLOP/s).
 //
 // Bound by the FP64 matrix pipe.  The flows are made by a launch of their own:
 // a wavefront that makes them beside the multiplying ones waits for the matrix
@@ -117,14 +139,14 @@ k_reserve_mm(RecParams P, FlowStore st, int node_begin, int n_sb)
     static_assert(4 * G == 8, "a pipeline step is a block of kept flows");
     const int wc = wave % WC, wr = wave / WC;
     const int l16 = lane & 15, lk = lane >> 4;
-    const int col0 = (sb * WC + wc) * 16 * NB + l16;   // column of fragment 0 in the run
+    const int col0 = ((sb * WC + wc) * 16 + l16) * NB;   // the lane's first scenario in the run
     const int drow = P.scen_pad;
     const double *D = P.disc + (size_t)node * disc_rows(P.n_steps) * drow + P.scen_begin;
     const double *F = st.flows + ((size_t)blockIdx.y * st.node_months + (P.tile_base[tile] - st.month_begin)) * 64;
-    int off[NB];   // of the lane's element of a fragment of four months (past the run: not stored)
-#pragma unroll
-    for (int n = 0; n < NB; ++n) off[n] = lk * drow + min(col0 + 16 * n, P.scen_count - 1);
-    const int aoff = lk * 64 + wr * (16 * MB) + l16;
+    // The lane's elements of a fragment of four months.  Lanes past the run read
+    // its last scenario (and the one after: rows are padded) and store nothing.
+    const int boff = lk * drow + min(col0, P.scen_count - 1);
+    const int aoff = lk * 64 + l16 * 4 + wr * MB;
     f64x4 acc[MB][NB];
 #pragma unroll
     for (int i = 0; i < MB; ++i)
@@ -138,10 +160,8 @@ k_reserve_mm(RecParams P, FlowStore st, int node_begin, int n_sb)
 #pragma unroll
         for (int k = 0; k < G; ++k) {
             const double *fa = F + (size_t)(t + 4 * k) * 64, *db = D + (size_t)(t + 4 * k) * drow;
-#pragma unroll
-            for (int i = 0; i < MB; ++i) x.a[k][i] = fa[aoff + 16 * i];
-#pragma unroll
-            for (int n = 0; n < NB; ++n) x.b[k][n] = db[off[n]];
+            load_run<MB>(x.a[k], fa + aoff);
+            load_run<NB>(x.b[k], db + boff);
         }
     };
     auto multiply = [&](const Frags &x, int s) {
@@ -158,10 +178,10 @@ k_reserve_mm(RecParams P, FlowStore st, int node_begin, int n_sb)
                     const int row = min(t + lk, P.n_steps - 1) - lk;
 #pragma unroll
                     for (int n = 0; n < NB; ++n) {
-                        const double y = x.b[k][n] * vf[(ptrdiff_t)row * drow + off[n]];
+                        const double y = x.b[k][n] * vf[(ptrdiff_t)row * drow + boff + n];
 #pragma unroll
                         for (int i = 0; i < MB; ++i)
-                            acc[i][n] = mfma64(F[(size_t)t * 64 + st.mid + aoff + 16 * i], y, acc[i][n]);
+                            acc[i][n] = mfma64(F[(size_t)t * 64 + st.mid + aoff + i], y, acc[i][n]);
                     }
                 }
             }
@@ -192,10 +212,16 @@ k_reserve_mm(RecParams P, FlowStore st, int node_begin, int n_sb)
         for (int r = 0; r < 4; ++r) {
             const int uid = P.uidx[first + (wr * MB + i) * 16 + 4 * r + lk];
             if (uid < 0) continue;
-            double *o = out + (size_t)uid * P.scen_count;
+            double *o = out + (size_t)uid * P.scen_count + col0;
+            if constexpr (NB == 2) {
+                if (col0 + 1 < P.scen_count) {
+                    *reinterpret_cast<f64x2 *>(o) = f64x2{acc[i][0][r], acc[i][1][r]};
+                    continue;
+                }
+            }
 #pragma unroll
             for (int n = 0; n < NB; ++n)
-                if (col0 + 16 * n < P.scen_count) o[col0 + 16 * n] = acc[i][n][r];
+                if (col0 + n < P.scen_count) o[n] = acc[i][n][r];
         }
 }
 
