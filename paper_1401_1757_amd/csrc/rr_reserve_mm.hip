@@ -4,6 +4,7 @@
 #include "rr_flows.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace rr {
 
@@ -152,42 +153,35 @@ k_reserve_mm(RecParams P, FlowStore st, int node_begin, int n_sb)
     for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int n = 0; n < NB; ++n) acc[i][n] = f64x4{0.0, 0.0, 0.0, 0.0};
-    struct Frags {
-        double a[G][MB], b[G][NB];
-    };
-    auto load = [&](Frags &x, int s) {   // step s (the last one again past it: not used)
-        const int t = min(s, steps - 1) * 4 * G;
+    // The product over the flows at `fl`, with the discount products or (MID) for
+    // flows within the month with D_t v_t^f.
+    auto product = [&](const double *fl, auto mid) {
+        constexpr bool MID = decltype(mid)::value;
+        struct Frags {
+            double a[G][MB], b[G][NB], c[MID ? G : 1][NB];
+        };
+        const double *vf = MID ? P.vf + (size_t)node * P.n_steps * drow + P.scen_begin : nullptr;
+        auto load = [&](Frags &x, int s) {   // step s (the last one again past it: not used)
+            const int t = min(s, steps - 1) * 4 * G;
 #pragma unroll
-        for (int k = 0; k < G; ++k) {
-            const double *fa = F + (size_t)(t + 4 * k) * 64, *db = D + (size_t)(t + 4 * k) * drow;
-            load_run<MB>(x.a[k], fa + aoff);
-            load_run<NB>(x.b[k], db + boff);
-        }
-    };
-    auto multiply = [&](const Frags &x, int s) {
-#pragma unroll
-        for (int k = 0; k < G; ++k) {
-#pragma unroll
-            for (int i = 0; i < MB; ++i)
-#pragma unroll
-                for (int n = 0; n < NB; ++n) acc[i][n] = mfma64(x.a[k][i], x.b[k][n], acc[i][n]);
-            if constexpr (FRAC) {
-                if (frac) {   // flows within the month: D_t v_t^f
-                    const int t = s * 4 * G + 4 * k;
-                    const double *vf = P.vf + (size_t)node * P.n_steps * drow + P.scen_begin;
-                    const int row = min(t + lk, P.n_steps - 1) - lk;
-#pragma unroll
-                    for (int n = 0; n < NB; ++n) {
-                        const double y = x.b[k][n] * vf[(ptrdiff_t)row * drow + boff + n];
-#pragma unroll
-                        for (int i = 0; i < MB; ++i)
-                            acc[i][n] = mfma64(F[(size_t)t * 64 + st.mid + aoff + i], y, acc[i][n]);
-                    }
+            for (int k = 0; k < G; ++k) {
+                load_run<MB>(x.a[k], fl + (size_t)(t + 4 * k) * 64 + aoff);
+                load_run<NB>(x.b[k], D + (size_t)(t + 4 * k) * drow + boff);
+                if constexpr (MID) {   // v^f has no row past the last month (its flows are 0)
+                    const int row = min(t + 4 * k + lk, P.n_steps - 1) - lk;
+                    load_run<NB>(x.c[k], vf + (ptrdiff_t)row * drow + boff);
                 }
             }
-        }
-    };
-    if (steps > 0) {
+        };
+        auto multiply = [&](const Frags &x) {
+#pragma unroll
+            for (int k = 0; k < G; ++k)
+#pragma unroll
+                for (int i = 0; i < MB; ++i)
+#pragma unroll
+                    for (int n = 0; n < NB; ++n)
+                        acc[i][n] = mfma64(x.a[k][i], MID ? x.b[k][n] * x.c[k][n] : x.b[k][n], acc[i][n]);
+        };
         // Two sets of fragments by turns: the next step's are requested before a
         // step's multiplications (thousands of cycles among a SIMD's wavefronts).
         Frags x0, x1;
@@ -197,13 +191,19 @@ k_reserve_mm(RecParams P, FlowStore st, int node_begin, int n_sb)
             __builtin_amdgcn_sched_barrier(0);
             load(x1, s + 1);
             __builtin_amdgcn_sched_barrier(0);
-            multiply(x0, s);
+            multiply(x0);
             __builtin_amdgcn_sched_barrier(0);
             load(x0, s + 2);
             __builtin_amdgcn_sched_barrier(0);
-            multiply(x1, s + 1);
+            multiply(x1);
         }
-        if (s < steps) multiply(x0, s);
+        if (s < steps) multiply(x0);
+    };
+    if (steps > 0) {
+        product(F, std::false_type{});
+        if constexpr (FRAC) {
+            if (frac) product(F + st.mid, std::true_type{});
+        }
     }
     double *out = P.r0 + (size_t)(node - P.node_begin) * P.n_user * P.scen_count;
 #pragma unroll
