@@ -170,6 +170,7 @@ struct rr_ctx {
     int mk_models = 0, mk_states = 0, mk_ages = 0;
     std::vector<double> mk_c_host;        // [model][mk_states] benefits
     DevBuf<double> mk_w;                  // [model][mk_ages][4][4] ([9][9] above 4 states)
+    DevBuf<double> mk_wt;                 // [model][mk_ages][column][row] (up to 4 states)
     DevBuf<double> mk_c;                  // [model][9] benefits per unit amount
     DevBuf<Tile> tiles;
     DevBuf<int> tile_order;               // tiles, longest remaining term first

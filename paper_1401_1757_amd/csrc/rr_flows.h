@@ -90,7 +90,7 @@ struct PatWalk {
 // accumulated by tr_step from tr_init, and start(k transfers in order) sets the
 // state they lead to.  W::TR of FLOW_TR doubles a lane (0: walked by one
 // wavefront from the start).
-constexpr int FLOW_TR = 16;
+constexpr int FLOW_TR = 4;
 
 // What every walker knows of its lane.
 struct FlowLane {
@@ -336,39 +336,93 @@ struct FlowThree {
     }
 };
 
-// One life on an uploaded Markov model of M states (4: the padded small form,
-// MAX_MK_STATES: the large one): occupancy row vector times the matrix at the
-// attained age; benefits at the end of a month, premium in state 0.
-//
-// The small model's matrices (128 scattered bytes a lane and month) are read a
-// month ahead; its transfer is the 4 x 4 product of the months' matrices.  The
-// large model's 81 values are read a row at a time, which keeps the registers of
-// the instance that holds it those of the other models.
-template <int M>
-struct FlowMarkov {
-    static constexpr bool SMALL = M <= 4;
-    static constexpr int TR = SMALL ? M * M : 0;
-    int S;
-    const double *wb;
-    double occ[M], c[M], carry, a0;
-    double next[SMALL ? M * M : 1];   // the matrix of the step to come
+// One life on an uploaded Markov model of up to four states: occupancy row
+// vector times the matrix at the attained age; benefits at the end of a month,
+// premium in state 0.  A lane of its own per policy would read 128 scattered
+// bytes a month, 512 cache lines for a wavefront, and the L1 takes them one a
+// cycle.  Here four lanes share a policy: lane l holds column l % 4 of the
+// matrices of the policies l / 4 + 16 s, s = 0..3 (transposed copy of the
+// model), so that an access covers whole lines of sixteen policies, and the
+// occupancies pass between the four lanes by quad permutations.  The matrices
+// are read two months ahead.  Lane l returns the flow of policy l / 4 + 16 (l %
+// 4), which is its place in a month's kept flows.
+template <int Q>
+__device__ __forceinline__ double quad_get(double x) { return dpp_f64<Q * 0x55>(x); }   // lane Q of the quad
 
-    __device__ __forceinline__ const double *matrix(int t) const   // (past the term: the last month's)
+struct FlowMarkov4 {
+    static constexpr int TR = 0;
+    int S[4], own;   // remaining terms of the four policies; which of them is the lane's own
+    const double *wb[4];
+    double occ[4], c[4], carry, a0;
+    double w1[4][4], w2[4][4];   // columns of the step to come and the one after
+
+    __device__ __forceinline__ void fetch(double (&w)[4][4], int t) const
     {
-        return wb + (size_t)max(min(t, S - 1), 0) * (M * M);
-    }
-    __device__ __forceinline__ void fetch(int t)
-    {
-        if constexpr (SMALL) {
-            const double2 *w = reinterpret_cast<const double2 *>(matrix(t));
 #pragma unroll
-            for (int i = 0; i < M * M / 2; ++i) {
-                next[2 * i] = w[i].x;
-                next[2 * i + 1] = w[i].y;
-            }
+        for (int s = 0; s < 4; ++s) {   // (past the term: the last month's)
+            const double2 *p = reinterpret_cast<const double2 *>(wb[s] + (size_t)max(min(t, S[s] - 1), 0) * 16);
+            const double2 x = p[0], y = p[1];
+            w[s][0] = x.x;
+            w[s][1] = x.y;
+            w[s][2] = y.x;
+            w[s][3] = y.y;
         }
     }
     __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int, int shift, int t0)
+    {
+        const int lane = threadIdx.x & 63, first = L.slot - lane, j = lane & 3;
+        own = j;
+        a0 = P.coef[first + j * 16 + (lane >> 2)];
+        carry = 0.0;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            FlowLane K;
+            K.init(P, first + s * 16 + (lane >> 2), shift);
+            S[s] = K.S;
+            const int model = K.live ? P.pat_code[K.slot] : 0;
+            const int age0 = K.live ? P.age1[K.slot] + shift : 0;
+            wb[s] = P.mk_wt + ((size_t)model * P.mk_ages + age0) * 16 + 4 * j;
+            c[s] = P.coef[(1 + j) * P.n_pad + K.slot];
+            occ[s] = K.live && j == 0 ? 1.0 : 0.0;
+        }
+        fetch(w1, t0);
+        fetch(w2, t0 + 1);
+    }
+    // f_t
+    __device__ __forceinline__ double step(int t)
+    {
+        double out = 0.0, arr = 0.0;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const double o = t < S[s] ? occ[s] : 0.0;
+            const double o0 = quad_get<0>(o), o1 = quad_get<1>(o), o2 = quad_get<2>(o), o3 = quad_get<3>(o);
+            const double n = fma(o3, w1[s][3], fma(o2, w1[s][2], fma(o1, w1[s][1], o0 * w1[s][0])));
+            double x = n * c[s];
+            x += dpp_f64<0xb1>(x);   // the quad's sum in every lane
+            x += dpp_f64<0x4e>(x);
+            out = own == s ? fma(o0, a0, carry) : out;
+            arr = own == s ? x : arr;
+            occ[s] = n;
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w1[s][i] = w2[s][i];
+        fetch(w2, t + 2);
+        carry = arr;
+        return out;
+    }
+};
+
+// A model of more states, one policy a lane: the matrix is read a row at a time,
+// which keeps the registers of the instance those of the other models.
+struct FlowMarkov9 {
+    static constexpr int M = MAX_MK_STATES, TR = 0;
+    int S;
+    const double *wb;
+    double occ[M], c[M], carry, a0;
+
+    __device__ __forceinline__ void init(const RecParams &P, const FlowLane &L, int, int shift, int)
     {
         S = L.S;
         a0 = P.coef[L.slot];
@@ -377,94 +431,30 @@ struct FlowMarkov {
         wb = P.mk_w + ((size_t)model * P.mk_ages + age0) * (M * M);
 #pragma unroll
         for (int j = 0; j < M; ++j) {
-            c[j] = SMALL ? P.coef[(1 + (j & 3)) * P.n_pad + L.slot]
-                         : P.coef[P.n_pad + L.slot] * P.mk_c[model * M + j];
+            c[j] = P.coef[P.n_pad + L.slot] * P.mk_c[model * M + j];
             occ[j] = 0.0;
         }
         occ[0] = L.live ? 1.0 : 0.0;
         carry = 0.0;
-        fetch(t0);
     }
-    // The product of the matrices of steps [t0, t1); the walk then starts at t0
-    // again (its matrix is fetched).
-    __device__ __forceinline__ void transfer(int t0, int t1, double (&x)[FLOW_TR])
-    {
-        if constexpr (SMALL) {
-#pragma unroll
-            for (int i = 0; i < M * M; ++i) x[i] = i % (M + 1) == 0 ? 1.0 : 0.0;
-            for (int t = t0; t < t1; ++t) {
-                double w[M * M];
-#pragma unroll
-                for (int i = 0; i < M * M; ++i) w[i] = next[i];
-                fetch(t + 1);
-#pragma unroll
-                for (int i = 0; i < M; ++i) {
-                    double r[M];
-#pragma unroll
-                    for (int j = 0; j < M; ++j) {
-                        r[j] = x[i * M] * w[j];
-#pragma unroll
-                        for (int k = 1; k < M; ++k) r[j] = fma(x[i * M + k], w[k * M + j], r[j]);
-                    }
-#pragma unroll
-                    for (int j = 0; j < M; ++j) x[i * M + j] = r[j];
-                }
-            }
-            fetch(t0);
-        }
-    }
-    __device__ __forceinline__ void advance(const double (&x)[FLOW_TR])
-    {
-        if constexpr (SMALL) {
-            double r[M];
-#pragma unroll
-            for (int j = 0; j < M; ++j) {
-                r[j] = occ[0] * x[j];
-#pragma unroll
-                for (int k = 1; k < M; ++k) r[j] = fma(occ[k], x[k * M + j], r[j]);
-            }
-#pragma unroll
-            for (int j = 0; j < M; ++j) occ[j] = r[j];
-        }
-    }
-    __device__ __forceinline__ void past(int t)
-    {
-        if (t > S) {
-#pragma unroll
-            for (int j = 0; j < M; ++j) occ[j] = 0.0;
-        }
-    }
-    // f_t
+    // f_t (past the term the last month's matrix is read again)
     __device__ __forceinline__ double step(int t)
     {
         if (t >= S) {
 #pragma unroll
             for (int j = 0; j < M; ++j) occ[j] = 0.0;
         }
+        const double *w = wb + (size_t)max(min(t, S - 1), 0) * (M * M);
         const double out = fma(occ[0], a0, carry);
         double n[M];
-        if constexpr (SMALL) {
-            double w[M * M];
 #pragma unroll
-            for (int i = 0; i < M * M; ++i) w[i] = next[i];
-            fetch(t + 1);
-#pragma unroll
-            for (int j = 0; j < M; ++j) n[j] = occ[0] * w[j];
-#pragma unroll
-            for (int i = 1; i < M; ++i)
-#pragma unroll
-                for (int j = 0; j < M; ++j) n[j] = fma(occ[i], w[i * M + j], n[j]);
-        } else {
-            const double *w = matrix(t);
-#pragma unroll
-            for (int j = 0; j < M; ++j) n[j] = occ[0] * w[j];
+        for (int j = 0; j < M; ++j) n[j] = occ[0] * w[j];
 #pragma unroll 1
-            for (int i = 1; i < M; ++i) {   // (the occupancies move down one place per row)
+        for (int i = 1; i < M; ++i) {   // (the occupancies move down one place per row)
 #pragma unroll
-                for (int j = 0; j + 1 < M; ++j) occ[j] = occ[j + 1];
+            for (int j = 0; j + 1 < M; ++j) occ[j] = occ[j + 1];
 #pragma unroll
-                for (int j = 0; j < M; ++j) n[j] = fma(occ[0], w[i * M + j], n[j]);
-            }
+            for (int j = 0; j < M; ++j) n[j] = fma(occ[0], w[i * M + j], n[j]);
         }
         double arr = 0.0;
 #pragma unroll
@@ -618,8 +608,7 @@ __device__ __forceinline__ void flow_transfer(const RecParams &P, const double *
     }
 }
 
-// Calls visit(walker type tag) for the tile's model, where the tag's type W is
-// tag.w's.  Markov tiles are visited with FlowMarkov.
+// Calls visit(tag) for the tile's model, its walker the tag's type.
 template <class W>
 struct FlowTag {
     typedef W type;
@@ -650,8 +639,8 @@ __device__ __forceinline__ void flow_model(const RecParams &P, int kind, int flo
             return;
         }
         if (flow == FLOW_MARKOV) {
-            if (P.mk_states > 4) visit(FlowTag<FlowMarkov<MAX_MK_STATES>>{});
-            else visit(FlowTag<FlowMarkov<4>>{});
+            if (P.mk_states > 4) visit(FlowTag<FlowMarkov9>{});
+            else visit(FlowTag<FlowMarkov4>{});
             return;
         }
         if (flow == FLOW_FRAC) {
@@ -672,8 +661,12 @@ template <class W>
 struct FlowTraits {
     static constexpr bool markov = false, frac = false;
 };
-template <int M>
-struct FlowTraits<FlowMarkov<M>> {
+template <>
+struct FlowTraits<FlowMarkov4> {
+    static constexpr bool markov = true, frac = false;
+};
+template <>
+struct FlowTraits<FlowMarkov9> {
     static constexpr bool markov = true, frac = false;
 };
 template <bool LDSQ, bool TWO>

@@ -72,7 +72,7 @@ struct FlowRow {
 // operations and two multiplications for the transfer.  See flow_shape for the
 // split and its figures.
 template <bool LDSQ, bool VEC, int SET, int CHUNKS>
-__global__ void __launch_bounds__(64 * FLOW_WAVES, 4)
+__global__ void __launch_bounds__(64 * FLOW_WAVES, SET == FLOWS_ALL ? 2 : 4)
 k_flow_sums(RecParams P, int node_begin, int R, int row_len, int table_doubles, double *__restrict__ rows,
             double *__restrict__ rows_mid, FlowStore st)
 {
@@ -91,9 +91,8 @@ k_flow_sums(RecParams P, int node_begin, int R, int row_len, int table_doubles, 
     const size_t unit = (size_t)blockIdx.y * R + min(g, R - 1);
     const int shift = node * P.node_step;
     double *stage0 = s_mem + table_doubles;
-    constexpr int TR = SET == FLOWS_ALL ? FLOW_TR : 4;   // doubles of a transfer, of the models in the set
-    static_assert(FLOW_WAVES * TR * 64 <= FLOW_WAVES * FLOW_STAGE * (SET == FLOWS_ALL ? 2 : 1), "transfers fit the stages");
-    double (*s_tr)[TR][64] = reinterpret_cast<double (*)[TR][64]>(stage0);   // before the stages' use
+    static_assert(FLOW_TR * 64 <= FLOW_STAGE, "transfers fit the stages");
+    double (*s_tr)[FLOW_TR][64] = reinterpret_cast<double (*)[FLOW_TR][64]>(stage0);   // before the stages' use
     FlowRow row, mid;
     row.stage = stage0 + wave * FLOW_STAGE * (SET == FLOWS_ALL ? 2 : 1);
     row.dst = rows + unit * row_len;
@@ -134,11 +133,9 @@ k_flow_sums(RecParams P, int node_begin, int R, int row_len, int table_doubles, 
             W w[1];
             w[0].init(P, L, kind, shift, s0);
             if constexpr (cut) {
-                static_assert(W::TR <= TR, "transfer size");
                 double x[FLOW_TR];
                 const int s1 = t1 > t0 && t1 < len ? t1 - 1 : s0;
-                if constexpr (X::markov) w[0].transfer(s0, s1, x);
-                else flow_transfer(P, s_mem, w[0], m, smax, s0, s1, x);
+                flow_transfer(P, s_mem, w[0], m, smax, s0, s1, x);
 #pragma unroll
                 for (int i = 0; i < W::TR; ++i) s_tr[wave][i][lane] = x[i];
                 __syncthreads();
@@ -156,13 +153,16 @@ k_flow_sums(RecParams P, int node_begin, int R, int row_len, int table_doubles, 
             mid.have = done_mid;
             if (t0 >= t1) return;
             if constexpr (X::markov) {
-                if (lead) (void)w[0].step(s0);
-                for (int t = t0; t < t1; ++t) {
-                    const double f = w[0].step(t);
-                    if (keep) keep[(size_t)t * 64] = f;
-                    if (!rows) continue;
-                    row.put(t, f, lane);
-                    if ((t & (FLOW_BLK - 1)) == FLOW_BLK - 1) row.flush(t + 1, lane);
+                // (FlowMarkov4's lanes stand in the order of the kept flows already)
+                double *k = std::is_same<W, FlowMarkov4>::value && keep ? keep - (lane & 15) * 4 - (lane >> 4) + lane : keep;
+                for (int t = t0; t < t1; t += FLOW_BLK) {
+#pragma unroll 2
+                    for (int u = 0; u < FLOW_BLK; ++u) {
+                        const double f = w[0].step(t + u);
+                        if (k) k[(size_t)(t + u) * 64] = f;
+                        if (rows) row.put(t + u, f, lane);
+                    }
+                    if (rows) row.flush(t + FLOW_BLK, lane);
                 }
             } else {
                 flow_walk<FLOW_U, 1>(

@@ -1220,6 +1220,13 @@ extern "C" int rr_markov_upload(rr_ctx *c, const rr_markov *m)
             }
     HIPCHK(c, c->mk_w.alloc(wp.size()));
     HIPCHK(c, hipMemcpy(c->mk_w.p, wp.data(), wp.size() * sizeof(double), hipMemcpyHostToDevice));
+    if (MP == 4) {
+        std::vector<double> wt(wp.size());
+        for (size_t k = 0; k < wp.size(); k += 16)
+            for (int i = 0; i < 4; ++i)
+                for (int j = 0; j < 4; ++j) wt[k + 4 * j + i] = wp[k + 4 * i + j];
+        if ((rc = upload_vec(c, c->mk_wt, wt))) return rc;
+    }
     std::vector<double> cpad((size_t)m->n_models * MAX_MK_STATES, 0.0);
     for (int md = 0; md < m->n_models; ++md)
         for (int j = 0; j < M; ++j) cpad[(size_t)md * MAX_MK_STATES + j] = ben[(size_t)md * M + j];
@@ -1415,6 +1422,7 @@ static RecParams make_params(rr_ctx *c, const rr_run *run, const rr_outputs *out
     P.cf_t = (c->has_flow && c->cf_cols > 0) ? c->cf_t.p : nullptr;
     P.cf_cols = c->cf_cols;
     P.mk_w = c->has_markov ? c->mk_w.p : nullptr;
+    P.mk_wt = c->has_markov ? c->mk_wt.p : nullptr;
     P.mk_ages = c->mk_ages;
     P.mk_states = c->mk_states;
     P.mk_c = c->has_markov ? c->mk_c.p : nullptr;
@@ -1605,7 +1613,7 @@ static void flow_work(const rr_ctx *c, const rr_run *run, long long most, long l
 //
 // Under capture (cap) the totals and the statistic are a branch of their own
 // beside the product, which leaves half of a CU's wavefront slots free: 10,000
-// policies x 1,000 scenarios 0.178 -> 0.157 ms.
+// policies x 1,000 scenarios 0.178 -> 0.165 ms.
 static int enqueue_flow_run(rr_ctx *c, const rr_run *run, const rr_outputs *out, double *work, long long kept,
                             double *totals, hipStream_t s, bool timed)
 {

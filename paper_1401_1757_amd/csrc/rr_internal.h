@@ -107,6 +107,7 @@ struct RecParams {
     int cf_cols;
     const double *mk_w;       // [model][mk_ages][4][4] uploaded Markov matrices (zero padded),
                               // [model][mk_ages][9][9] for models of 5-9 states
+    const double *mk_wt;      // the four-state form transposed: [model][mk_ages][column][row]
     int mk_ages;
     int mk_states;
     const double *mk_c;       // [model][9] benefits per unit amount (models of 5-9 states)
