@@ -548,7 +548,7 @@ static double vasicek_log_span(const VasParams &P, const std::vector<double> &r0
 // first if they change while earlier work may still read them), the work
 // buffer sized, then the kernels.
 static int enqueue_vasicek(rr_ctx *c, const VasParams &P, const std::vector<double> &r0, double *v,
-                           int month_major, double *r_out)
+                           int month_major, double *r_out, double *D)
 {
     const size_t need = vasicek_work_doubles(P.n_nodes, P.n_scen, P.n_steps, P.scen_pad);
     const bool new_r0 = r0 != c->vas_r0_host;
@@ -560,7 +560,7 @@ static int enqueue_vasicek(rr_ctx *c, const VasParams &P, const std::vector<doub
         HIPCHK(c, hipMemcpy(c->vas_r0.p, r0.data(), r0.size() * sizeof(double), hipMemcpyHostToDevice));
         c->vas_r0_host = r0;
     }
-    HIPCHK(c, launch_vasicek(P, c->vas_r0.p, c->vas_work.p, v, month_major, r_out, c->stream));
+    HIPCHK(c, launch_vasicek(P, c->vas_r0.p, c->vas_work.p, v, month_major, r_out, D, c->stream));
     // Regenerating an installed basis in place: v^frac follows (install_basis
     // sizes and fills it itself after the first generation).
     if (c->has_basis && v == c->v.p && c->frac > 0.0 && c->vf.p)
@@ -569,20 +569,16 @@ static int enqueue_vasicek(rr_ctx *c, const VasParams &P, const std::vector<doub
     return RR_OK;
 }
 
-// Discount products of the installed curves, kept beside them (8 bytes per
-// curve value): formed where no product can leave the FP64 range and the
-// memory is there; without them runs take the recurrence kernel.
-static int enqueue_discounts(rr_ctx *c)
+// Room for the discount products of the curves to come, kept beside them (8
+// bytes per curve value): given where no product can leave the FP64 range and
+// the memory is there; without them (null) runs take the recurrence kernel.
+static double *discount_room(rr_ctx *c)
 {
     c->has_disc = false;
-    if (!(c->curve_log_span <= kSafeLogSpan)) return RR_OK;
-    if (c->disc.alloc((size_t)c->n_nodes * disc_rows(c->n_steps) * c->scen_pad) != hipSuccess) {
-        (void)hipGetLastError();
-        return RR_OK;
-    }
-    HIPCHK(c, launch_discounts(c->v.p, c->n_nodes, c->n_steps, c->scen_pad, c->disc.p, c->stream));
-    c->has_disc = true;
-    return RR_OK;
+    if (!(c->curve_log_span <= kSafeLogSpan)) return nullptr;
+    if (c->disc.alloc((size_t)c->n_nodes * disc_rows(c->n_steps) * c->scen_pad) == hipSuccess) return c->disc.p;
+    (void)hipGetLastError();
+    return nullptr;
 }
 
 // Shared tail of rr_basis_upload and rr_basis_generate_vasicek: install the
@@ -630,6 +626,7 @@ static int install_basis(rr_ctx *c, const rr_basis *b, std::vector<double> &q,
     c->shock_host.assign((size_t)b->n_nodes, 1.0);
     if (b->shock) c->shock_host = sh;
     HIPCHK(c, c->v.alloc((size_t)b->n_nodes * b->n_steps * c->scen_pad));
+    double *D = discount_room(c);
     int rc;
     if (v) {   // curves as given, transposed to month-major on the device
         const size_t nv = v->size();
@@ -638,18 +635,19 @@ static int install_basis(rr_ctx *c, const rr_basis *b, std::vector<double> &q,
         HIPCHK(c, hipMemcpy(tmp.p, v->data(), nv * sizeof(double), hipMemcpyHostToDevice));
         HIPCHK(c, launch_transpose_curves(tmp.p, c->v.p, b->n_nodes, b->n_scen, b->n_steps,
                                           c->scen_pad, c->stream));
+        if (D) HIPCHK(c, launch_discounts(c->v.p, c->n_nodes, c->n_steps, c->scen_pad, D, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
     } else {
         VasParams P = *gen;
         P.scen_pad = c->scen_pad;
-        if ((rc = enqueue_vasicek(c, P, *gen_r0, c->v.p, 1, nullptr))) return rc;
+        if ((rc = enqueue_vasicek(c, P, *gen_r0, c->v.p, 1, nullptr, D))) return rc;
     }
     if (c->frac > 0.0) {   // v^frac beside v for fractional annuities
         const long long nvv = (long long)b->n_nodes * b->n_steps * c->scen_pad;
         HIPCHK(c, c->vf.alloc((size_t)nvv));
         HIPCHK(c, launch_pow_curves(c->v.p, c->vf.p, nvv, c->frac, c->stream));
     }
-    if ((rc = enqueue_discounts(c))) return rc;
+    c->has_disc = D != nullptr;
     HIPCHK(c, c->shock.alloc((size_t)b->n_nodes));
     HIPCHK(c, hipMemcpy(c->shock.p, c->shock_host.data(), sizeof(double) * b->n_nodes,
                         hipMemcpyHostToDevice));
@@ -720,8 +718,10 @@ extern "C" int rr_curves_generate_vasicek(rr_ctx *c, const rr_vasicek *vs)
     const double span = vasicek_log_span(P, r0);
     if ((span <= kSafeLogSpan) != (c->curve_log_span <= kSafeLogSpan)) drop_graphs(c);   // other kernels
     c->curve_log_span = span;
-    if ((rc = enqueue_vasicek(c, P, r0, c->v.p, 1, nullptr))) return rc;
-    return enqueue_discounts(c);
+    double *D = discount_room(c);
+    if ((rc = enqueue_vasicek(c, P, r0, c->v.p, 1, nullptr, D))) return rc;
+    c->has_disc = D != nullptr;
+    return RR_OK;
 }
 
 extern "C" int rr_vasicek_curves(rr_ctx *c, const rr_vasicek *vs, int32_t n_nodes, int32_t n_scen,
@@ -735,7 +735,7 @@ extern "C" int rr_vasicek_curves(rr_ctx *c, const rr_vasicek *vs, int32_t n_node
     const int scen_pad = (n_scen + 63) / 64 * 64;
     if ((rc = vasicek_params(c, vs, n_nodes, n_scen, n_steps, scen_pad, &P, &r0))) return rc;
     if (!v) return fail(c, RR_EINVAL, "vasicek: v must not be NULL");
-    return enqueue_vasicek(c, P, r0, v, 0, r);
+    return enqueue_vasicek(c, P, r0, v, 0, r, nullptr);
 }
 
 extern "C" int rr_portfolio_upload(rr_ctx *c, const rr_portfolio *p)

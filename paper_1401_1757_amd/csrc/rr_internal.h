@@ -228,9 +228,10 @@ struct VasParams {
 // work: vasicek_work_doubles(...) doubles (normals and short rates, month-
 // major with stride scen_pad); r0: device [n_nodes]; v: month-major with
 // stride scen_pad (the library's curves) or [node][scen][step]; r_out:
-// [node][scen][step + 1] or null.
+// [node][scen][step + 1] or null; D: the month-major curves' discount products
+// (launch_discounts) or null.  scen_pad: a multiple of 8.
 hipError_t launch_vasicek(const VasParams &P, const double *r0, double *work, double *v,
-                          int month_major, double *r_out, hipStream_t stream);
+                          int month_major, double *r_out, double *D, hipStream_t stream);
 size_t vasicek_work_doubles(int n_nodes, int n_scen, int n_steps, int scen_pad);
 // Mean discount curve of the run's scenarios per node (rr_kernels.hip): D
 // holds node_count * n_steps * scen_count doubles; vbar is [n_nodes][n_steps][64]

@@ -6,9 +6,11 @@
 // The random numbers of (node k, scenario s, step t) are the Philox4x64-10
 // block of the counter (t, s, k, 0) under the caller's key, so every value
 // is computed independently: the normals of all steps in parallel, then the
-// short-rate chain per scenario (a first-order linear recurrence in t), then
-// the discount factors in parallel again.
+// short-rate chain (a first-order linear recurrence in t, cut in time chunks)
+// with the discount factors and their products.
 #include "rr_internal.h"
+
+#include <algorithm>
 
 namespace rr {
 
@@ -64,75 +66,108 @@ __global__ void __launch_bounds__(256) k_vas_normals(VasParams P, double *__rest
     z1[o] = rad * sn;
 }
 
-// Short-rate chain of each (node, scenario): r[(k * (n_steps + 1) + t) *
-// scen_pad + s] for t = 0..n_steps.  Consecutive threads take consecutive
-// scenarios, so every load and store of a step is coalesced.  The chain is
-// sequential in t but its normals are not: they are loaded RATES_CHUNK steps
-// ahead into registers, so a step waits on arithmetic, not on memory.
-constexpr int RATES_CHUNK = 32;
-constexpr int RATES_THREADS = 64;
-
-__global__ void __launch_bounds__(RATES_THREADS) k_vas_rates(VasParams P,
-                                                             const double *__restrict__ r0,
-                                                             const double *__restrict__ z0,
-                                                             double *__restrict__ r)
-{
-    const int id = blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= P.n_nodes * P.n_scen) return;
-    const int k = id / P.n_scen, s = id % P.n_scen;
-    const double *zk = z0 + (size_t)k * P.n_steps * P.scen_pad + s;
-    double *rk = r + (size_t)k * (P.n_steps + 1) * P.scen_pad + s;
-    double rt = r0[k];
-    rk[0] = rt;
-    double zc[RATES_CHUNK];
-#pragma unroll
-    for (int i = 0; i < RATES_CHUNK; ++i)
-        zc[i] = i < P.n_steps ? zk[(size_t)i * P.scen_pad] : 0.0;
-    for (int t0 = 0; t0 < P.n_steps; t0 += RATES_CHUNK) {
-        double zn[RATES_CHUNK];
-#pragma unroll
-        for (int i = 0; i < RATES_CHUNK; ++i) {
-            const int t = t0 + RATES_CHUNK + i;
-            zn[i] = t < P.n_steps ? zk[(size_t)t * P.scen_pad] : 0.0;
-        }
-#pragma unroll
-        for (int i = 0; i < RATES_CHUNK; ++i) {
-            const int t = t0 + i;
-            if (t < P.n_steps) {
-                rt = P.b + (rt - P.b) * P.e + P.sd_r * zc[i];
-                rk[(size_t)(t + 1) * P.scen_pad] = rt;
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < RATES_CHUNK; ++i) zc[i] = zn[i];
-    }
-}
-
-// Discount factor of each (node, step, scenario): v = exp(-Y), Y the
-// integral of the short rate over the step given r_t and the two normals.
+// Short rates, discount factors and (D) discount products of every (node,
+// scenario) in one pass over the normals.  r_t - b is a first-order linear
+// recurrence, so a workgroup cuts the months of eight scenarios
+// in 64 chunks of up to 16: a thread holds its chunk's normals in registers, runs
+// the chunk from 0, takes its true start from the ends of the chunks before it
+// (all of one length) through LDS, and runs it again for the rates and
+// v = exp(-Y), Y the integral of the short rate over the step given r_t and the
+// two normals.  The products of v go through LDS the same way.  Months past
+// 1,024 months follow as further segments from where the last one ended.
+//
 // month_major: v[(k * n_steps + t) * ld + s] (the library's curve layout,
-// padding scenarios set to 1), else v[(k * n_scen + s) * n_steps + t].
-__global__ void __launch_bounds__(256) k_vas_discount(VasParams P, const double *__restrict__ z0,
-                                                      const double *__restrict__ z1,
-                                                      const double *__restrict__ r,
-                                                      double *__restrict__ v, int month_major)
+// padding scenarios set to 1), else v[(k * n_scen + s) * n_steps + t].  r (or
+// null): r[(k * (n_steps + 1) + t) * scen_pad + s], t = 0 .. n_steps.  D (or
+// null; month-major): D[(k * disc_rows + t) * scen_pad + s], zeros past t = n_steps.
+//
+// Bound by latency at the usual sizes (a thread's loads go out together) and by
+// the 32 bytes a value that it moves at many curves.  It takes the place of a
+// chain a thread (600 dependent steps on 16 wavefronts), a pass for the factors
+// and one for the products: 1,000 scenarios x 600 months drawn and valued for
+// 10,000 policies 0.244 -> 0.196 ms.  Eight scenarios a workgroup: sixteen
+// leave half of the CUs idle there and spill registers.
+constexpr int SCAN_S = 8, SCAN_C = 64, SCAN_LEN = 16;
+
+__global__ void __launch_bounds__(SCAN_S * SCAN_C)
+k_vas_scan(VasParams P, int node0, const double *__restrict__ r0, const double *__restrict__ z0,
+           const double *__restrict__ z1, double *__restrict__ r, double *__restrict__ v, int month_major,
+           double *__restrict__ D)
 {
-    const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long total = (long long)P.n_nodes * P.n_steps * P.scen_pad;
-    if (id >= total) return;
-    const int s = (int)(id % P.scen_pad);
-    const long long kt = id / P.scen_pad;
-    const int t = (int)(kt % P.n_steps);
-    const int k = (int)(kt / P.n_steps);
-    if (s >= P.n_scen) {
-        if (month_major) v[id] = 1.0;
-        return;
+    __shared__ double s_end[SCAN_C][SCAN_S], s_prod[SCAN_C][SCAN_S], s_dev[SCAN_S], s_disc[SCAN_S];
+    const int lane = threadIdx.x % SCAN_S, c = threadIdx.x / SCAN_S, k = node0 + blockIdx.y;
+    const int n_sb = P.scen_pad / SCAN_S, n = P.n_steps;
+    const size_t row = P.scen_pad;
+    for (int sb = blockIdx.x; sb < n_sb; sb += gridDim.x) {
+        const int s = sb * SCAN_S + lane;
+        const bool real = s < P.n_scen;
+        const double *zk0 = z0 + (size_t)k * n * row + s, *zk1 = z1 + (size_t)k * n * row + s;
+        double dev0 = r0[k] - P.b, disc0 = 1.0;   // at the segment's start
+        if (c == 0) {
+            if (D) D[(size_t)k * disc_rows(n) * row + s] = 1.0;
+            if (r && real) r[(size_t)k * (n + 1) * row + s] = r0[k];
+        }
+        for (int seg = 0; seg < n; seg += SCAN_C * SCAN_LEN) {
+            const int per = min(SCAN_LEN, (n - seg + SCAN_C - 1) / SCAN_C);
+            // Every thread walks `per` months (a month past the end repeats the last
+            // one's normals, and stores nothing): only whole chunks are followed
+            // by others, so what a cut one ends with is not read.
+            const int t0 = seg + c * per;
+            double za[SCAN_LEN], zb[SCAN_LEN];
+#pragma unroll
+            for (int i = 0; i < SCAN_LEN; ++i) {
+                const size_t o = (size_t)min(t0 + min(i, per - 1), n - 1) * row;
+                za[i] = zk0[o];
+                zb[i] = zk1[o];
+            }
+            double x = 0.0, e = 1.0;
+#pragma unroll
+            for (int i = 0; i < SCAN_LEN; ++i) {
+                if (i >= per) continue;
+                x = fma(x, P.e, P.sd_r * za[i]);
+                e *= P.e;
+            }
+            s_end[c][lane] = x;
+            __syncthreads();
+            x = dev0;
+            for (int w = 0; w < c; ++w) x = fma(x, e, s_end[w][lane]);
+            double p = 1.0;
+#pragma unroll
+            for (int i = 0; i < SCAN_LEN; ++i) {
+                if (i >= per) continue;
+                const double y = P.b * P.dt + x * P.om + P.rho_sd_y * za[i] + P.sd_y_perp * zb[i];
+                x = fma(x, P.e, P.sd_r * za[i]);
+                za[i] = real ? exp(-y) : 1.0;
+                p *= za[i];
+                const int t = t0 + i;
+                if (t >= n) continue;
+                if (month_major) v[((size_t)k * n + t) * row + s] = za[i];
+                else if (real) v[((size_t)k * P.n_scen + s) * n + t] = za[i];
+                if (r && real) r[((size_t)k * (n + 1) + t + 1) * row + s] = P.b + x;
+            }
+            s_prod[c][lane] = p;
+            if (c == SCAN_C - 1) s_dev[lane] = x;
+            __syncthreads();
+            dev0 = s_dev[lane];
+            if (D) {
+                double d = disc0;
+                for (int w = 0; w < c; ++w) d *= s_prod[w][lane];
+                double *Dk = D + (size_t)k * disc_rows(n) * row + s;
+#pragma unroll
+                for (int i = 0; i < SCAN_LEN; ++i) {
+                    if (i >= per) continue;
+                    d *= za[i];
+                    if (t0 + i < n) Dk[(size_t)(t0 + i + 1) * row] = d;
+                }
+                if (c == SCAN_C - 1) s_disc[lane] = d;
+            }
+            __syncthreads();   // the next segment writes what this one's threads read
+            disc0 = s_disc[lane];
+        }
+        if (D)   // rows that whole blocks of months reach
+            for (int t = n + 1 + c; t < disc_rows(n); t += SCAN_C)
+                D[((size_t)k * disc_rows(n) + t) * row + s] = 0.0;
     }
-    const double rt = r[((size_t)k * (P.n_steps + 1) + t) * P.scen_pad + s];
-    const double y = P.b * P.dt + (rt - P.b) * P.om + P.rho_sd_y * z0[id] + P.sd_y_perp * z1[id];
-    const double x = exp(-y);
-    if (month_major) v[id] = x;
-    else v[((size_t)k * P.n_scen + s) * P.n_steps + t] = x;
 }
 
 // Short rates in the caller's layout r_out[(k * n_scen + s) * (n_steps + 1) + t].
@@ -152,18 +187,16 @@ __global__ void __launch_bounds__(256) k_vas_rates_out(VasParams P, const double
 static unsigned blocks_of(long long n) { return (unsigned)((n + 255) / 256); }
 
 hipError_t launch_vasicek(const VasParams &P, const double *r0, double *work, double *v,
-                          int month_major, double *r_out, hipStream_t stream)
+                          int month_major, double *r_out, double *D, hipStream_t stream)
 {
     if (P.n_nodes <= 0 || P.n_scen <= 0 || P.n_steps <= 0) return hipSuccess;
     const size_t zn = (size_t)P.n_nodes * P.n_steps * P.scen_pad;
-    double *z0 = work, *z1 = work + zn, *r = work + 2 * zn;
+    double *z0 = work, *z1 = work + zn, *r = r_out ? work + 2 * zn : nullptr;
     hipLaunchKernelGGL(k_vas_normals, dim3(blocks_of((long long)P.n_nodes * P.n_steps * P.n_scen)),
                        dim3(256), 0, stream, P, z0, z1);
-    hipLaunchKernelGGL(k_vas_rates,
-                       dim3((unsigned)(((long long)P.n_nodes * P.n_scen + RATES_THREADS - 1) / RATES_THREADS)),
-                       dim3(RATES_THREADS), 0, stream, P, r0, z0, r);
-    hipLaunchKernelGGL(k_vas_discount, dim3(blocks_of((long long)zn)), dim3(256), 0, stream, P, z0,
-                       z1, r, v, month_major);
+    for (int k = 0; k < P.n_nodes; k += 32768)
+        hipLaunchKernelGGL(k_vas_scan, dim3(std::min(P.scen_pad / SCAN_S, 1 << 16), std::min(P.n_nodes - k, 32768)),
+                           dim3(SCAN_S * SCAN_C), 0, stream, P, k, r0, z0, z1, r, v, month_major, D);
     if (r_out)
         hipLaunchKernelGGL(k_vas_rates_out,
                            dim3(blocks_of((long long)P.n_nodes * (P.n_steps + 1) * P.n_scen)),

@@ -66,6 +66,19 @@ def test_curves_full_c3_size(ctx):
     check_curves(to_np(gv), to_np(gr), ov, orr)
 
 
+@pytest.mark.parametrize("n_scen,n_steps", [(1, 1), (7, 63), (8, 64), (9, 65), (3, 1023), (17, 1024),
+                                            (5, 1025), (64, 2049)])
+def test_curves_at_the_edges_of_the_time_chunks(ctx, n_scen, n_steps):
+    """64 chunks of up to 16 months per segment, eight scenarios per workgroup."""
+    r0, key = [0.03, -0.02], (3, n_steps)
+    _say(f"curves {n_scen} x {n_steps}")
+    gv, gr = ctx.vasicek_curves(n_scen, n_steps, r0, A, B, SIG, DT, key)
+    torch.cuda.synchronize()
+    ov, orr = oracle.vasicek_curves(A, B, SIG, DT, r0, n_scen, n_steps, key)
+    check_curves(to_np(gv), to_np(gr), ov, orr)
+    assert np.array_equal(to_np(gr)[..., 0], np.broadcast_to(np.array(r0)[:, None], (2, n_scen)))
+
+
 def reserves_on_generated(ctx, w, r0, key, nscen):
     """Reserves from a device-generated basis vs the oracle on its own curves."""
     b, pf = w.basis, w.portfolio
@@ -104,6 +117,17 @@ def test_generated_basis_reserves_and_in_place_regeneration(ctx):
         ctx.reserve_recurrence(0, 2, 0, 45, w.node_step_m, again)
         torch.cuda.synchronize()
         assert np.array_equal(to_np(again["r0"]), first_r0)
+
+
+@pytest.mark.parametrize("n_scen,n_steps", [(2, 7), (33, 64), (9, 65), (12, 1030)])
+def test_reserves_by_the_generated_discount_products(ctx, n_scen, n_steps):
+    """Terms up to the last month, scenario counts that leave padding columns."""
+    w = synth.random_small(np.random.default_rng(n_steps), n=150, n_steps=n_steps, n_scen=1, n_nodes=2)
+    r0, key = [0.03, 0.05], (21, n_steps)
+    _say(f"reserves on generated curves {n_scen} x {n_steps}")
+    ctx.basis_generate_vasicek(w.basis.q, n_scen, n_steps, r0, A, B, SIG, DT, key, shock=w.basis.shock)
+    ctx.portfolio_upload(w.portfolio)
+    reserves_on_generated(ctx, w, r0, key, n_scen)
 
 
 def test_invalid_generator_calls(ctx, rr):
