@@ -214,6 +214,29 @@ __global__ void __launch_bounds__(512) k_flow_reduce(const double *__restrict__ 
     }
 }
 
+// Sum and product with their rounding error in the second part (error-free transformations of Knuth and Dekker).
+struct Pair {
+    double hi, lo;
+};
+__device__ __forceinline__ Pair exact_add(double a, double b)
+{
+#pragma clang fp contract(off)
+    const double s = a + b, t = s - a;
+    return {s, (a - (s - t)) + (b - t)};
+}
+__device__ __forceinline__ Pair exact_mul(double a, double b)
+{
+#pragma clang fp contract(off)
+    const double p = a * b;
+    return {p, __builtin_fma(a, b, -p)};
+}
+// x r + f to first order in the errors.
+__device__ __forceinline__ Pair pair_step(Pair x, Pair r, Pair f)
+{
+    const Pair p = exact_mul(x.hi, r.hi), s = exact_add(p.hi, f.hi);
+    return {s.hi, fma(x.hi, r.lo, fma(x.lo, r.hi, (p.lo + s.lo) + f.lo))};
+}
+
 // Totals of 64 scenarios of a node: R_t = F_t + vf_t M_t + v_t R_{t+1} from the
 // last flow down to t = 0 (M: the flows within the month, discounted by
 // vf = v^frac).  CH wavefronts take a time chunk each as the affine map
@@ -221,13 +244,18 @@ __global__ void __launch_bounds__(512) k_flow_reduce(const double *__restrict__ 
 // is the plain recurrence, for curves whose products could leave the FP64
 // range.  Reads every live curve value once: bound by that read at many nodes,
 // by the chunk's serial chain at one.
+//
+// One chain carries the whole portfolio, so its rounding errors do not average
+// out as those of the policies' own chains do (10,000 policies x 60 nodes:
+// 1.0e-15 against 0.95e-15): the chunked form keeps the error of every operation
+// beside the value.
 template <int CH>
 __global__ void __launch_bounds__(64 * CH)
 k_flow_totals(RecParams P, const double *__restrict__ sums, const double *__restrict__ sums_mid, int n_sums,
               int row_len, int max_term, int node_begin, double *__restrict__ totals)
 {
     extern __shared__ double s_mem[];   // F[len + 1], then M[len + 1]
-    __shared__ double sA[CH][64], sB[CH][64];
+    __shared__ Pair sA[CH][64], sB[CH][64];
     const int node_rel = blockIdx.y, node = node_begin + node_rel;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int s = blockIdx.x * 64 + lane;
@@ -251,18 +279,29 @@ k_flow_totals(RecParams P, const double *__restrict__ sums, const double *__rest
         }
     }
     __syncthreads();
-    const int step = (len + CH - 1) / CH;
-    const int lo = wave * step, hi = min(lo + step, len);
+    const int per = (len + CH - 1) / CH;
+    const int lo = wave * per, hi = min(lo + per, len);
     const size_t off = (size_t)node * P.n_steps * P.scen_pad + P.scen_begin + min(s, P.scen_count - 1);
     const double *v = P.v + off;
-    double A = 1.0, B = CH == 1 ? F[len] : 0.0;
+    if constexpr (CH == 1) {
+        double R = F[len];
+        for (int t = len - 1; t >= 0; --t) {
+            const double f = sums_mid ? fma(P.vf[off + (size_t)t * P.scen_pad], M[t], F[t]) : F[t];
+            R = fma(v[(size_t)t * P.scen_pad], R, f);
+        }
+        if (s < P.scen_count) out[s] = R;
+        return;
+    }
+    Pair A{1.0, 0.0}, B{0.0, 0.0};
+    auto step = [&](double x, Pair f) {
+        const Pair q = exact_mul(A.hi, x);
+        A = {q.hi, fma(A.lo, x, q.lo)};
+        B = pair_step({x, 0.0}, B, f);
+    };
     if (sums_mid) {
         const double *vf = P.vf + off;
-        for (int t = hi - 1; t >= lo; --t) {
-            const double x = v[(size_t)t * P.scen_pad];
-            B = fma(x, B, fma(vf[(size_t)t * P.scen_pad], M[t], F[t]));
-            A *= x;
-        }
+        for (int t = hi - 1; t >= lo; --t)
+            step(v[(size_t)t * P.scen_pad], pair_step({vf[(size_t)t * P.scen_pad], 0.0}, {M[t], 0.0}, {F[t], 0.0}));
     } else {
         constexpr int U = 16;   // curve values in flight
         int t = hi - 1;
@@ -271,29 +310,18 @@ k_flow_totals(RecParams P, const double *__restrict__ sums, const double *__rest
 #pragma unroll
             for (int i = 0; i < U; ++i) x[i] = v[(size_t)(t - i) * P.scen_pad];
 #pragma unroll
-            for (int i = 0; i < U; ++i) {
-                B = fma(x[i], B, F[t - i]);
-                A *= x[i];
-            }
+            for (int i = 0; i < U; ++i) step(x[i], {F[t - i], 0.0});
         }
-        for (; t >= lo; --t) {
-            const double x = v[(size_t)t * P.scen_pad];
-            B = fma(x, B, F[t]);
-            A *= x;
-        }
-    }
-    if constexpr (CH == 1) {
-        if (s < P.scen_count) out[s] = B;
-        return;
+        for (; t >= lo; --t) step(v[(size_t)t * P.scen_pad], {F[t], 0.0});
     }
     sA[wave][lane] = A;
     sB[wave][lane] = B;
     __syncthreads();
     if (wave == 0 && s < P.scen_count) {
-        double R = F[len];
+        Pair R{F[len], 0.0};
 #pragma unroll
-        for (int w = CH - 1; w >= 0; --w) R = fma(sA[w][lane], R, sB[w][lane]);
-        out[s] = R;
+        for (int w = CH - 1; w >= 0; --w) R = pair_step(sA[w][lane], R, sB[w][lane]);
+        out[s] = isfinite(R.hi + R.lo) ? R.hi + R.lo : R.hi;   // (an overflow has no error term)
     }
 }
 
@@ -337,9 +365,9 @@ static size_t sums_lds(const RecParams &p, int set)
 
 bool flow_fits(const FlowShape &f, const RecParams &p, int set, bool has_mid, size_t lds_per_block)
 {
-    // 16 KiB of the totals kernel's LDS are its static part
+    // 32 KiB of the totals kernel's LDS are its static part
     return sums_lds(p, set) <= lds_per_block &&
-           (size_t)f.row_len * 8 * (has_mid ? 2 : 1) + (size_t)(16 << 10) <= lds_per_block;
+           (size_t)f.row_len * 8 * (has_mid ? 2 : 1) + (size_t)(32 << 10) <= lds_per_block;
 }
 
 template <bool LDSQ, int CHUNKS>

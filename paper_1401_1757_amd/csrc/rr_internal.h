@@ -92,7 +92,6 @@ struct RecParams {
     int n_steps;
     int scen_pad;
     const double *shock;      // [n_nodes]: multiplier on q (1.0 when none)
-    const double *disc;       // [n_nodes][disc_rows(n_steps)][scen_pad] discount products, or null
     // portfolio, sorted and padded to whole tiles
     const int *age1;          // attained age at node 0 (padding: 0)
     const int *age2;
@@ -107,7 +106,6 @@ struct RecParams {
     int cf_cols;
     const double *mk_w;       // [model][mk_ages][4][4] uploaded Markov matrices (zero padded),
                               // [model][mk_ages][9][9] for models of 5-9 states
-    const double *mk_wt;      // the four-state form transposed: [model][mk_ages][column][row]
     int mk_ages;
     int mk_states;
     const double *mk_c;       // [model][9] benefits per unit amount (models of 5-9 states)
@@ -120,8 +118,6 @@ struct RecParams {
     int ring_off;             // curve-ring launches: first double of the rings in LDS
     int path_lds;             // path output: first double of the wavefronts' stages in LDS
     const Tile *tiles;
-    const int *tile_order;    // [n_tiles] tiles, longest remaining term first
-    const int *tile_base;     // [n_tiles + 1] first month of a tile's kept flows (whole blocks of 8)
     int n_tiles;
     // work
     const Item *items;
@@ -140,6 +136,11 @@ struct RecParams {
     double *partial;          // [node_count][n_tiles][scen_count] or null
     double *path;             // or null
     const long long *path_off;  // [n_user + 1] (path mode)
+    // cash-flow kernels only (last, so that the recurrence kernels' argument loads stay as they are)
+    const double *disc;       // [n_nodes][disc_rows(n_steps)][scen_pad] discount products, or null
+    const double *mk_wt;      // the four-state form transposed: [model][mk_ages][column][row]
+    const int *tile_order;    // [n_tiles] tiles, longest remaining term first
+    const int *tile_base;     // [n_tiles + 1] first month of a tile's kept flows (whole blocks of 8)
 };
 
 // Curve ring (level scalar-reserve portfolios): each wavefront stages the
