@@ -329,11 +329,7 @@ extern "C" int rr_create(rr_ctx **out, int device, uint64_t stream)
     c->lds_per_cu = prop.maxSharedMemoryPerMultiProcessor > 0 ? prop.maxSharedMemoryPerMultiProcessor
                                                               : prop.sharedMemPerBlock;
     c->stream = (hipStream_t)(uintptr_t)stream;   // 0 = the null stream
-    if (hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking) != hipSuccess ||
-        hipStreamCreateWithFlags(&c->cap_side, hipStreamNonBlocking) != hipSuccess ||
-        hipEventCreateWithFlags(&c->cap_fork, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&c->cap_join, hipEventDisableTiming) != hipSuccess)
-        return RR_EDEVICE;
+    if (hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking) != hipSuccess) return RR_EDEVICE;
     void *scratch = nullptr;   // static scratch of rr_reserve_recurrence_noalloc on this device
     if (noalloc_scratch(device, &scratch) != hipSuccess) return RR_EDEVICE;
     c->scratch = static_cast<double *>(scratch);
@@ -1582,23 +1578,33 @@ static bool flow_totals_run(rr_ctx *c, const rr_run *run)
 
 // Largest share of a tile's kept flows: sixteen thousand months.
 constexpr long long kFlowTileDoubles = 1LL << 21;
-
-// The flows are written and read back once per policy and month, and the
-// product works on sixteen scenarios at least: 0.28 ms for 100,000 policies at
-// 2 scenarios as at 16, where the chains, with every month in registers, take
-// 0.077 and 0.206 ms.  The lines cross at 40 to 60 tiles a scenario (chains
-// against product: 5,000 policies x 2 0.053 / 0.052 ms, 30,000 x 5 0.091 / 0.111,
-// 30,000 x 8 0.114 / 0.111).
-constexpr long long kFlowTiles = 40;
+// Kept flows at a time (256 MiB).
+constexpr long long kFlowKept = 1LL << 25;
 
 // Whether the run's per-policy reserves come from the matrix product of the
 // policies' flows and the discount products: state-0 reserves of two scenarios
-// or more, and at most kFlowTiles tiles (at all nodes) per scenario.
+// or more, by the tiles (at all nodes) per scenario.
+//
+// The flows are written and read back once per policy and month, and the
+// product works on sixteen scenarios at least, so its time depends on the tiles
+// first; the chains keep every month in registers, but pay per scenario.  Up to
+// 64 tiles the walk is latency (chains against product: 500 level policies x 2
+// 0.065 / 0.044 ms, 5,003 x 2 0.054 / 0.055), past that level chains win down to
+// 16 tiles a scenario (30,000 x 12 0.068 / 0.075, x 24 0.076 / 0.080, x 35 0.094 /
+// 0.092; 10,000 x 10 0.065 / 0.062) and, where the flows come in batches and the
+// totals need a walk of their own, down to 10 (100,000 x 60 0.235 / 0.270, x 100
+// 0.343 / 0.351).  The chains of the other kinds of tiles cost several times as
+// much (8,000 of every product x 4 0.321 / 0.218, 60,000 annuities with patterns
+// x 60 0.441 / 0.298).
 static bool flow_reserves_run(rr_ctx *c, const rr_run *run)
 {
     if (!(run->out_mask & RR_OUT_R0) || (run->out_mask & (RR_OUT_PATH | RR_OUT_ALL_STATES))) return false;
     if (c->n_user == 0 || !c->has_disc || c->v_override) return false;
-    if (run->scen_count < 2 || (long long)c->n_tiles * run->node_count > kFlowTiles * run->scen_count) return false;
+    if (run->scen_count < 2) return false;
+    const long long tiles = (long long)c->n_tiles * run->node_count;
+    const bool whole = (long long)c->tile_base_host.back() * 64 * (c->has_frac ? 2 : 1) * run->node_count <= kFlowKept;
+    const int level = whole ? 16 : 10, other = whole ? 40 : 16;   // tiles per scenario
+    if (tiles > 64 && tiles > (long long)(c->flow_set ? other : level) * run->scen_count) return false;
     if ((long long)(c->max_term + DISC_BLOCK) * 128 > kFlowTileDoubles || c->tile_base_host.back() >= (1 << 30)) return false;
     return unpinned(c) && flow_ok(c, run);
 }
@@ -1614,6 +1620,16 @@ static void flow_work(const rr_ctx *c, const rr_run *run, long long most, long l
     if (!(run->out_mask & RR_OUT_R0)) return;
     const long long node = (long long)c->tile_base_host.back() * 64 * (c->has_frac ? 2 : 1);
     *kept = std::min(node * run->node_count, std::max(most - *totals, kFlowTileDoubles));
+}
+
+// The stream and events of a captured run's second branch, made before the
+// first capture that has one.
+static int branch_handles(rr_ctx *c)
+{
+    if (!c->cap_fork) HIPCHK(c, hipEventCreateWithFlags(&c->cap_fork, hipEventDisableTiming));
+    if (!c->cap_join) HIPCHK(c, hipEventCreateWithFlags(&c->cap_join, hipEventDisableTiming));
+    if (!c->cap_side) HIPCHK(c, hipStreamCreateWithFlags(&c->cap_side, hipStreamNonBlocking));
+    return RR_OK;
 }
 
 // The run by cash flows: reserves (if asked for), totals, statistics.  work:
@@ -1924,6 +1940,7 @@ static std::vector<uint64_t> run_key(rr_ctx *c, const rr_run *run, const rr_outp
 {
     uint64_t tail_bits;
     memcpy(&tail_bits, &run->tail, 8);
+    key.reserve(key.size() + 12);
     for (uint64_t x : {(uint64_t)run->node_begin, (uint64_t)run->node_count, (uint64_t)run->scen_begin,
                        (uint64_t)run->scen_count, (uint64_t)run->node_step_m, (uint64_t)run->out_mask,
                        (uint64_t)(uintptr_t)out->r0, (uint64_t)(uintptr_t)out->totals,
@@ -1999,10 +2016,11 @@ extern "C" int rr_reserve_recurrence(rr_ctx *c, const rr_run *run, const rr_outp
     int rc;
     if (flow_run(c, run)) {
         long long need, kept;
-        flow_work(c, run, 1LL << 25, &need, &kept);   // flows of 256 MiB at a time
+        flow_work(c, run, kFlowKept, &need, &kept);
         need += kept;
         if ((size_t)need > c->flow_work.n) drop_graphs(c);
         HIPCHK(c, c->flow_work.alloc((size_t)need));
+        if ((rc = branch_handles(c))) return rc;
         note_flow_launch(c);
         return launch_graphed(c, run_key(c, run, out, {1, (uint64_t)(uintptr_t)c->flow_work.p, (uint64_t)(uintptr_t)totals}),
                               [&](hipStream_t s, bool timed) {
