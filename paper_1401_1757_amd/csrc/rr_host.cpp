@@ -1151,11 +1151,11 @@ extern "C" int rr_node_expected_reserves(rr_ctx *c, const rr_run *run, double *n
                                       "(policy %d)", i);
     if (run->node_count == 0 || (!node_r0 && !node_totals)) return RR_OK;
     HIPCHK(c, hipSetDevice(c->device));
-    HIPCHK(c, c->mean_D.alloc((size_t)run->node_count * c->n_steps * run->scen_count));
+    if (!c->has_disc) HIPCHK(c, c->mean_D.alloc((size_t)run->node_count * c->n_steps * run->scen_count));
     HIPCHK(c, c->mean_v.alloc((size_t)c->n_nodes * c->n_steps * 64));
     HIPCHK(c, launch_mean_curve(c->v.p, c->n_steps, c->scen_pad, run->node_begin, run->node_count,
-                                run->scen_begin, run->scen_count, c->mean_D.p, c->mean_v.p,
-                                c->stream));
+                                run->scen_begin, run->scen_count, c->has_disc ? c->disc.p : nullptr,
+                                c->mean_D.p, c->mean_v.p, c->stream));
     // One scenario per node on the mean curve, through the ordinary path
     // (direct launches: a captured graph would hold the curve pointer).
     rr_run r = *run;

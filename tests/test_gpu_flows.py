@@ -246,3 +246,24 @@ def test_reserves_on_curves_whose_products_leave_the_range(ctx, big):
     upload(ctx, w)
     _say(f"reserves, factors {big}")
     check_reserves(ctx, w)
+
+
+@pytest.mark.parametrize("steps,scen,big", [(1, 1, 0.0), (15, 63, 0.0), (16, 64, 0.0), (17, 65, 0.0), (33, 257, 0.0),
+                                            (160, 70, 1.0e4)])
+def test_node_means_from_the_discount_products(ctx, steps, scen, big):
+    """Sixteen months a workgroup, 256 scenarios a round; a part of the
+    scenarios; curves without kept products (`big`)."""
+    w = every_kind(steps + scen, 150, steps, scen, 2, special=False, shock=big == 0.0)
+    if big:
+        w.basis.v[:, :, :60] = np.where(np.arange(60) % 2 == 0, big, 1.0 / big)
+        w.basis.v[:, :, 60:] = 1.0 / big
+    upload(ctx, w)
+    for s0, ns in ((0, scen), (scen // 3, scen - scen // 3)):
+        _say(f"node means {steps} steps, scenarios {s0}..{s0 + ns - 1}")
+        out = ctx.node_expected_reserves(0, 2, s0, ns, w.node_step_m)
+        torch.cuda.synchronize()
+        ref = oracle.reserves(w.basis, w.portfolio, 0, 2, s0, ns, w.node_step_m)
+        mean = ref["r_all"][..., 0].mean(axis=2)
+        assert np.all(np.abs(to_np(out["r0"]) - mean) <= RTOL * np.maximum(np.abs(mean), ref["gross"].mean(axis=2)))
+        total = ref["totals"].mean(axis=1)
+        assert np.all(np.abs(to_np(out["totals"]) - total) <= RTOL * np.maximum(ref["gross_totals"].mean(axis=1), 1e-300))
