@@ -388,11 +388,12 @@ def representative_leg(rr, synth, sync, steps=5):
         ctx.set_option(rr.OPT_KERNEL_TIMING, 0)
         flops, ops, live, vsteps = scenario_step_work(pf)
         ms = 1e3 * e / steps
-        achieved = flops * b.n_scen / (kms * 1e-3) / 1e12
+        chains = ctx.get_option(rr.OPT_LAST_K) > 0   # else summed cash flows: other work
+        achieved = flops * b.n_scen / (kms * 1e-3) / 1e12 if chains else None
         return {"workload": w.name, "policies": pf.n, "scenarios": b.n_scen,
                 "ms_per_step": ms, "kernel_ms": kms,
-                "kernel_tflops": achieved, "kernel_frac_fp64_peak": achieved / FP64_PEAK_TFLOPS,
-                "kernel_issue_frac": ops * b.n_scen / (kms * 1e-3) / FP64_ISSUE_PEAK,
+                "kernel_tflops": achieved, "kernel_frac_fp64_peak": achieved / FP64_PEAK_TFLOPS if chains else None,
+                "kernel_issue_frac": ops * b.n_scen / (kms * 1e-3) / FP64_ISSUE_PEAK if chains else None,
                 "valuations_per_s": live * b.n_scen / (e / steps),
                 "valuation_steps_per_s": vsteps * b.n_scen / (e / steps),
                 "escalating": int((pf.escalation > 0).sum()), "annual": int(pf.annual.sum()),
@@ -551,9 +552,12 @@ def main():
     kms = ctx.kernel_times()
     ctx.set_option(rr.OPT_KERNEL_TIMING, 0)
     kernel_ms = float(np.mean(kms))
-    achieved = flops * b.n_scen / (kernel_ms * 1e-3) / 1e12
-    issue_frac = ops * b.n_scen / (kernel_ms * 1e-3) / FP64_ISSUE_PEAK
     k_opt = ctx.get_option(rr.OPT_LAST_K)
+    by_flows = k_opt == 0      # no recurrence kernel: cash flows x discount products
+    if by_flows:               # one multiply-add per valuation step, on the matrix cores
+        flops, ops = 2 * vsteps, vsteps
+    achieved = flops * b.n_scen / (kernel_ms * 1e-3) / 1e12
+    issue_frac = None if by_flows else ops * b.n_scen / (kernel_ms * 1e-3) / FP64_ISSUE_PEAK
     wg_opt = ctx.get_option(rr.OPT_LAST_WG)
     j_opt = ctx.get_option(rr.OPT_LAST_J)
     ring_opt = ctx.get_option(rr.OPT_LAST_RING)
@@ -576,9 +580,10 @@ def main():
                    "max_steps": b.n_steps, "valuations_per_step": n_val,
                    "valuation_steps_per_step": vsteps * b.n_scen,
                    "outputs": "r0 [policy][scenario] + totals + tail statistic"},
-        "roofline": {"bound": "alu", "achieved": achieved, "peak": FP64_PEAK_TFLOPS,
+        "roofline": {"bound": "mfma" if by_flows else "alu", "achieved": achieved, "peak": FP64_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": achieved / FP64_PEAK_TFLOPS, "traffic": traffic,
-                     "kernel": "k_recurrence", "kernel_ms": kernel_ms,
+                     "kernel": "k_flow_sums, k_reserve_mm, k_flow_totals" if by_flows else "k_recurrence",
+                     "kernel_ms": kernel_ms,
                      "kernel_launches": len(kms),
                      "algorithmic_flops_per_launch": flops * b.n_scen,
                      "algorithmic_bytes_per_launch": algorithmic_bytes(b, pf),
@@ -626,14 +631,16 @@ def main():
         ctx.set_option(rr.OPT_KERNEL_TIMING, 0)
         flops4 = sum(scenario_step_work(w4.portfolio, k, 12)[0] for k in range(w4.basis.n_nodes))
         flops4 *= w4.basis.n_scen
+        chains4 = ctx.get_option(rr.OPT_LAST_K) > 0   # else summed cash flows: other work
         sec["C4_nested_60_nodes"] = {"valuations_per_s": live4 * w4.basis.n_scen / (e4 / 10),
                                      "ms_per_step": 1e3 * e4 / 10,
                                      "live_valuations": live4 * w4.basis.n_scen,
                                      "nominal_valuations": w4.portfolio.n * w4.basis.n_nodes * w4.basis.n_scen,
                                      "kernel_ms": k4,
                                      "algorithmic_flops_per_launch": flops4,
-                                     "kernel_tflops": flops4 / (k4 * 1e-3) / 1e12,
-                                     "kernel_frac_fp64_peak": flops4 / (k4 * 1e-3) / 1e12 / FP64_PEAK_TFLOPS,
+                                     "kernel_tflops": flops4 / (k4 * 1e-3) / 1e12 if chains4 else None,
+                                     "kernel_frac_fp64_peak": flops4 / (k4 * 1e-3) / 1e12 / FP64_PEAK_TFLOPS
+                                     if chains4 else None,
                                      "launch": {"block_k": ctx.get_option(rr.OPT_LAST_K),
                                                 "block_j": ctx.get_option(rr.OPT_LAST_J),
                                                 "wg_per_cu": ctx.get_option(rr.OPT_LAST_WG)}}
