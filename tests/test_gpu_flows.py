@@ -267,3 +267,13 @@ def test_node_means_from_the_discount_products(ctx, steps, scen, big):
         assert np.all(np.abs(to_np(out["r0"]) - mean) <= RTOL * np.maximum(np.abs(mean), ref["gross"].mean(axis=2)))
         total = ref["totals"].mean(axis=1)
         assert np.all(np.abs(to_np(out["totals"]) - total) <= RTOL * np.maximum(ref["gross_totals"].mean(axis=1), 1e-300))
+
+
+@pytest.mark.parametrize("n,scen", [(4096, 2), (4160, 4), (4160, 5)])
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_reserves_both_sides_of_the_tile_rule(ctx, n, scen, noalloc):
+    """64 tiles, and 65 at more and fewer than sixteen a scenario."""
+    w = every_kind(n + scen, n, 20, scen, 1, special=False, products=(0,))
+    upload(ctx, w)
+    _say(f"reserves {n} policies x {scen}")
+    check_reserves(ctx, w, noalloc=noalloc)
