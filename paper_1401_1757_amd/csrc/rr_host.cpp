@@ -1635,13 +1635,19 @@ static int branch_handles(rr_ctx *c)
 // The run by cash flows: reserves (if asked for), totals, statistics.  work:
 // flow_work's two parts, one after the other.
 //
-// Under capture (cap) the totals and the statistic are a branch of their own
-// beside the product, which leaves half of a CU's wavefront slots free: 10,000
-// policies x 1,000 scenarios 0.178 -> 0.165 ms.
+// Under capture the totals and the statistic of a large run are a branch of
+// their own beside the product, which leaves half of a CU's wavefront slots
+// free: 10,000 policies x 1,000 scenarios 0.178 -> 0.165 ms.  A graph with a fork
+// and a join starts some 15 us later than a plain sequence, which is more than
+// the branch saves a small run: 1,002 x 9 0.053 with the branch, 0.038 without;
+// 340 x 16 0.048 / 0.033; 10,000 x 200 (31,400 tiles x scenarios) 0.096 without.
+constexpr long long kBranchTiles = 40000;   // tiles x scenarios
+
 static int enqueue_flow_run(rr_ctx *c, const rr_run *run, const rr_outputs *out, double *work, long long kept,
                             double *totals, hipStream_t s, bool timed)
 {
-    const bool branch = s == c->cap_stream && totals && (run->out_mask & RR_OUT_R0);
+    const bool branch = s == c->cap_stream && totals && (run->out_mask & RR_OUT_R0) &&
+                        (long long)c->n_tiles * run->node_count * run->scen_count > kBranchTiles;
     auto sums = [&](const RecParams &P, const FlowShape &f, bool have_rows) -> int {
         hipStream_t q = s;
         if (branch) {
