@@ -284,8 +284,12 @@ int rr_basis_generate_vasicek(rr_ctx *ctx, const rr_basis *b, const rr_vasicek *
 
 /* Regenerate the installed basis's curves in place (same sizes), e.g. for the
  * next outer node of a nested valuation: asynchronous on the context's stream;
- * portfolio, plans and captured graphs stay valid.  Waits for the stream only
- * when vs->r0 differs from the values of the previous generation. */
+ * portfolio, plans and captured graphs stay valid, the caller's own too: what a
+ * graph captured from rr_reserve_recurrence_noalloc reads is renewed in place (a
+ * graph captured while the curves' bounds allowed it may work on the discount
+ * products of the curves; those beyond the FP64 range are its largest value).
+ * Waits for the stream only when vs->r0 differs from the values of the
+ * previous generation. */
 int rr_curves_generate_vasicek(rr_ctx *ctx, const rr_vasicek *vs);
 
 /* The curves of a generator in caller-owned device memory (asynchronous):

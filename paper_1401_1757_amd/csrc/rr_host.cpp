@@ -465,6 +465,8 @@ extern "C" int rr_get_option(rr_ctx *c, int32_t option, int64_t *value)
 // survival probabilities in FP64.
 constexpr double kSafeLogSpan = 600.0;
 
+static bool safe_products(const rr_ctx *c) { return c->curve_log_span <= kSafeLogSpan; }   // (NaN: no)
+
 static int stage_tables(rr_ctx *c)
 {
     // Keep only the ages the portfolio can reach, so the tables fit in LDS,
@@ -568,11 +570,15 @@ static int enqueue_vasicek(rr_ctx *c, const VasParams &P, const std::vector<doub
 // Room for the discount products of the curves to come, kept beside them (8
 // bytes per curve value): given where no product can leave the FP64 range and
 // the memory is there; without them (null) runs take the recurrence kernel.
+// Room that is there already is always filled: a graph that the caller captured
+// may read it, and replays have to see the present curves' products.
 static double *discount_room(rr_ctx *c)
 {
+    const size_t need = (size_t)c->n_nodes * disc_rows(c->n_steps) * c->scen_pad;
     c->has_disc = false;
-    if (!(c->curve_log_span <= kSafeLogSpan)) return nullptr;
-    if (c->disc.alloc((size_t)c->n_nodes * disc_rows(c->n_steps) * c->scen_pad) == hipSuccess) return c->disc.p;
+    if (c->disc.p && c->disc.n >= need) return c->disc.p;
+    if (!safe_products(c)) return nullptr;
+    if (c->disc.alloc(need) == hipSuccess) return c->disc.p;
     (void)hipGetLastError();
     return nullptr;
 }
@@ -643,7 +649,7 @@ static int install_basis(rr_ctx *c, const rr_basis *b, std::vector<double> &q,
         HIPCHK(c, c->vf.alloc((size_t)nvv));
         HIPCHK(c, launch_pow_curves(c->v.p, c->vf.p, nvv, c->frac, c->stream));
     }
-    c->has_disc = D != nullptr;
+    c->has_disc = D && safe_products(c);
     HIPCHK(c, c->shock.alloc((size_t)b->n_nodes));
     HIPCHK(c, hipMemcpy(c->shock.p, c->shock_host.data(), sizeof(double) * b->n_nodes,
                         hipMemcpyHostToDevice));
@@ -711,12 +717,12 @@ extern "C" int rr_curves_generate_vasicek(rr_ctx *c, const rr_vasicek *vs)
     int rc;
     if ((rc = vasicek_params(c, vs, c->n_nodes, c->n_scen, c->n_steps, c->scen_pad, &P, &r0))) return rc;
     ++c->curve_gen;   // cached per-scenario decisions (the surrogate's range flags) are stale
-    const double span = vasicek_log_span(P, r0);
-    if ((span <= kSafeLogSpan) != (c->curve_log_span <= kSafeLogSpan)) drop_graphs(c);   // other kernels
-    c->curve_log_span = span;
+    const bool safe = safe_products(c);
+    c->curve_log_span = vasicek_log_span(P, r0);
+    if (safe != safe_products(c)) drop_graphs(c);   // other kernels
     double *D = discount_room(c);
     if ((rc = enqueue_vasicek(c, P, r0, c->v.p, 1, nullptr, D))) return rc;
-    c->has_disc = D != nullptr;
+    c->has_disc = D && safe_products(c);
     return RR_OK;
 }
 
@@ -1655,7 +1661,7 @@ static int enqueue_flow_run(rr_ctx *c, const rr_run *run, const rr_outputs *out,
             HIPCHK(c, hipStreamWaitEvent(c->cap_side, c->cap_fork, 0));
             q = c->cap_side;
         }
-        HIPCHK(c, launch_flow_totals(P, run->node_count, f, c->flow_set, c->has_frac, c->curve_log_span <= kSafeLogSpan,
+        HIPCHK(c, launch_flow_totals(P, run->node_count, f, c->flow_set, c->has_frac, safe_products(c),
                                      have_rows, c->max_term, work, totals, q));
         return branch ? enqueue_stats(c, run, out, totals, q) : RR_OK;
     };

@@ -11,6 +11,7 @@
 #include "rr_internal.h"
 
 #include <algorithm>
+#include <cfloat>
 
 namespace rr {
 
@@ -79,7 +80,9 @@ __global__ void __launch_bounds__(256) k_vas_normals(VasParams P, double *__rest
 // month_major: v[(k * n_steps + t) * ld + s] (the library's curve layout,
 // padding scenarios set to 1), else v[(k * n_scen + s) * n_steps + t].  r (or
 // null): r[(k * (n_steps + 1) + t) * scen_pad + s], t = 0 .. n_steps.  D (or
-// null; month-major): D[(k * disc_rows + t) * scen_pad + s], zeros past t = n_steps.
+// null; month-major): D[(k * disc_rows + t) * scen_pad + s], zeros past t = n_steps;
+// products beyond the FP64 range are its largest value, so that a policy whose
+// flows are over by then still adds 0 x D = 0.
 //
 // Bound by latency at the usual sizes (a thread's loads go out together) and by
 // the 32 bytes a value that it moves at many curves.  It takes the place of a
@@ -157,7 +160,7 @@ k_vas_scan(VasParams P, int node0, const double *__restrict__ r0, const double *
                 for (int i = 0; i < SCAN_LEN; ++i) {
                     if (i >= per) continue;
                     d *= za[i];
-                    if (t0 + i < n) Dk[(size_t)(t0 + i + 1) * row] = d;
+                    if (t0 + i < n) Dk[(size_t)(t0 + i + 1) * row] = fmin(d, DBL_MAX);
                 }
                 if (c == SCAN_C - 1) s_disc[lane] = d;
             }

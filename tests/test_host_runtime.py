@@ -1,0 +1,118 @@
+"""The library's host code on a stand-in for the HIP runtime (hip_double.cpp; no
+GPU, no kernel runs): which kernels a call launches, what it does when device
+memory runs out, and what may be destroyed while the GPU is still at work.
+Each test is a program of its own, in a child process that loads the stand-in
+before the library."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = """
+import ctypes, sys
+import numpy as np
+hd = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+hd.hd_log.restype = hd.hd_faults.restype = ctypes.c_char_p
+hd.hd_used.restype = hd.hd_buffer_end.restype = ctypes.c_uint64
+for f, a in ((hd.hd_set_memory, [ctypes.c_uint64]), (hd.hd_buffer_end, [ctypes.c_uint64]),
+             (hd.hd_set_capturing, [ctypes.c_uint64, ctypes.c_int])):
+    f.argtypes = a
+import paper_1401_1757_amd as rr
+import synth
+lib = rr.load_library()
+STREAM = 0x51000          # the caller's stream (a name: the stand-in never looks behind it)
+SAFE, WIDE = dict(a=0.1, b=0.03, sigma=0.01), dict(a=0.02, b=0.03, sigma=0.01)
+
+
+class Ctx:
+    def __init__(self):
+        self.h = ctypes.c_void_p()
+        assert lib.rr_create(ctypes.byref(self.h), 0, STREAM) == 0
+
+    def ok(self, rc):
+        assert rc == 0, (rc, lib.rr_last_error(self.h))
+
+    def generate(self, q, n_scen, n_steps, nodes=1, frac=0.0, **vs):
+        keep = []
+        q = np.ascontiguousarray(q)
+        b = rr.Basis(q.shape[0], q.shape[1], q.ctypes.data, nodes, n_scen, n_steps, None, None, rr.HOST, frac)
+        self.ok(lib.rr_basis_generate_vasicek(self.h, ctypes.byref(b), ctypes.byref(self.vas(nodes, keep, vs))))
+
+    def vas(self, nodes, keep, vs):
+        return rr.vasicek_struct(vs["a"], vs["b"], vs["sigma"], 1.0 / 12.0, [0.03] * nodes, (3, 4), keep)
+
+    def regenerate(self, nodes=1, **vs):
+        keep = []
+        self.ok(lib.rr_curves_generate_vasicek(self.h, ctypes.byref(self.vas(nodes, keep, vs))))
+
+    def portfolio(self, pf):
+        keep = []
+        self.ok(lib.rr_portfolio_upload(self.h, ctypes.byref(rr.portfolio_struct(pf, keep))))
+        self.n = pf.n
+
+    def run(self, nodes, scen, mask, noalloc=False, at=1):
+        # output buffers are never touched: made-up addresses, another set per `at`
+        r = rr.Run(0, nodes, 0, scen, 12, mask, 0.005)
+        base = at << 40
+        o = rr.Outputs(base, base + (1 << 38), None, 0, base + (1 << 39))
+        f = lib.rr_reserve_recurrence_noalloc if noalloc else lib.rr_reserve_recurrence
+        return f(self.h, ctypes.byref(r), ctypes.byref(o))
+
+
+def log():
+    s = hd.hd_log().decode()
+    hd.hd_clear()
+    return s
+
+
+def book(n, n_steps, products=(0, 1, 4, 5), seed=1, scen=2):
+    w = synth.random_small(np.random.default_rng(seed), n=n, n_steps=n_steps, n_scen=scen, products=products)
+    return w.basis.q, w.portfolio
+"""
+
+
+@pytest.fixture(scope="module")
+def double(tmp_path_factory):
+    import paper_1401_1757_amd as rr
+    if not os.path.exists(rr.LIB_PATH):
+        from paper_1401_1757_amd import build
+        build.build()
+    so = str(tmp_path_factory.mktemp("hip") / "libhip_double.so")
+    subprocess.check_call(["g++", "-shared", "-fPIC", "-O1", "-std=c++17", "-I", "/opt/rocm/include", "-o", so,
+                           os.path.join(ROOT, "tests", "hip_double.cpp")])
+    return so
+
+
+def run(double, program):
+    code = PRELUDE + textwrap.dedent(program)
+    res = subprocess.run([sys.executable, "-c", code, double], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stdout[-2000:] + res.stderr[-3000:]
+
+
+@pytest.mark.parametrize("model", ["SAFE", "WIDE"])
+def test_discount_products_follow_every_regeneration(double, model):
+    """A graph that the caller captured reads the kept discount products, so
+    curves regenerated in place renew them whatever the model's range, also
+    where runs made afterwards go by the recurrence kernel."""
+    run(double, f"""
+    q, pf = book(300, 120)
+    c = Ctx()
+    c.generate(q, 70, 600, **SAFE)
+    first = log()
+    D = [int(l.split(" D ")[1]) for l in first.splitlines() if "k_vas_scan" in l]
+    assert len(D) == 1 and D[0], first
+    c.portfolio(pf)
+    hd.hd_set_capturing(STREAM, 1)
+    c.ok(c.run(1, 70, rr.OUT_R0 | rr.OUT_TOTALS, noalloc=True))
+    hd.hd_set_capturing(STREAM, 0)
+    assert "k_reserve_mm" in log() and not hd.hd_faults()
+    c.regenerate(**{model})
+    again = log()
+    assert [int(l.split(" D ")[1]) for l in again.splitlines() if "k_vas_scan" in l] == D, again
+    c.ok(c.run(1, 70, rr.OUT_R0, noalloc=True))
+    assert ("k_reserve_mm" in log()) == ({model} is SAFE)
+    """)
