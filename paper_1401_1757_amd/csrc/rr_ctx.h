@@ -98,6 +98,13 @@ struct GraphEntry {
     std::vector<uint64_t> key;
 };
 
+// Graphs no longer used, kept until the launches made before `done` was
+// recorded have finished (null: until the device is idle).
+struct RetiredGraphs {
+    hipEvent_t done = nullptr;
+    std::vector<GraphEntry> graphs;
+};
+
 }  // namespace host
 }  // namespace rr
 
@@ -208,6 +215,7 @@ struct rr_ctx {
 
     // graphs
     std::vector<GraphEntry> graphs;
+    std::vector<rr::host::RetiredGraphs> retired;   // oldest first
 
     // work lists of the surrogate's exact fallback
     Plan item_plan[2];

@@ -340,13 +340,50 @@ extern "C" int rr_create(rr_ctx **out, int device, uint64_t stream)
     return RR_OK;
 }
 
-static void drop_graphs(rr_ctx *c)
+// Destroy the retired graphs whose launches have finished; all of them, waiting,
+// where there are more than a few sets or one of them has no event.  An
+// executable graph must not go while a launch of it runs: with two branches the
+// process ended on a lock that had gone with it.
+constexpr size_t kRetiredSets = 4;
+
+static void reap_graphs(rr_ctx *c, bool all)
 {
-    for (auto &g : c->graphs) {
-        if (g.exec) (void)hipGraphExecDestroy(g.exec);
-        if (g.graph) (void)hipGraphDestroy(g.graph);
+    for (const auto &r : c->retired)
+        if (!r.done) {
+            (void)hipDeviceSynchronize();
+            all = true;
+            break;
+        }
+    while (!c->retired.empty()) {
+        auto &r = c->retired.front();
+        if (r.done && hipEventQuery(r.done) == hipErrorNotReady) {
+            (void)hipGetLastError();   // (not an error of the caller's)
+            if (!all && c->retired.size() <= kRetiredSets) break;
+            (void)hipEventSynchronize(r.done);
+        }
+        for (auto &g : r.graphs) {
+            if (g.exec) (void)hipGraphExecDestroy(g.exec);
+            if (g.graph) (void)hipGraphDestroy(g.graph);
+        }
+        if (r.done) (void)hipEventDestroy(r.done);
+        c->retired.erase(c->retired.begin());
     }
-    c->graphs.clear();
+}
+
+// Forget the captured graphs.  Their launches may still run, and the call does
+// not wait for them.  hold: no stream may be touched now.
+static void drop_graphs(rr_ctx *c, bool hold = false)
+{
+    if (c->graphs.empty()) return;
+    rr::host::RetiredGraphs r;
+    r.graphs.swap(c->graphs);
+    if (!hold && hipEventCreateWithFlags(&r.done, hipEventDisableTiming) == hipSuccess &&
+        hipEventRecord(r.done, c->stream) != hipSuccess) {
+        (void)hipEventDestroy(r.done);
+        r.done = nullptr;
+    }
+    c->retired.push_back(std::move(r));
+    if (!hold) reap_graphs(c, false);
 }
 
 extern "C" int rr_destroy(rr_ctx *c)
@@ -355,6 +392,7 @@ extern "C" int rr_destroy(rr_ctx *c)
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
     drop_graphs(c);
+    reap_graphs(c, true);
     for (auto &e : c->ev_pending) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
     for (auto &e : c->ev_free) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
     rr::surrogate_destroy(c->sur);
@@ -375,7 +413,12 @@ extern "C" const char *rr_last_error(const rr_ctx *c) { return c ? c->err.c_str(
 extern "C" int rr_set_stream(rr_ctx *c, uint64_t stream)
 {
     if (!c) return RR_EINVAL;
-    drop_graphs(c);
+    // (while the caller captures the new stream, nothing may be done on another)
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (stream && !c->graphs.empty() &&
+        hipStreamIsCapturing((hipStream_t)(uintptr_t)stream, &status) != hipSuccess)
+        status = hipStreamCaptureStatusActive;
+    drop_graphs(c, status != hipStreamCaptureStatusNone);
     c->stream = (hipStream_t)(uintptr_t)stream;
     return RR_OK;
 }

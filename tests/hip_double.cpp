@@ -39,6 +39,7 @@ std::map<hipStream_t, Graph *> g_captures;   // by the capture's origin
 std::string g_log, g_faults;
 size_t g_used = 0, g_limit = (size_t)1 << 36;
 long long g_ticket = 0, g_done = 0;          // work handed out, work known to be finished
+int g_execs = 0, g_waits = 0;                // executable graphs alive; waits for the GPU
 hipError_t g_last = hipSuccess;
 dim3 g_grid, g_block;
 size_t g_shmem = 0;
@@ -83,6 +84,9 @@ extern "C" {
 // -- what the test reads and sets
 const char *hd_log() { return g_log.c_str(); }
 const char *hd_faults() { return g_faults.c_str(); }
+int hd_last_error() { return (int)g_last; }
+int hd_live_execs() { return g_execs; }
+int hd_waits() { return g_waits; }
 void hd_clear()
 {
     g_log.clear();
@@ -229,11 +233,13 @@ hipError_t hipStreamDestroy(hipStream_t s)
 hipError_t hipStreamSynchronize(hipStream_t)
 {
     not_in_capture("hipStreamSynchronize");
+    ++g_waits;
     g_done = g_ticket;
     return hipSuccess;
 }
 hipError_t hipDeviceSynchronize(void)
 {
+    ++g_waits;
     g_done = g_ticket;
     return hipSuccess;
 }
@@ -256,10 +262,11 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
 }
 hipError_t hipEventSynchronize(hipEvent_t e)
 {
+    ++g_waits;
     g_done = std::max(g_done, ((Event *)e)->ticket);
     return hipSuccess;
 }
-hipError_t hipEventQuery(hipEvent_t e) { return ((Event *)e)->ticket <= g_done ? hipSuccess : hipErrorNotReady; }
+hipError_t hipEventQuery(hipEvent_t e) { return err(((Event *)e)->ticket <= g_done ? hipSuccess : hipErrorNotReady); }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t)
 {
     *ms = 0.1f;
@@ -298,6 +305,7 @@ hipError_t hipStreamEndCapture(hipStream_t s, hipGraph_t *g)
 hipError_t hipGraphInstantiate(hipGraphExec_t *x, hipGraph_t g, hipGraphNode_t *, char *, size_t)
 {
     Exec *e = new Exec();
+    ++g_execs;
     e->work = ((Graph *)g)->work;
     *x = (hipGraphExec_t)e;
     return hipSuccess;
@@ -311,6 +319,7 @@ hipError_t hipGraphLaunch(hipGraphExec_t x, hipStream_t)
 hipError_t hipGraphExecDestroy(hipGraphExec_t x)
 {
     if (((Exec *)x)->last > g_done) g_faults += "executable graph destroyed before its launch has finished\n";
+    --g_execs;
     delete (Exec *)x;
     return hipSuccess;
 }

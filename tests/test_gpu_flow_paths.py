@@ -1,5 +1,6 @@
 """Runs by cash flows (test_gpu_flows.py) in the situations that need a size, a
-graph or a change of curves of their own: graphs that the caller captured."""
+graph or a change of curves of their own: graphs that the caller captured, and
+the library's own graphs with a second branch."""
 import sys
 
 import numpy as np
@@ -80,6 +81,45 @@ def test_caller_graph_follows_regenerated_curves(rr, frac):
                 err = np.abs(to_np(out["totals"]) - ref["totals"])
                 assert np.all(err <= RTOL * ref["gross_totals"])
                 assert np.array_equal(to_np(out["stats"])[:, 1], oracle.node_stats(to_np(out["totals"]))[1])
+    finally:
+        torch.cuda.synchronize()
+        ctx.close()
+
+
+def test_two_branch_graphs_over_many_output_sets(rr):
+    """Runs large enough for the graph's second branch (more than 40,000 tiles x
+    scenarios), on more output sets than graphs are kept, without a wait
+    between them and with other work on the stream: every set is that of the
+    direct launches, bit for bit, and no graph goes while it runs."""
+    rng = np.random.default_rng(61)
+    n, scen, sets = 9_000, 300, 14
+    assert (n // 64) * scen > 40_000
+    w = synth.random_small(rng, n=n, n_steps=60, n_scen=scen, n_nodes=1, products=(0, 1, 4, 5))
+    ctx = rr.Context(0)
+    try:
+        ctx.basis_upload(w.basis.q, w.basis.v)
+        ctx.portfolio_upload(w.portfolio)
+        ctx.set_option(rr.OPT_USE_GRAPH, 0)
+        _say("direct launches")
+        ref = ctx.reserve_recurrence(0, 1, 0, scen, 12, ctx.alloc_outputs(1, scen, stats=True))
+        assert ctx.get_option(rr.OPT_LAST_K) == 0
+        torch.cuda.synchronize()
+        ctx.set_option(rr.OPT_USE_GRAPH, 1)
+        outs = [ctx.alloc_outputs(1, scen, stats=True) for _ in range(sets)]
+        for rep in range(3):
+            _say(f"round {rep}")
+            for o in outs:
+                for x in o.values():
+                    x.fill_(float("nan"))
+            kept = []
+            for i, o in enumerate(outs):
+                ctx.reserve_recurrence(0, 1, 0, scen, 12, o)
+                if i % 3 == 0:   # a replay of the graph just made, and a read behind it
+                    ctx.reserve_recurrence(0, 1, 0, scen, 12, o)
+                    kept.append({k: x.clone() for k, x in o.items()})
+            torch.cuda.synchronize()
+            for o in outs + kept:
+                assert all(torch.equal(o[k], ref[k]) for k in ref)
     finally:
         torch.cuda.synchronize()
         ctx.close()

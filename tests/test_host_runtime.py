@@ -116,3 +116,53 @@ def test_discount_products_follow_every_regeneration(double, model):
     c.ok(c.run(1, 70, rr.OUT_R0, noalloc=True))
     assert ("k_reserve_mm" in log()) == ({model} is SAFE)
     """)
+
+
+def test_graphs_are_destroyed_after_their_launches(double):
+    """More output sets than graphs are kept, a larger run, another stream, other
+    options, other uploads: no executable graph is destroyed while a launch of
+    it may still run, nothing waits on the way, and those set aside stay few."""
+    run(double, """
+    q, pf = book(3000, 60)
+    c = Ctx()
+    c.generate(q, 1000, 60, **SAFE)
+    c.portfolio(pf)
+    mask = rr.OUT_R0 | rr.OUT_TOTALS | rr.OUT_STATS
+    for at in range(1, 40):
+        c.ok(c.run(1, 1000, mask, at=at))
+        assert hd.hd_live_execs() <= 8 * 6, hd.hd_live_execs()
+    assert "graph: " in log()
+    c.ok(lib.rr_set_option(c.h, rr.OPT_BLOCK_K, 8))
+    c.ok(lib.rr_set_option(c.h, rr.OPT_BLOCK_J, 1))
+    c.ok(lib.rr_set_option(c.h, rr.OPT_WG_PER_CU, 1))
+    for at in range(1, 12):
+        c.ok(c.run(1, 1000, mask, at=at))
+    c.ok(lib.rr_set_option(c.h, rr.OPT_CURVE_SHARE, 0))
+    c.ok(c.run(1, 1000, mask))
+    c.ok(lib.rr_set_stream(c.h, STREAM + 0x100))
+    c.ok(c.run(1, 1000, mask))
+    c.regenerate(**WIDE)
+    c.ok(c.run(1, 1000, mask))
+    c.portfolio(book(5000, 60, seed=2)[1])
+    c.ok(c.run(1, 1000, mask))
+    c.generate(q, 2000, 60, **SAFE)
+    c.ok(c.run(1, 2000, mask))
+    assert not hd.hd_faults(), hd.hd_faults()
+    lib.rr_destroy(c.h)
+    assert not hd.hd_faults() and hd.hd_live_execs() == 0, hd.hd_faults()
+    """)
+
+
+def test_dropping_graphs_does_not_wait(double):
+    run(double, """
+    q, pf = book(300, 60)
+    c = Ctx()
+    c.generate(q, 70, 60, **SAFE)
+    c.portfolio(pf)
+    c.ok(c.run(1, 70, rr.OUT_R0 | rr.OUT_TOTALS))
+    waits = hd.hd_waits()
+    for at in range(1, 20):
+        c.ok(c.run(1, 70, rr.OUT_R0 | rr.OUT_TOTALS, at=at))
+    c.ok(lib.rr_set_stream(c.h, STREAM + 0x100))
+    assert hd.hd_waits() == waits and hd.hd_last_error() == 0
+    """)
