@@ -147,7 +147,7 @@ struct rr_ctx {
     std::vector<double> shock_host;
     DevBuf<double> disc;                 // [n_nodes][disc_rows][scen_pad] discount products of v
     bool has_disc = false;               // disc holds the present curves' products
-    double curve_log_span = 0.0;         // bound on |log| of any product of one scenario's factors
+    double curve_log_step = 0.0;         // bound on |log| of any discount factor
 
     // portfolio
     bool has_pf = false;

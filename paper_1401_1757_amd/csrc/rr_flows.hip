@@ -240,20 +240,19 @@ __device__ __forceinline__ Pair pair_step(Pair x, Pair r, Pair f)
 // Totals of 64 scenarios of a node: R_t = F_t + vf_t M_t + v_t R_{t+1} from the
 // last flow down to t = 0 (M: the flows within the month, discounted by
 // vf = v^frac).  CH wavefronts take a time chunk each as the affine map
-// R_lo = A R_hi + B (A the chunk's discount product), composed in order; CH = 1
-// is the plain recurrence, for curves whose products could leave the FP64
-// range.  Reads every live curve value once: bound by that read at many nodes,
-// by the chunk's serial chain at one.
+// R_lo = A R_hi + B (A the chunk's discount product), composed in order.  Reads
+// every live curve value once: bound by that read at many nodes, by the chunk's
+// serial chain at one.
 //
 // One chain carries the whole portfolio, so its rounding errors do not average
 // out as those of the policies' own chains do (10,000 policies x 60 nodes:
-// 1.0e-15 against 0.95e-15): the chunked form keeps the error of every operation
-// beside the value.
-template <int CH>
-__global__ void __launch_bounds__(64 * CH)
+// 1.0e-15 against 0.95e-15): the error of every operation is kept beside the
+// value.
+__global__ void __launch_bounds__(64 * FLOW_TOTALS_CHUNKS)
 k_flow_totals(RecParams P, const double *__restrict__ sums, const double *__restrict__ sums_mid, int n_sums,
               int row_len, int max_term, int node_begin, double *__restrict__ totals)
 {
+    constexpr int CH = FLOW_TOTALS_CHUNKS;
     extern __shared__ double s_mem[];   // F[len + 1], then M[len + 1]
     __shared__ Pair sA[CH][64], sB[CH][64];
     const int node_rel = blockIdx.y, node = node_begin + node_rel;
@@ -283,15 +282,6 @@ k_flow_totals(RecParams P, const double *__restrict__ sums, const double *__rest
     const int lo = wave * per, hi = min(lo + per, len);
     const size_t off = (size_t)node * P.n_steps * P.scen_pad + P.scen_begin + min(s, P.scen_count - 1);
     const double *v = P.v + off;
-    if constexpr (CH == 1) {
-        double R = F[len];
-        for (int t = len - 1; t >= 0; --t) {
-            const double f = sums_mid ? fma(P.vf[off + (size_t)t * P.scen_pad], M[t], F[t]) : F[t];
-            R = fma(v[(size_t)t * P.scen_pad], R, f);
-        }
-        if (s < P.scen_count) out[s] = R;
-        return;
-    }
     Pair A{1.0, 0.0}, B{0.0, 0.0};
     auto step = [&](double x, Pair f) {
         const Pair q = exact_mul(A.hi, x);
@@ -411,8 +401,8 @@ hipError_t launch_flow_store(const RecParams &p, const FlowShape &f, int set, bo
     return hipGetLastError();
 }
 
-hipError_t launch_flow_totals(const RecParams &p, int node_count, const FlowShape &f, int set, bool has_mid,
-                              bool safe_curves, bool kept, int max_term, double *scratch, double *totals, hipStream_t s)
+hipError_t launch_flow_totals(const RecParams &p, int node_count, const FlowShape &f, int set, bool has_mid, bool kept,
+                              int max_term, double *scratch, double *totals, hipStream_t s)
 {
     const FlowStore none{nullptr, 0, 0, 0, 0, p.n_tiles};
     const size_t rows_d = (size_t)f.nodes * f.R * f.row_len;
@@ -437,10 +427,8 @@ hipError_t launch_flow_totals(const RecParams &p, int node_count, const FlowShap
         }
         const dim3 g((p.scen_count + 63) / 64, nodes);
         const size_t lds = (size_t)f.row_len * sizeof(double) * (has_mid ? 2 : 1);
-        if (safe_curves)
-            hipLaunchKernelGGL(k_flow_totals<16>, g, dim3(64 * 16), lds, s, p, src, src_mid, n_sums, f.row_len, max_term, nb, totals);
-        else
-            hipLaunchKernelGGL(k_flow_totals<1>, g, dim3(64), lds, s, p, src, src_mid, n_sums, f.row_len, max_term, nb, totals);
+        hipLaunchKernelGGL(k_flow_totals, g, dim3(64 * FLOW_TOTALS_CHUNKS), lds, s, p, src, src_mid, n_sums, f.row_len, max_term,
+                           nb, totals);
     }
     return hipGetLastError();
 }

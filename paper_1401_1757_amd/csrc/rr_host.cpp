@@ -508,7 +508,9 @@ extern "C" int rr_get_option(rr_ctx *c, int32_t option, int64_t *value)
 // survival probabilities in FP64.
 constexpr double kSafeLogSpan = 600.0;
 
-static bool safe_products(const rr_ctx *c) { return c->curve_log_span <= kSafeLogSpan; }   // (NaN: no)
+// No product of up to n discount factors of a scenario leaves the range (NaN: it may).
+static bool safe_product(const rr_ctx *c, int n) { return n * c->curve_log_step <= kSafeLogSpan; }
+static bool safe_products(const rr_ctx *c) { return safe_product(c, c->n_steps); }
 
 static int stage_tables(rr_ctx *c)
 {
@@ -573,16 +575,16 @@ static int vasicek_params(rr_ctx *c, const rr_vasicek *vs, int n_nodes, int n_sc
     return RR_OK;
 }
 
-// Bound on |sum of log v| over the steps of any generated scenario: the normals
-// of 53-bit uniforms are at most sqrt(-2 log 2^-54) = 8.66 in size, which bounds
-// the short rate's distance from b and with it every step's integral.
-static double vasicek_log_span(const VasParams &P, const std::vector<double> &r0)
+// Bound on |log v| of any step of any generated scenario: the normals of 53-bit
+// uniforms are at most sqrt(-2 log 2^-54) = 8.66 in size, which bounds the short
+// rate's distance from b and with it every step's integral.
+static double vasicek_log_step(const VasParams &P, const std::vector<double> &r0)
 {
     const double z = 8.66;
     double dist = 0.0;
     for (double x : r0) dist = std::max(dist, std::fabs(x - P.b));
     dist += P.e < 1.0 ? z * P.sd_r * std::min(1.0 / (1.0 - P.e), (double)P.n_steps) : z * P.sd_r * P.n_steps;
-    return P.n_steps * (std::fabs(P.b) * P.dt + dist * P.om + z * (std::fabs(P.rho_sd_y) + P.sd_y_perp));
+    return std::fabs(P.b) * P.dt + dist * P.om + z * (std::fabs(P.rho_sd_y) + P.sd_y_perp);
 }
 
 // Enqueue a generation: start rates to the device (waiting for the stream
@@ -637,9 +639,9 @@ static int install_basis(rr_ctx *c, const rr_basis *b, std::vector<double> &q,
     bool keep_pf = c->has_pf;
     if (v) {
         const auto mm = std::minmax_element(v->begin(), v->end());
-        c->curve_log_span = b->n_steps * std::max(std::fabs(std::log(*mm.first)), std::fabs(std::log(*mm.second)));
+        c->curve_log_step = std::max(std::fabs(std::log(*mm.first)), std::fabs(std::log(*mm.second)));
     } else {
-        c->curve_log_span = vasicek_log_span(*gen, *gen_r0);
+        c->curve_log_step = vasicek_log_step(*gen, *gen_r0);
     }
     if (keep_pf) {
         for (int i = 0; i < c->n_user && keep_pf; ++i) {
@@ -760,9 +762,7 @@ extern "C" int rr_curves_generate_vasicek(rr_ctx *c, const rr_vasicek *vs)
     int rc;
     if ((rc = vasicek_params(c, vs, c->n_nodes, c->n_scen, c->n_steps, c->scen_pad, &P, &r0))) return rc;
     ++c->curve_gen;   // cached per-scenario decisions (the surrogate's range flags) are stale
-    const bool safe = safe_products(c);
-    c->curve_log_span = vasicek_log_span(P, r0);
-    if (safe != safe_products(c)) drop_graphs(c);   // other kernels
+    c->curve_log_step = vasicek_log_step(P, r0);
     double *D = discount_room(c);
     if ((rc = enqueue_vasicek(c, P, r0, c->v.p, 1, nullptr, D))) return rc;
     c->has_disc = D && safe_products(c);
@@ -1616,12 +1616,17 @@ static int enqueue_run(rr_ctx *c, const rr_run *run, const rr_outputs *out, Plan
 // large book on one scenario has the same number of policy-months either way
 // and pays for the rows (100,000 x 1: 0.054 / 0.073 ms), so one scenario of more
 // than 512 tiles keeps the chains.  A pinned launch shape or queue mode asks
-// for the recurrence kernel itself.
+// for the recurrence kernel itself, and so do curves on which the product of a
+// time chunk of k_flow_totals could leave the FP64 range (factors of e^16 and
+// more a month at 600 months; one chain over all months instead, which such
+// curves once took here, was up to 2.5 times slower than the policies' own:
+// 30,000 x 1 0.129 against 0.052 ms).
 static bool flow_totals_run(rr_ctx *c, const rr_run *run)
 {
     if (run->out_mask & (RR_OUT_R0 | RR_OUT_PATH)) return false;
     if (!(run->out_mask & (RR_OUT_TOTALS | RR_OUT_STATS)) || c->n_user == 0) return false;
     if (run->scen_count == 1 && (long long)c->n_tiles * run->node_count > 512) return false;
+    if (!safe_product(c, (c->max_term + FLOW_TOTALS_CHUNKS - 1) / FLOW_TOTALS_CHUNKS)) return false;
     return unpinned(c) && flow_ok(c, run);
 }
 
@@ -1704,8 +1709,8 @@ static int enqueue_flow_run(rr_ctx *c, const rr_run *run, const rr_outputs *out,
             HIPCHK(c, hipStreamWaitEvent(c->cap_side, c->cap_fork, 0));
             q = c->cap_side;
         }
-        HIPCHK(c, launch_flow_totals(P, run->node_count, f, c->flow_set, c->has_frac, safe_products(c),
-                                     have_rows, c->max_term, work, totals, q));
+        HIPCHK(c, launch_flow_totals(P, run->node_count, f, c->flow_set, c->has_frac, have_rows,
+                                     c->max_term, work, totals, q));
         return branch ? enqueue_stats(c, run, out, totals, q) : RR_OK;
     };
     Plan pl;   // no work lists

@@ -185,12 +185,13 @@ FlowShape flow_shape(int node_count, int n_tiles, int max_term, bool has_mid, si
 // set: the kinds of tiles the portfolio has (0 level ones only, 1 payment
 // patterns too, 2 others).  Whether the kernels' LDS suffices.
 bool flow_fits(const FlowShape &f, const RecParams &p, int set, bool has_mid, size_t lds_per_block);
-// totals[node][scen] of the run in p (its node_begin, scen_begin, scen_count);
-// safe_curves: no product of a run's discount factors leaves the FP64 range.
+// Time chunks of k_flow_totals.  It forms the product of a chunk's discount
+// factors, which the caller has to know to stay within the FP64 range.
+constexpr int FLOW_TOTALS_CHUNKS = 16;
+// totals[node][scen] of the run in p (its node_begin, scen_begin, scen_count).
 // kept: the rows are there already (launch_flow_store with the same scratch).
-hipError_t launch_flow_totals(const RecParams &p, int node_count, const FlowShape &f, int set, bool has_mid,
-                              bool safe_curves, bool kept, int max_term, double *scratch, double *totals,
-                              hipStream_t s);
+hipError_t launch_flow_totals(const RecParams &p, int node_count, const FlowShape &f, int set, bool has_mid, bool kept,
+                              int max_term, double *scratch, double *totals, hipStream_t s);
 // Kept cash flows of tiles [tile_begin, tile_end) at some nodes: 64 doubles a
 // month, node k's from month k * node_months, a tile's from tile_base[tile] -
 // month_begin; flows within the month `mid` doubles further on.  Lane l of the

@@ -1,6 +1,7 @@
 """Runs by cash flows (test_gpu_flows.py) in the situations that need a size, a
-graph or a change of curves of their own: graphs that the caller captured, and
-the library's own graphs with a second branch."""
+graph or a change of curves of their own: graphs that the caller captured,
+the library's own graphs with a second branch, curves whose products leave the
+FP64 range."""
 import sys
 
 import numpy as np
@@ -122,4 +123,34 @@ def test_two_branch_graphs_over_many_output_sets(rr):
                 assert all(torch.equal(o[k], ref[k]) for k in ref)
     finally:
         torch.cuda.synchronize()
+        ctx.close()
+
+
+@pytest.mark.parametrize("log10,flows", [(4.0, True), (25.0, True), (27.0, False)])
+def test_totals_on_both_sides_of_the_chunk_range(rr, log10, flows):
+    """Factors 10^x and 10^-x by turns, then 10^-x: products over all months leave
+    the FP64 range; those of a time chunk (ten of 160 months) stay within e^600
+    up to x = 26."""
+    rng = np.random.default_rng(62)
+    w = synth.random_small(rng, n=300, n_steps=160, n_scen=66, n_nodes=1, products=(0, 1, 2, 3, 4, 5))
+    big = 10.0 ** log10
+    v = w.basis.v
+    v[:, :, :60] = np.where(np.arange(60) % 2 == 0, big, 1.0 / big)
+    v[:, :, 60:] = 1.0 / big
+    chunk = -(-int(w.portfolio.term_m.max()) // 16)
+    assert (chunk * log10 * np.log(10.0) <= 600.0) == flows
+    ctx = rr.Context(0)
+    try:
+        ctx.basis_upload(w.basis.q, v)
+        ctx.portfolio_upload(w.portfolio)
+        ref = oracle.reserves(w.basis, w.portfolio, 0, 1, 0, 66)
+        for call in (ctx.reserve_recurrence, ctx.reserve_recurrence_noalloc):
+            _say(f"totals, factors 1e{log10:g}, {call.__name__}")
+            out = ctx.alloc_outputs(1, 66, r0=False, stats=True)
+            call(0, 1, 0, 66, 12, out)
+            torch.cuda.synchronize()
+            assert (ctx.get_option(rr.OPT_LAST_K) == 0) == flows
+            err = np.abs(to_np(out["totals"]) - ref["totals"])
+            assert np.all(err <= RTOL * ref["gross_totals"]), err.max()
+    finally:
         ctx.close()

@@ -166,3 +166,21 @@ def test_dropping_graphs_does_not_wait(double):
     c.ok(lib.rr_set_stream(c.h, STREAM + 0x100))
     assert hd.hd_waits() == waits and hd.hd_last_error() == 0
     """)
+
+
+@pytest.mark.parametrize("sigma,steps,flows", [(0.01, 600, True), (0.3, 600, True), (8.0, 600, False), (8.0, 16, True)])
+def test_totals_route_by_the_range_of_a_time_chunk(double, sigma, steps, flows):
+    """Totals by summed flows need the products of a sixteenth of the months
+    only; where those too could leave the range, the policies' own chains."""
+    run(double, f"""
+    q, pf = book(300, {min(steps, 120)})
+    c = Ctx()
+    c.generate(q, 70, {steps}, a=0.02, b=0.03, sigma={sigma})
+    c.portfolio(pf)
+    log()
+    for noalloc in (False, True):
+        c.ok(c.run(1, 70, rr.OUT_TOTALS | rr.OUT_STATS, noalloc=noalloc))
+        names = log()
+        assert ("k_flow_totals" in names) == {flows} and ("k_recurrence" in names) != {flows}, names
+        assert "k_flow_totalsILi" not in names   # one form of the kernel
+    """)
