@@ -147,3 +147,34 @@ def test_invalid_generator_calls(ctx, rr):
     ctx.basis_generate_vasicek(q, 10, 50, [0.03], A, B, SIG, DT, (1, 2))
     with pytest.raises(rr.RRError, match="r0"):
         ctx.curves_generate_vasicek([float("nan")], A, B, SIG, DT, (1, 2))
+
+
+@pytest.mark.parametrize("n_steps,few,many", [(1, 16300, 16400), (63, 16300, 16400), (64, 16300, 16400),
+                                              (65, 28050, 28200), (130, 28050, 28200), (1030, 28050, 28200)])
+def test_a_scenario_does_not_depend_on_how_many_are_drawn(ctx, n_steps, few, many):
+    """Generations on both sides of the rule between the two kernels (256
+    wavefronts of 64 scenarios up to 64 months, 440 above): the scenarios that
+    both have are the same, bit for bit, into the caller's arrays and as the
+    basis's own curves and discount products."""
+    key = (19, n_steps)
+    _say(f"{few} and {many} scenarios x {n_steps}")
+    v0, r0 = ctx.vasicek_curves(few, n_steps, [0.04], A, B, SIG, DT, key)
+    v1, r1 = ctx.vasicek_curves(many, n_steps, [0.04], A, B, SIG, DT, key)
+    torch.cuda.synchronize()
+    assert torch.equal(v0, v1[:, :few]) and torch.equal(r0, r1[:, :few])
+    assert bool(torch.isfinite(v1).all()) and bool(torch.isfinite(r1).all())
+    del v0, v1, r0, r1
+    rng = np.random.default_rng(n_steps)
+    w = synth.random_small(rng, n=9, n_steps=n_steps, n_scen=1, products=(0, 1, 4, 5))
+    kept = []
+    for n_scen in (few, many):
+        ctx.basis_generate_vasicek(w.basis.q, n_scen, n_steps, [0.04], A, B, SIG, DT, (1, 1))
+        ctx.portfolio_upload(w.portfolio)
+        ctx.curves_generate_vasicek([0.04], A, B, SIG, DT, key)
+        out = ctx.reserve_recurrence(0, 1, few - 700, 700, 12, all_states=False)
+        every = ctx.reserve_recurrence(0, 1, few - 700, 700, 12, all_states=True)
+        torch.cuda.synchronize()
+        kept.append((out["r0"].clone(), every["r0"].clone()))
+    assert torch.equal(kept[0][0], kept[1][0]) and torch.equal(kept[0][1], kept[1][1])
+    gross = kept[0][1][..., 0].abs().amax()
+    assert float((kept[0][0] - kept[0][1][..., 0]).abs().amax()) <= 1e-10 * float(gross)
