@@ -160,7 +160,9 @@ struct rr_ctx {
     std::vector<int32_t> h_patterned;     // 1: escalating or annual annuity
     std::vector<Tile> tiles_host;
     std::vector<int> slot_of_user;       // user index -> sorted slot
-    DevBuf<int> age1, age2, term, qoff1, qoff2, uidx;
+    DevBuf<int> age1, age2, term, qoff1, qoff2;
+    DevBuf<int> lists;                    // upload index [n_pad]; tiles, longest remaining term first [n_tiles];
+                                          // first month of each tile's kept flows [n_tiles + 1]
     DevBuf<int> age3, qoff3;              // life 3 of three-life tiles (0 elsewhere)
     DevBuf<double> coef;
     DevBuf<double> pat_g;                 // [n_pad] (with pattern or table tiles)
@@ -176,13 +178,11 @@ struct rr_ctx {
     bool has_markov = false;
     int mk_models = 0, mk_states = 0, mk_ages = 0;
     std::vector<double> mk_c_host;        // [model][mk_states] benefits
-    DevBuf<double> mk_w;                  // [model][mk_ages][4][4] ([9][9] above 4 states)
-    DevBuf<double> mk_wt;                 // [model][mk_ages][column][row] (up to 4 states)
+    DevBuf<double> mk_w;                  // [model][mk_ages][4][4], then the same transposed
+                                          // ([9][9] above 4 states, no second part)
     DevBuf<double> mk_c;                  // [model][9] benefits per unit amount
     DevBuf<Tile> tiles;
-    DevBuf<int> tile_order;               // tiles, longest remaining term first
-    DevBuf<int> tile_base;                // [n_tiles + 1] first month of each tile's kept flows
-    std::vector<int> tile_base_host;
+    std::vector<int> tile_base_host;      // first month of each tile's kept flows
     int gen = 0;                          // bumps on every upload
     long long curve_gen = 0;              // bumps whenever the curve values change (uploads
                                           // and in-place regeneration)

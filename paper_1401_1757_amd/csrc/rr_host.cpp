@@ -101,10 +101,39 @@ static int fetch(rr_ctx *c, const T *src, size_t n, int mem_kind, std::vector<T>
 // ---------------------------------------------------------------------------
 // Validation (host only)
 // ---------------------------------------------------------------------------
-// v == nullptr with generated = true: the curves come from a generator.
+// Smallest and largest of n values; false if one is not a number.  One pass, eight
+// at a time.
+static bool value_range(const double *x, long long n, double range[2])
+{
+    constexpr int B = 8;
+    double lo[B], hi[B], odd[B];
+    for (int j = 0; j < B; ++j) {
+        lo[j] = hi[j] = x[0];
+        odd[j] = 0.0;
+    }
+    long long i = 0;
+    for (; i + B <= n; i += B)
+        for (int j = 0; j < B; ++j) {
+            const double y = x[i + j];
+            lo[j] = y < lo[j] ? y : lo[j];
+            hi[j] = y > hi[j] ? y : hi[j];
+            odd[j] = y == y ? odd[j] : 1.0;
+        }
+    for (; i < n; ++i) {
+        lo[0] = std::min(lo[0], x[i]);
+        hi[0] = std::max(hi[0], x[i]);
+        if (x[i] != x[i]) odd[0] = 1.0;
+    }
+    range[0] = *std::min_element(lo, lo + B);
+    range[1] = *std::max_element(hi, hi + B);
+    return *std::max_element(odd, odd + B) == 0.0;
+}
+
+// v == nullptr with generated = true: the curves come from a generator.  v_range:
+// smallest and largest discount factor of curves that pass.
 static std::string check_basis_arrays(int n_tables, int n_ages, const double *q, int n_nodes,
-                                      int n_scen, int n_steps, const double *v,
-                                      const double *shock, bool generated = false)
+                                      int n_scen, int n_steps, const double *v, const double *shock,
+                                      bool generated = false, double *v_range = nullptr)
 {
     char b[256];
     if (n_tables < 1 || n_ages < 2) return "basis: need n_tables >= 1 and n_ages >= 2";
@@ -120,13 +149,18 @@ static std::string check_basis_arrays(int n_tables, int n_ages, const double *q,
             return b;
         }
     }
-    for (long long i = 0; v && i < (long long)n_nodes * n_scen * n_steps; ++i) {
-        double x = v[i];
-        if (!(x > 0.0) || !std::isfinite(x)) {
-            snprintf(b, sizeof b, "basis: v[%lld] = %g is not a positive finite discount factor", i, x);
-            return b;
+    const long long nv = v ? (long long)n_nodes * n_scen * n_steps : 0;
+    double range[2] = {1.0, 1.0};
+    if (nv && !(value_range(v, nv, range) && range[0] > 0.0 && std::isfinite(range[1]))) {
+        for (long long i = 0; i < nv; ++i) {
+            double x = v[i];
+            if (!(x > 0.0) || !std::isfinite(x)) {
+                snprintf(b, sizeof b, "basis: v[%lld] = %g is not a positive finite discount factor", i, x);
+                return b;
+            }
         }
     }
+    if (v_range) std::copy(range, range + 2, v_range);
     if (shock)
         for (int i = 0; i < n_nodes; ++i)
             if (!(shock[i] >= 0.0) || !std::isfinite(shock[i])) {
@@ -630,19 +664,16 @@ static double *discount_room(rr_ctx *c)
 
 // Shared tail of rr_basis_upload and rr_basis_generate_vasicek: install the
 // checked mortality part and the sizes, then the curves from the host copy
-// `v` (scenario-major) or from the generator.
+// `v` (scenario-major; v_range: its smallest and largest value) or from the
+// generator.
 static int install_basis(rr_ctx *c, const rr_basis *b, std::vector<double> &q,
-                         const std::vector<double> &sh, const std::vector<double> *v,
+                         const std::vector<double> &sh, const std::vector<double> *v, const double *v_range,
                          const VasParams *gen, const std::vector<double> *gen_r0)
 {
     // A loaded portfolio that the new basis does not cover is dropped.
     bool keep_pf = c->has_pf;
-    if (v) {
-        const auto mm = std::minmax_element(v->begin(), v->end());
-        c->curve_log_step = std::max(std::fabs(std::log(*mm.first)), std::fabs(std::log(*mm.second)));
-    } else {
-        c->curve_log_step = vasicek_log_step(*gen, *gen_r0);
-    }
+    c->curve_log_step = v ? std::max(std::fabs(std::log(v_range[0])), std::fabs(std::log(v_range[1])))
+                          : vasicek_log_step(*gen, *gen_r0);
     if (keep_pf) {
         for (int i = 0; i < c->n_user && keep_pf; ++i) {
             if (c->h_product[i] == RR_MARKOV) {   // uploaded model: only the term matters here
@@ -722,10 +753,11 @@ extern "C" int rr_basis_upload(rr_ctx *c, const rr_basis *b)
     if ((rc = fetch(c, b->q, (size_t)b->n_tables * b->n_ages, b->mem_kind, q))) return rc;
     if ((rc = fetch(c, b->v, nv, b->mem_kind, v))) return rc;
     if (b->shock && (rc = fetch(c, b->shock, (size_t)b->n_nodes, b->mem_kind, sh))) return rc;
+    double v_range[2];
     std::string s = check_basis_arrays(b->n_tables, b->n_ages, q.data(), b->n_nodes, b->n_scen,
-                                       b->n_steps, v.data(), b->shock ? sh.data() : nullptr);
+                                       b->n_steps, v.data(), b->shock ? sh.data() : nullptr, false, v_range);
     if (!s.empty()) return fail(c, RR_EINVAL, "%s", s.c_str());
-    return install_basis(c, b, q, sh, &v, nullptr, nullptr);
+    return install_basis(c, b, q, sh, &v, v_range, nullptr, nullptr);
 }
 
 extern "C" int rr_basis_generate_vasicek(rr_ctx *c, const rr_basis *b, const rr_vasicek *vs)
@@ -749,7 +781,7 @@ extern "C" int rr_basis_generate_vasicek(rr_ctx *c, const rr_basis *b, const rr_
     VasParams P;
     const int scen_pad = (b->n_scen + 31) / 32 * 32 + 32;
     if ((rc = vasicek_params(c, vs, b->n_nodes, b->n_scen, b->n_steps, scen_pad, &P, &r0))) return rc;
-    return install_basis(c, b, q, sh, nullptr, &P, &r0);
+    return install_basis(c, b, q, sh, nullptr, nullptr, &P, &r0);
 }
 
 extern "C" int rr_curves_generate_vasicek(rr_ctx *c, const rr_vasicek *vs)
@@ -1092,20 +1124,22 @@ extern "C" int rr_portfolio_upload(rr_ctx *c, const rr_portfolio *p)
     if ((rc = upload_vec(c, c->qoff2, s_qoff2))) return rc;
     if ((rc = upload_vec(c, c->age3, s_age3))) return rc;
     if ((rc = upload_vec(c, c->qoff3, s_qoff3))) return rc;
-    if ((rc = upload_vec(c, c->uidx, s_uidx))) return rc;
     if ((rc = upload_vec(c, c->coef, coef))) return rc;
     if ((rc = upload_vec(c, c->tiles, tiles))) return rc;
     std::vector<int> by_term(tiles.size());
     std::iota(by_term.begin(), by_term.end(), 0);
     std::stable_sort(by_term.begin(), by_term.end(), [&](int a, int b) { return tiles[a].smax > tiles[b].smax; });
-    if ((rc = upload_vec(c, c->tile_order, by_term))) return rc;
     c->tile_base_host.assign(1, 0);
     long long months = 0;
     for (const Tile &T : tiles) {
         months += (T.smax / DISC_BLOCK + 1) * DISC_BLOCK;
         c->tile_base_host.push_back((int)std::min<long long>(months, 1 << 30));   // (then no flows are kept)
     }
-    if ((rc = upload_vec(c, c->tile_base, c->tile_base_host))) return rc;
+    // (one copy: a copy costs as much as ten thousand tiles' lists)
+    std::vector<int> lists = s_uidx;
+    lists.insert(lists.end(), by_term.begin(), by_term.end());
+    lists.insert(lists.end(), c->tile_base_host.begin(), c->tile_base_host.end());
+    if ((rc = upload_vec(c, c->lists, lists))) return rc;
     // Payment patterns of the slots (level slots: g = 1, anniversary 12) and
     // the cash flows of table slots, amount x table value, month-major over
     // the table tiles' slots (padding slots: 0).
@@ -1263,15 +1297,14 @@ extern "C" int rr_markov_upload(rr_ctx *c, const rr_markov *m)
                 if (std::fabs(sum - 1.0) > 1e-12)
                     return fail(c, RR_EINVAL, "markov: model %d age %d row %d sums to %.17g", md, a, i, sum);
             }
-    HIPCHK(c, c->mk_w.alloc(wp.size()));
-    HIPCHK(c, hipMemcpy(c->mk_w.p, wp.data(), wp.size() * sizeof(double), hipMemcpyHostToDevice));
-    if (MP == 4) {
-        std::vector<double> wt(wp.size());
-        for (size_t k = 0; k < wp.size(); k += 16)
+    if (MP == 4) {   // the transposed copy behind the matrices
+        const size_t n = wp.size();
+        wp.resize(2 * n);
+        for (size_t k = 0; k < n; k += 16)
             for (int i = 0; i < 4; ++i)
-                for (int j = 0; j < 4; ++j) wt[k + 4 * j + i] = wp[k + 4 * i + j];
-        if ((rc = upload_vec(c, c->mk_wt, wt))) return rc;
+                for (int j = 0; j < 4; ++j) wp[n + k + 4 * j + i] = wp[k + 4 * i + j];
     }
+    if ((rc = upload_vec(c, c->mk_w, wp))) return rc;
     std::vector<double> cpad((size_t)m->n_models * MAX_MK_STATES, 0.0);
     for (int md = 0; md < m->n_models; ++md)
         for (int j = 0; j < M; ++j) cpad[(size_t)md * MAX_MK_STATES + j] = ben[(size_t)md * M + j];
@@ -1460,14 +1493,14 @@ static RecParams make_params(rr_ctx *c, const rr_run *run, const rr_outputs *out
     P.term = c->term.p;
     P.qoff1 = c->qoff1.p;
     P.qoff2 = c->qoff2.p;
-    P.uidx = c->uidx.p;
+    P.uidx = c->lists.p;
     P.coef = c->coef.p;
     P.pat_g = c->has_flow ? c->pat_g.p : nullptr;
     P.pat_code = c->has_flow ? c->pat_code.p : nullptr;
     P.cf_t = (c->has_flow && c->cf_cols > 0) ? c->cf_t.p : nullptr;
     P.cf_cols = c->cf_cols;
     P.mk_w = c->has_markov ? c->mk_w.p : nullptr;
-    P.mk_wt = c->has_markov ? c->mk_wt.p : nullptr;
+    P.mk_wt = c->has_markov ? c->mk_w.p + (size_t)c->mk_models * c->mk_ages * 16 : nullptr;   // (up to 4 states)
     P.mk_ages = c->mk_ages;
     P.mk_states = c->mk_states;
     P.mk_c = c->has_markov ? c->mk_c.p : nullptr;
@@ -1478,8 +1511,8 @@ static RecParams make_params(rr_ctx *c, const rr_run *run, const rr_outputs *out
     P.n_pad = c->n_pad;
     P.n_user = c->n_user;
     P.tiles = c->tiles.p;
-    P.tile_order = c->tile_order.p;
-    P.tile_base = c->tile_base.p;
+    P.tile_order = c->lists.p + c->n_pad;
+    P.tile_base = P.tile_order + c->n_tiles;
     P.disc = !c->v_override && c->has_disc ? c->disc.p : nullptr;
     P.n_tiles = c->n_tiles;
     P.has_vector = 0;
