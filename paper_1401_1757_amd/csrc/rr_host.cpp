@@ -1235,7 +1235,7 @@ extern "C" int rr_node_expected_reserves(rr_ctx *c, const rr_run *run, double *n
     if (run->node_count == 0 || (!node_r0 && !node_totals)) return RR_OK;
     HIPCHK(c, hipSetDevice(c->device));
     if (!c->has_disc) HIPCHK(c, c->mean_D.alloc((size_t)run->node_count * c->n_steps * run->scen_count));
-    HIPCHK(c, c->mean_v.alloc((size_t)c->n_nodes * c->n_steps * 64));
+    HIPCHK(c, c->mean_v.alloc((size_t)c->n_nodes * c->n_steps));
     HIPCHK(c, launch_mean_curve(c->v.p, c->n_steps, c->scen_pad, run->node_begin, run->node_count,
                                 run->scen_begin, run->scen_count, c->has_disc ? c->disc.p : nullptr,
                                 c->mean_D.p, c->mean_v.p, c->stream));
@@ -1252,7 +1252,7 @@ extern "C" int rr_node_expected_reserves(rr_ctx *c, const rr_run *run, double *n
     const int graph = c->opt_graph;
     c->opt_graph = 0;
     c->v_override = c->mean_v.p;
-    c->pad_override = 64;
+    c->pad_override = 1;   // a curve's months side by side
     const int rc = rr_reserve_recurrence(c, &r, &o);
     c->v_override = nullptr;
     c->pad_override = 0;

@@ -238,7 +238,7 @@ size_t vasicek_work_doubles(int n_nodes, int n_scen, int n_steps, int scen_pad);
 // Mean discount curve of the run's scenarios per node (rr_kernels.hip) from the
 // kept discount products `disc` or, where there are none (null), from v by way
 // of D, which holds node_count * n_steps * scen_count doubles; vbar is
-// [n_nodes][n_steps][64] with the curve at lane 0 of the run's nodes.
+// [n_nodes][n_steps], filled at the run's nodes.
 hipError_t launch_mean_curve(const double *v, int n_steps, int scen_pad, int node_begin,
                              int node_count, int scen_begin, int scen_count, const double *disc, double *D,
                              double *vbar, hipStream_t stream);

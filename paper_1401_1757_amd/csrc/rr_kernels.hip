@@ -436,9 +436,11 @@ __global__ void __launch_bounds__(64) k_disc_products(const double *__restrict__
 
 // Means over the scenarios of the discount products (row t - 1 of a node: D_t
 // of every scenario, t = 1 .. n_steps), then the one-step factors of the mean
-// curve, written at scenario 0 of vbar[node][t][64] (other lanes 1).  A
-// workgroup takes sixteen months of a node (and the mean before them), a
-// wavefront a row at a time with its loads coalesced; sums in a fixed order.
+// curve vbar[node][t].  A workgroup takes sixteen months of a node (and the mean
+// before them), a wavefront a row at a time with its loads coalesced; sums in a
+// fixed order.  The curve's months lie side by side: a cache line a month, as in
+// the scenarios' layout, made the recurrence behind it wait for lines that other
+// XCDs had written (100 policies, one scenario: 30 us, side by side 17).
 // Bound by the one read of the products.  Read a row a thread after a chain per
 // scenario had written them, 10,000 policies' node means at 60 nodes x 500
 // scenarios took 0.372 ms, now 0.113.
@@ -466,9 +468,9 @@ k_mean_curve(const double *__restrict__ D, size_t node_stride, size_t row, int n
         if (lane == 0) s_mean[j] = m;
     }
     __syncthreads();
-    double *o = vbar + ((size_t)(node_begin + kr) * n_steps + t0) * 64;
-    for (int j = wave; j < MEAN_MONTHS && t0 + j < n_steps; j += MEAN_WAVES)
-        o[j * 64 + lane] = lane > 0 ? 1.0 : (s_mean[j] != 0.0 ? s_mean[j + 1] / s_mean[j] : 0.0);   // (0: underflowed)
+    const int j = threadIdx.x;
+    if (j < MEAN_MONTHS && t0 + j < n_steps)
+        vbar[(size_t)(node_begin + kr) * n_steps + t0 + j] = s_mean[j] != 0.0 ? s_mean[j + 1] / s_mean[j] : 0.0;   // (0: underflowed)
 }
 
 hipError_t launch_mean_curve(const double *v, int n_steps, int scen_pad, int node_begin,
