@@ -216,6 +216,7 @@ struct rr_ctx {
     // graphs
     std::vector<GraphEntry> graphs;
     std::vector<rr::host::RetiredGraphs> retired;   // oldest first
+    std::vector<std::vector<uint64_t>> recent;      // keys of runs launched once, oldest first
 
     // work lists of the surrogate's exact fallback
     Plan item_plan[2];

@@ -2043,8 +2043,15 @@ static std::vector<uint64_t> run_key(rr_ctx *c, const rr_run *run, const rr_outp
     return key;
 }
 
+// Captured runs kept, and runs remembered for their second call.
+constexpr size_t kGraphs = 8;
+
 // Launch the work of `enqueue(stream, timed)`: replayed from a captured graph,
-// or directly (no graphs, or kernels are timed).
+// or directly (no graphs, kernels are timed, or the run is none of the last
+// eight: capturing pays from the second call on, and a program that takes new
+// outputs on each call, or more sets in turn than are kept, would pay for it
+// every time: 64 policies x 2 scenarios on twelve sets in turn 41 us by
+// captures, 20 directly).
 template <class F>
 static int launch_graphed(rr_ctx *c, const std::vector<uint64_t> &key, F enqueue)
 {
@@ -2053,7 +2060,14 @@ static int launch_graphed(rr_ctx *c, const std::vector<uint64_t> &key, F enqueue
     for (auto &g : c->graphs)
         if (g.key == key) { ge = &g; break; }
     if (!ge) {
-        if (c->graphs.size() >= 8) drop_graphs(c);
+        const auto seen = std::find(c->recent.begin(), c->recent.end(), key);
+        if (seen == c->recent.end()) {
+            if (c->recent.size() >= kGraphs) c->recent.erase(c->recent.begin());
+            c->recent.push_back(key);
+            return enqueue(c->stream, false);
+        }
+        c->recent.erase(seen);
+        if (c->graphs.size() >= kGraphs) drop_graphs(c);
         GraphEntry g;
         g.key = key;
         HIPCHK(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));

@@ -114,8 +114,11 @@ def test_two_branch_graphs_over_many_output_sets(rr):
                     x.fill_(float("nan"))
             kept = []
             for i, o in enumerate(outs):
-                ctx.reserve_recurrence(0, 1, 0, scen, 12, o)
+                for _ in range(2):   # launched directly, then captured
+                    ctx.reserve_recurrence(0, 1, 0, scen, 12, o)
                 if i % 3 == 0:   # a replay of the graph just made, and a read behind it
+                    for x in o.values():
+                        x.fill_(float("nan"))
                     ctx.reserve_recurrence(0, 1, 0, scen, 12, o)
                     kept.append({k: x.clone() for k, x in o.items()})
             torch.cuda.synchronize()

@@ -130,23 +130,26 @@ def test_graphs_are_destroyed_after_their_launches(double):
     mask = rr.OUT_R0 | rr.OUT_TOTALS | rr.OUT_STATS
     for at in range(1, 40):
         c.ok(c.run(1, 1000, mask, at=at))
+        c.ok(c.run(1, 1000, mask, at=at))
         assert hd.hd_live_execs() <= 8 * 6, hd.hd_live_execs()
     assert "graph: " in log()
     c.ok(lib.rr_set_option(c.h, rr.OPT_BLOCK_K, 8))
     c.ok(lib.rr_set_option(c.h, rr.OPT_BLOCK_J, 1))
     c.ok(lib.rr_set_option(c.h, rr.OPT_WG_PER_CU, 1))
     for at in range(1, 12):
-        c.ok(c.run(1, 1000, mask, at=at))
+        for rep in range(2):
+            c.ok(c.run(1, 1000, mask, at=at))
+    runs = lambda scen: [c.ok(c.run(1, scen, mask)) for rep in range(3)]
     c.ok(lib.rr_set_option(c.h, rr.OPT_CURVE_SHARE, 0))
-    c.ok(c.run(1, 1000, mask))
+    runs(1000)
     c.ok(lib.rr_set_stream(c.h, STREAM + 0x100))
-    c.ok(c.run(1, 1000, mask))
+    runs(1000)
     c.regenerate(**WIDE)
-    c.ok(c.run(1, 1000, mask))
+    runs(1000)
     c.portfolio(book(5000, 60, seed=2)[1])
-    c.ok(c.run(1, 1000, mask))
+    runs(1000)
     c.generate(q, 2000, 60, **SAFE)
-    c.ok(c.run(1, 2000, mask))
+    runs(2000)
     assert not hd.hd_faults(), hd.hd_faults()
     lib.rr_destroy(c.h)
     assert not hd.hd_faults() and hd.hd_live_execs() == 0, hd.hd_faults()
@@ -162,7 +165,8 @@ def test_dropping_graphs_does_not_wait(double):
     c.ok(c.run(1, 70, rr.OUT_R0 | rr.OUT_TOTALS))
     waits = hd.hd_waits()
     for at in range(1, 20):
-        c.ok(c.run(1, 70, rr.OUT_R0 | rr.OUT_TOTALS, at=at))
+        for rep in range(2):
+            c.ok(c.run(1, 70, rr.OUT_R0 | rr.OUT_TOTALS, at=at))
     c.ok(lib.rr_set_stream(c.h, STREAM + 0x100))
     assert hd.hd_waits() == waits and hd.hd_last_error() == 0
     """)
@@ -183,4 +187,31 @@ def test_totals_route_by_the_range_of_a_time_chunk(double, sigma, steps, flows):
         names = log()
         assert ("k_flow_totals" in names) == {flows} and ("k_recurrence" in names) != {flows}, names
         assert "k_flow_totalsILi" not in names   # one form of the kernel
+    """)
+
+
+def test_a_run_is_captured_on_its_second_call(double):
+    """The first call of a run launches directly, the second captures, later ones
+    replay; more output sets in turn than are kept are always launched directly."""
+    run(double, """
+    q, pf = book(300, 60)
+    c = Ctx()
+    c.generate(q, 70, 60, **SAFE)
+    c.portfolio(pf)
+    mask = rr.OUT_R0 | rr.OUT_TOTALS
+    log()
+    kinds = []
+    for rep in range(3):
+        c.ok(c.run(1, 70, mask))
+        lines = log().splitlines()
+        kinds.append((all(l.startswith("graph: ") for l in lines), hd.hd_live_execs()))
+    assert kinds == [(False, 0), (True, 1), (True, 1)], kinds
+    for rep in range(3):
+        for at in range(2, 11):
+            c.ok(c.run(1, 70, mask, at=at))
+    assert hd.hd_live_execs() == 1 and "graph: " not in log()
+    for rep in range(3):
+        for at in range(2, 10):
+            c.ok(c.run(1, 70, mask, at=at))
+    assert "graph: " in log() and not hd.hd_faults()
     """)
