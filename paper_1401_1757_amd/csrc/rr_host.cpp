@@ -1709,6 +1709,17 @@ static void flow_work(const rr_ctx *c, const rr_run *run, long long most, long l
     *kept = std::min(node * run->node_count, std::max(most - *totals, kFlowTileDoubles));
 }
 
+// Scratch for a run by cash flows.  Where the memory is not there the run takes
+// the recurrence kernel, which needs none for reserves.
+static bool flow_room(rr_ctx *c, size_t doubles)
+{
+    if (c->flow_work.p && c->flow_work.n >= doubles) return true;
+    if (c->flow_work.p) drop_graphs(c);   // captured runs hold the present one
+    if (c->flow_work.alloc(doubles) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+}
+
 // The stream and events of a captured run's second branch, made before the
 // first capture that has one.
 static int branch_handles(rr_ctx *c)
@@ -2121,12 +2132,10 @@ extern "C" int rr_reserve_recurrence(rr_ctx *c, const rr_run *run, const rr_outp
         return RR_OK;
     }
     int rc;
-    if (flow_run(c, run)) {
-        long long need, kept;
-        flow_work(c, run, kFlowKept, &need, &kept);
-        need += kept;
-        if ((size_t)need > c->flow_work.n) drop_graphs(c);
-        HIPCHK(c, c->flow_work.alloc((size_t)need));
+    long long rows = 0, kept = 0;
+    const bool by_flows = flow_run(c, run);
+    if (by_flows) flow_work(c, run, kFlowKept, &rows, &kept);
+    if (by_flows && flow_room(c, (size_t)(rows + kept))) {
         if ((rc = branch_handles(c))) return rc;
         note_flow_launch(c);
         return launch_graphed(c, run_key(c, run, out, {1, (uint64_t)(uintptr_t)c->flow_work.p, (uint64_t)(uintptr_t)totals}),

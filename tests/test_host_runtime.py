@@ -215,3 +215,24 @@ def test_a_run_is_captured_on_its_second_call(double):
             c.ok(c.run(1, 70, mask, at=at))
     assert "graph: " in log() and not hd.hd_faults()
     """)
+
+
+@pytest.mark.parametrize("mask", ["rr.OUT_R0", "rr.OUT_R0 | rr.OUT_TOTALS | rr.OUT_STATS", "rr.OUT_TOTALS"])
+def test_runs_without_room_for_flows_take_the_recurrence_kernel(double, mask):
+    run(double, f"""
+    q, pf = book(20000, 120)
+    c = Ctx()
+    c.generate(q, 30, 120, **SAFE)
+    c.portfolio(pf)
+    log()
+    hd.hd_set_memory(hd.hd_used() + (2 << 20))   # the flows of 313 tiles take 20 MiB, their rows 0.3
+    for rep in range(4):
+        c.ok(c.run(1, 30, {mask}))
+        names = log()
+        if {mask} & rr.OUT_R0:
+            assert "k_recurrence" in names and "k_flow" not in names and "k_reserve_mm" not in names, names
+            assert ("graph: " in names) == (rep > 0), (rep, names)   # nothing is captured anew
+    hd.hd_set_memory(1 << 36)
+    c.ok(c.run(1, 30, {mask}))
+    assert "k_flow_sums" in log() and not hd.hd_faults()
+    """)
