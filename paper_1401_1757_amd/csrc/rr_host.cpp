@@ -648,7 +648,9 @@ static int enqueue_vasicek(rr_ctx *c, const VasParams &P, const std::vector<doub
 
 // Room for the discount products of the curves to come, kept beside them (8
 // bytes per curve value): given where no product can leave the FP64 range and
-// the memory is there; without them (null) runs take the recurrence kernel.
+// they are at most an eighth of the free memory, so that v^frac, the generator's
+// work and the outputs to come find theirs as without them; without the
+// products (null) runs take the recurrence kernel.
 // Room that is there already is always filled: a graph that the caller captured
 // may read it, and replays have to see the present curves' products.
 static double *discount_room(rr_ctx *c)
@@ -657,7 +659,11 @@ static double *discount_room(rr_ctx *c)
     c->has_disc = false;
     if (c->disc.p && c->disc.n >= need) return c->disc.p;
     if (!safe_products(c)) return nullptr;
-    if (c->disc.alloc(need) == hipSuccess) return c->disc.p;
+    c->disc.release();
+    size_t avail = 0, total = 0;
+    if (hipMemGetInfo(&avail, &total) == hipSuccess && need * sizeof(double) <= avail / 8 &&
+        c->disc.alloc(need) == hipSuccess)
+        return c->disc.p;
     (void)hipGetLastError();
     return nullptr;
 }

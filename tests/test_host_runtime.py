@@ -236,3 +236,26 @@ def test_runs_without_room_for_flows_take_the_recurrence_kernel(double, mask):
     c.ok(c.run(1, 30, {mask}))
     assert "k_flow_sums" in log() and not hd.hd_faults()
     """)
+
+
+def test_discount_products_leave_the_memory_to_others(double):
+    """The kept products take at most an eighth of what is free; a basis that leaves
+    less is valued by the recurrence kernel as if there were none."""
+    run(double, """
+    q, pf = book(300, 120)
+    for room, kept in ((40, True), (6, False)):     # in curve arrays, which take one; the generator three more
+        c = Ctx()
+        hd.hd_set_memory(1 << 36)
+        base = hd.hd_used()
+        curves = 120 * 1056 * 8
+        hd.hd_set_memory(base + room * curves)
+        c.generate(q, 1024, 120, **SAFE)
+        c.portfolio(pf)
+        log()
+        c.ok(c.run(1, 1024, rr.OUT_R0, noalloc=True))
+        assert ("k_reserve_mm" in log()) == kept
+        c.regenerate(**SAFE)
+        c.ok(c.run(1, 1024, rr.OUT_R0, noalloc=True))
+        assert ("k_reserve_mm" in log()) == kept
+        lib.rr_destroy(c.h)
+    """)
