@@ -984,7 +984,9 @@ extern "C" int rr_portfolio_upload(rr_ctx *c, const rr_portfolio *p)
     }
     c->head_pad = head_pad;
     c->has_pf = true;          // stage_tables reads max_age_needed
-    if ((rc = stage_tables(c))) { c->has_pf = false; return rc; }
+    rc = stage_tables(c);
+    c->has_pf = false;         // until every array of it is there
+    if (rc) return rc;
     for (int j = 0; j < n_pad; ++j) {
         s_qoff1[j] *= c->n_ages_stage;
         s_qoff2[j] *= c->n_ages_stage;
@@ -1219,6 +1221,7 @@ extern "C" int rr_portfolio_upload(rr_ctx *c, const rr_portfolio *p)
     c->slot_of_user.assign(n, -1);
     for (int j = 0; j < n_pad; ++j)
         if (s_uidx[j] >= 0) c->slot_of_user[s_uidx[j]] = j;
+    c->has_pf = true;
     ++c->gen;
     return RR_OK;
 }

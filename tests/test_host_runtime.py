@@ -259,3 +259,24 @@ def test_discount_products_leave_the_memory_to_others(double):
         assert ("k_reserve_mm" in log()) == kept
         lib.rr_destroy(c.h)
     """)
+
+
+def test_a_portfolio_that_found_no_room_is_not_valued(double):
+    run(double, """
+    q, pf = book(300, 60)
+    c = Ctx()
+    c.generate(q, 70, 60, **SAFE)
+    c.portfolio(pf)
+    c.ok(c.run(1, 70, rr.OUT_R0))
+    keep = []
+    big = rr.portfolio_struct(book(20000, 60, seed=2)[1], keep)
+    used = hd.hd_used()
+    for extra in range(0, 3 << 20, 100 << 10):
+        hd.hd_set_memory(used + extra)
+        rc = lib.rr_portfolio_upload(c.h, ctypes.byref(big))
+        log()
+        if rc == 0:
+            break
+        assert rc == rr.RR_ENOMEM and c.run(1, 70, rr.OUT_R0) == rr.RR_ESTATE and log() == ""
+    assert rc == 0 and extra > 0
+    """)
