@@ -87,8 +87,9 @@ struct PatWalk {
 };
 
 // A walk may be cut in time: the walker's transfer over steps [t0, t1) is
-// accumulated by tr_step from tr_init, and start(k transfers in order) sets the
-// state they lead to.  W::TR of FLOW_TR doubles a lane (0: walked by one
+// accumulated by tr_step from tr_init, advance(transfer), once for each chunk
+// before in order, sets the state they lead to, and past(t) ends a lane whose
+// term is over by then.  W::TR of FLOW_TR doubles a lane (0: walked by one
 // wavefront from the start).
 constexpr int FLOW_TR = 4;
 
@@ -521,68 +522,46 @@ struct FlowFrac {
     }
 };
 
-// Walk of J tiles of one model (64 slots apart) at one node over the steps
-// [t0, t1), t0 a multiple of U: emit(t, flow) for each step of a block of U
-// consecutive steps, the flows of the J tiles added in order, then done(t + U)
-// once per block.  Blocks are whole: steps past the last flow give
-// 0.  The walkers stand at step t0 (or, `lead`, at t0 - 1: that step is taken
-// first and its flow dropped, so that the amounts it leaves for t0 are there).
-// smax: the last flow's time; every lane of every tile lives past smin.
-template <int U, int J, class W, class Emit, class Done>
-__device__ __forceinline__ void flow_walk(const RecParams &P, const double *__restrict__ lq, W (&w)[J], double m,
-                                          int smax, int smin, int t0, int t1, bool lead, Emit emit, Done done)
+// Walk of a tile at one node over the steps [t0, t1), t0 a multiple of U: emit(t,
+// flow) for each step of a block of U consecutive steps, then done(t + U) once
+// per block.  Blocks are whole: steps past the last flow give 0.  The walker
+// stands at step t0 (or, `lead`, at t0 - 1: that step is taken first and its flow
+// dropped, so that the amounts it leaves for t0 are there).  smax: the last
+// flow's time; every lane of the tile lives past smin.
+template <int U, class W, class Emit, class Done>
+__device__ __forceinline__ void flow_walk(const RecParams &P, const double *__restrict__ lq, W &w, double m, int smax,
+                                          int smin, int t0, int t1, bool lead, Emit emit, Done done)
 {
     const bool shock = m != 1.0;
     if (lead) {
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            FlowIn a = w[j].load(P, lq, min(t0 - 1, smax - 1));
-            if (shock) w[j].shock(a, m);
-            (void)w[j].template step<true>(t0 - 1, a);
-        }
+        FlowIn a = w.load(P, lq, min(t0 - 1, smax - 1));
+        if (shock) w.shock(a, m);
+        (void)w.template step<true>(t0 - 1, a);
     }
     int t = t0;
     for (; t + U <= min(smin, t1); t += U) {
-        FlowIn a[J][U];
+        FlowIn a[U];
 #pragma unroll
-        for (int j = 0; j < J; ++j)
-#pragma unroll
-            for (int u = 0; u < U; ++u) a[j][u] = w[j].load(P, lq, t + u);
+        for (int u = 0; u < U; ++u) a[u] = w.load(P, lq, t + u);
         if (shock) {
 #pragma unroll
-            for (int j = 0; j < J; ++j)
-#pragma unroll
-                for (int u = 0; u < U; ++u) w[j].shock(a[j][u], m);
+            for (int u = 0; u < U; ++u) w.shock(a[u], m);
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            double f = w[0].template step<false>(t + u, a[0][u]);
-#pragma unroll
-            for (int j = 1; j < J; ++j) f += w[j].template step<false>(t + u, a[j][u]);
-            emit(t + u, f);
-        }
+        for (int u = 0; u < U; ++u) emit(t + u, w.template step<false>(t + u, a[u]));
         done(t + U);
     }
 #pragma unroll 1
     for (; t < t1; t += U) {
-        FlowIn a[J][U];
+        FlowIn a[U];
 #pragma unroll
-        for (int j = 0; j < J; ++j)
-#pragma unroll
-            for (int u = 0; u < U; ++u) a[j][u] = w[j].load(P, lq, min(t + u, smax - 1));
+        for (int u = 0; u < U; ++u) a[u] = w.load(P, lq, min(t + u, smax - 1));
         if (shock) {
 #pragma unroll
-            for (int j = 0; j < J; ++j)
-#pragma unroll
-                for (int u = 0; u < U; ++u) w[j].shock(a[j][u], m);
+            for (int u = 0; u < U; ++u) w.shock(a[u], m);
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            double f = w[0].template step<true>(t + u, a[0][u]);
-#pragma unroll
-            for (int j = 1; j < J; ++j) f += w[j].template step<true>(t + u, a[j][u]);
-            emit(t + u, f);
-        }
+        for (int u = 0; u < U; ++u) emit(t + u, w.template step<true>(t + u, a[u]));
         done(t + U);
     }
 }

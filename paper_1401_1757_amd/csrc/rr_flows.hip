@@ -130,21 +130,21 @@ k_flow_sums(RecParams P, int node_begin, int R, int row_len, int table_doubles, 
             const int t1 = !cut ? len : min(t0 + per, len);
             const bool lead = cut && t0 > 0;
             const int s0 = lead ? t0 - 1 : t0;   // first step walked
-            W w[1];
-            w[0].init(P, L, kind, shift, s0);
+            W w;
+            w.init(P, L, kind, shift, s0);
             if constexpr (cut) {
                 double x[FLOW_TR];
                 const int s1 = t1 > t0 && t1 < len ? t1 - 1 : s0;
-                flow_transfer(P, s_mem, w[0], m, smax, s0, s1, x);
+                flow_transfer(P, s_mem, w, m, smax, s0, s1, x);
 #pragma unroll
                 for (int i = 0; i < W::TR; ++i) s_tr[wave][i][lane] = x[i];
                 __syncthreads();
                 for (int c = 0; c < chunk; ++c) {
 #pragma unroll
                     for (int i = 0; i < W::TR; ++i) x[i] = s_tr[wave0 + c][i][lane];
-                    w[0].advance(x);
+                    w.advance(x);
                 }
-                w[0].past(s0);
+                w.past(s0);
             } else {
                 __syncthreads();
             }
@@ -158,21 +158,21 @@ k_flow_sums(RecParams P, int node_begin, int R, int row_len, int table_doubles, 
                 for (int t = t0; t < t1; t += FLOW_BLK) {
 #pragma unroll 2
                     for (int u = 0; u < FLOW_BLK; ++u) {
-                        const double f = w[0].step(t + u);
+                        const double f = w.step(t + u);
                         if (k) k[(size_t)(t + u) * 64] = f;
                         if (rows) row.put(t + u, f, lane);
                     }
                     if (rows) row.flush(t + FLOW_BLK, lane);
                 }
             } else {
-                flow_walk<FLOW_U, 1>(
+                flow_walk<FLOW_U>(
                     P, s_mem, w, m, smax, smin, t0, t1, lead,
                     [&](int t, double f) {
                         if (keep) keep[(size_t)t * 64] = f;
                         if (rows) row.put(t, f, lane);
                         if constexpr (X::frac) {
-                            if (keep) keep[(size_t)t * 64 + st.mid] = w[0].mid;
-                            if (rows) mid.put(t, w[0].mid, lane);
+                            if (keep) keep[(size_t)t * 64 + st.mid] = w.mid;
+                            if (rows) mid.put(t, w.mid, lane);
                         }
                     },
                     [&](int t) {

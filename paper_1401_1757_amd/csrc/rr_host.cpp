@@ -627,7 +627,7 @@ static double vasicek_log_step(const VasParams &P, const std::vector<double> &r0
 static int enqueue_vasicek(rr_ctx *c, const VasParams &P, const std::vector<double> &r0, double *v,
                            int month_major, double *r_out, double *D)
 {
-    const size_t need = vasicek_work_doubles(P.n_nodes, P.n_scen, P.n_steps, P.scen_pad);
+    const size_t need = vasicek_work_doubles(P.n_nodes, P.n_steps, P.scen_pad, r_out != nullptr);
     const bool new_r0 = r0 != c->vas_r0_host;
     if (need > c->vas_work.n || new_r0 || r0.size() > c->vas_r0.n)
         HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1729,8 +1729,21 @@ static bool flow_room(rr_ctx *c, size_t doubles)
     return false;
 }
 
-// The stream and events of a captured run's second branch, made before the
-// first capture that has one.
+// Whether a captured run has a second branch: the totals and the statistic of a
+// large run beside the product, which leaves half of a CU's wavefront slots
+// free: 10,000 policies x 1,000 scenarios 0.178 -> 0.165 ms.  A graph with a fork
+// and a join starts some 15 us later than a plain sequence, which is more than
+// the branch saves a small run: 1,002 x 9 0.053 with the branch, 0.038 without;
+// 340 x 16 0.048 / 0.033; 10,000 x 200 (31,400 tiles x scenarios) 0.096 without.
+constexpr long long kBranchTiles = 40000;   // tiles x scenarios
+
+static bool two_branches(const rr_ctx *c, const rr_run *run)
+{
+    return (run->out_mask & RR_OUT_R0) && (run->out_mask & (RR_OUT_TOTALS | RR_OUT_STATS)) &&
+           (long long)c->n_tiles * run->node_count * run->scen_count > kBranchTiles;
+}
+
+// The stream and events of the second branch, made for the first run that has one.
 static int branch_handles(rr_ctx *c)
 {
     if (!c->cap_fork) HIPCHK(c, hipEventCreateWithFlags(&c->cap_fork, hipEventDisableTiming));
@@ -1741,20 +1754,10 @@ static int branch_handles(rr_ctx *c)
 
 // The run by cash flows: reserves (if asked for), totals, statistics.  work:
 // flow_work's two parts, one after the other.
-//
-// Under capture the totals and the statistic of a large run are a branch of
-// their own beside the product, which leaves half of a CU's wavefront slots
-// free: 10,000 policies x 1,000 scenarios 0.178 -> 0.165 ms.  A graph with a fork
-// and a join starts some 15 us later than a plain sequence, which is more than
-// the branch saves a small run: 1,002 x 9 0.053 with the branch, 0.038 without;
-// 340 x 16 0.048 / 0.033; 10,000 x 200 (31,400 tiles x scenarios) 0.096 without.
-constexpr long long kBranchTiles = 40000;   // tiles x scenarios
-
 static int enqueue_flow_run(rr_ctx *c, const rr_run *run, const rr_outputs *out, double *work, long long kept,
                             double *totals, hipStream_t s, bool timed)
 {
-    const bool branch = s == c->cap_stream && totals && (run->out_mask & RR_OUT_R0) &&
-                        (long long)c->n_tiles * run->node_count * run->scen_count > kBranchTiles;
+    const bool branch = s == c->cap_stream && two_branches(c, run);
     auto sums = [&](const RecParams &P, const FlowShape &f, bool have_rows) -> int {
         hipStream_t q = s;
         if (branch) {
@@ -2145,7 +2148,7 @@ extern "C" int rr_reserve_recurrence(rr_ctx *c, const rr_run *run, const rr_outp
     const bool by_flows = flow_run(c, run);
     if (by_flows) flow_work(c, run, kFlowKept, &rows, &kept);
     if (by_flows && flow_room(c, (size_t)(rows + kept))) {
-        if ((rc = branch_handles(c))) return rc;
+        if (two_branches(c, run) && (rc = branch_handles(c))) return rc;
         note_flow_launch(c);
         return launch_graphed(c, run_key(c, run, out, {1, (uint64_t)(uintptr_t)c->flow_work.p, (uint64_t)(uintptr_t)totals}),
                               [&](hipStream_t s, bool timed) {

@@ -227,14 +227,14 @@ struct VasParams {
     unsigned long long key0, key1;
     int n_nodes, n_scen, n_steps, scen_pad;
 };
-// work: vasicek_work_doubles(...) doubles (normals and short rates, month-
-// major with stride scen_pad); r0: device [n_nodes]; v: month-major with
+// work: vasicek_work_doubles(...) doubles (normals and, where asked for, short
+// rates, month-major with stride scen_pad); r0: device [n_nodes]; v: month-major with
 // stride scen_pad (the library's curves) or [node][scen][step]; r_out:
 // [node][scen][step + 1] or null; D: the month-major curves' discount products
 // (launch_discounts) or null.  scen_pad: a multiple of 8.
 hipError_t launch_vasicek(const VasParams &P, const double *r0, double *work, double *v,
                           int month_major, double *r_out, double *D, hipStream_t stream);
-size_t vasicek_work_doubles(int n_nodes, int n_scen, int n_steps, int scen_pad);
+size_t vasicek_work_doubles(int n_nodes, int n_steps, int scen_pad, bool rates);
 // Mean discount curve of the run's scenarios per node (rr_kernels.hip) from the
 // kept discount products `disc` or, where there are none (null), from v by way
 // of D, which holds node_count * n_steps * scen_count doubles; vbar is

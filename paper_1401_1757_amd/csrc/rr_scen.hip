@@ -349,10 +349,9 @@ hipError_t launch_vasicek(const VasParams &P, const double *r0, double *work, do
     return hipGetLastError();
 }
 
-size_t vasicek_work_doubles(int n_nodes, int n_scen, int n_steps, int scen_pad)
+size_t vasicek_work_doubles(int n_nodes, int n_steps, int scen_pad, bool rates)
 {
-    (void)n_scen;
-    return (size_t)n_nodes * scen_pad * (3 * (size_t)n_steps + 1);
+    return (size_t)n_nodes * scen_pad * (2 * (size_t)n_steps + (rates ? n_steps + 1 : 0));
 }
 
 }  // namespace rr
