@@ -113,13 +113,15 @@ __device__ __forceinline__ f64x4 mfma64(double a, double b, f64x4 c)
 // into fragments, eight months ahead of their use; the workgroup's wavefronts
 // share their lines in the L1.  No LDS, no barriers.  A lane's policies of all
 // fragments lie side by side in the kept flows, and its NB scenarios are
-// neighbours, so that every access is 16 bytes a lane: the L1 takes 16 cycles
-// for a wavefront's access of 8 bytes a lane as for one of 16, and with 8-byte
-// ones it, not the matrix pipe, was the limit (53 against 77 TFLOP/s).
+// neighbours, so that every access is 16 bytes a lane (NB = 2): the L1 takes 16
+// cycles for a wavefront's access of 8 bytes a lane as for one of 16 (10,000
+// policies x 1,000 scenarios, the whole call: 0.189 -> 0.178 ms).
 //
-// Bound by the FP64 matrix pipe.  The flows are made by a launch of their own:
-// a wavefront that makes them beside the multiplying ones waits for the matrix
-// pipe at every FP64 operation (10,000 policies x 1,000 scenarios: 0.156 ms).
+// Bound by the FP64 matrix pipe while the chip is full, and by the long tiles
+// after that: 10,000 x 1,000 are 6.9 GFLOP with their padding in 127 us, the pipe
+// busy 0.76 of the kernel's cycles.  The flows are made by a launch of their own:
+// with a wavefront that makes them beside the multiplying ones, waiting for the
+// matrix pipe at every FP64 operation, that call took 0.192 ms instead of 0.189.
 // Tiles go longest first; the block index modulo the scenario blocks is the
 // scenario block, so that (eight blocks: exactly) one XCD's L2 serves few
 // columns of the discount products.
@@ -234,13 +236,26 @@ static void launch_mm(const RecParams &p, const FlowStore &st, int node_begin, i
     else hipLaunchKernelGGL((k_reserve_mm<false, WC, NB>), g, b, 0, s, p, st, node_begin, n_sb);
 }
 
+// The shape of a workgroup's part, 64 policies x 16, 32, 64 or 128 scenarios, by the
+// number of workgroups: a larger part reads less a product, and keeps fewer
+// CUs at work.  Whole calls, us, (WC, NB) = (1, 1) / (2, 1) / (2, 2) / (4, 2):
+//   10,000 policies x 48 44 / 45 / 49 / 68, x 64 49 / 45 / 50 / 69 (471 and 628
+//   parts of 16 scenarios), 1,000 x 20 nodes x 24 53 / 50 / 63 / 92;
+//   10,000 x 160 73 / 58 / 60 / 78, x 200 85 / 69 / 66 / 78 (471 and 628 parts of
+//   64), 30,000 x 40 78 / 68 / 63 / 91;
+//   10,000 x 1,000 284 / 171 / 147 / 154 (2,512 parts of 64), 1,000 x 20 x 500
+//   228 / 166 / 137 / 131 (2,560), 30,000 x 1,000 811 / 439 / 362 / 334.
+// Every shape adds a reserve's products in the same order: the same bits.
 hipError_t launch_reserve_mm(const RecParams &p, int node_begin, int nodes, bool has_mid, const FlowStore &st,
                              hipStream_t s)
 {
-    if (p.scen_count > 64) launch_mm<4, 2>(p, st, node_begin, nodes, has_mid, s);
-    else if (p.scen_count > 32) launch_mm<4, 1>(p, st, node_begin, nodes, has_mid, s);
-    else if (p.scen_count > 16) launch_mm<2, 1>(p, st, node_begin, nodes, has_mid, s);
-    else launch_mm<1, 1>(p, st, node_begin, nodes, has_mid, s);
+    const int sc = p.scen_count;
+    const long long tiles = (long long)(st.tile_end - st.tile_begin) * nodes;
+    auto parts = [&](int scenarios) { return tiles * ((sc + scenarios - 1) / scenarios); };
+    if (sc <= 16 || parts(16) < 512) launch_mm<1, 1>(p, st, node_begin, nodes, has_mid, s);
+    else if (sc <= 32 || parts(64) < 460) launch_mm<2, 1>(p, st, node_begin, nodes, has_mid, s);
+    else if (parts(64) < 2560) launch_mm<2, 2>(p, st, node_begin, nodes, has_mid, s);
+    else launch_mm<4, 2>(p, st, node_begin, nodes, has_mid, s);
     return hipGetLastError();
 }
 

@@ -327,3 +327,23 @@ def test_pinned_options_ask_for_the_recurrence_kernel(rr, ctx):
         ctx.set_option(opt, back)
     again = b.run(stats=True)
     assert all(torch.equal(a[k], again[k]) for k in a)
+
+
+@pytest.mark.parametrize("frac", [False, True])
+def test_reserve_product_shapes_give_the_same_bits(rr, ctx, frac):
+    """The four shapes of a workgroup's part, chosen by their number: every one
+    against the oracle, and the scenarios they share bit for bit."""
+    n, scen = 30_080, 345    # 470 tiles and more
+    b = Book(rr, ctx, kinds(71, n, 24, scen, 1, frac=frac, products=tuple(range(7)) if frac else (0,)), sample=700)
+    _say(f"reserves {n} x {scen}, frac={frac}")
+    a = b.run(stats=True)["r0"]                     # 64 policies x 128 scenarios
+    for scen0, nscen in ((0, 31), (7, 33), (9, 64), (3, 65), (281, 64), (0, 344)):
+        _say(f"scenarios {scen0} .. {scen0 + nscen - 1}")
+        part = b.run(scen0=scen0, nscen=nscen, totals=False)["r0"]
+        assert torch.equal(part, a[:, :, scen0:scen0 + nscen])
+    small = kinds(72, 200, 100, scen, 2, frac=frac)   # 64 x 16
+    b = Book(rr, ctx, small)
+    a = b.run(totals=False)["r0"]
+    for scen0, nscen in ((0, 2), (5, 15), (1, 16), (328, 17)):
+        part = b.run(scen0=scen0, nscen=nscen, totals=False)["r0"]
+        assert torch.equal(part, a[:, :, scen0:scen0 + nscen])
