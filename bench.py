@@ -66,29 +66,39 @@ def scenario_step_work(pf, node=0, node_step=12):
     return float((flops * S).sum()), float((ops * S).sum()), int((S > 0).sum()), int(S.sum())
 
 
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_recurrence_c3_10k_policies_1000_scenarios_traffic.json")
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_1401_1757_amd", "csrc", f)
-                  for f in ("rr_recurrence.h", "rr_internal.h")]
+CSRC = os.path.join(ROOT, "paper_1401_1757_amd", "csrc")
+# Committed FETCH_SIZE / WRITE_SIZE counters of the C3 launch, and the kernel
+# sources that they hold for: the recurrence kernel, a run by cash flows.
+TRAFFIC = {False: (os.path.join(ROOT, "profiles", "k_recurrence_c3_10k_policies_1000_scenarios_traffic.json"),
+                   ("rr_recurrence.h", "rr_internal.h")),
+           True: (os.path.join(ROOT, "profiles", "k_reserve_mm_c3_10k_policies_1000_scenarios_traffic.json"),
+                  ("rr_flows.h", "rr_flows.hip", "rr_reserve_mm.hip", "rr_recurrence.h", "rr_internal.h"))}
+
+
+def source_sha(by_flows):
+    import hashlib
+    h = hashlib.sha256()
+    for src in TRAFFIC[by_flows][1]:
+        with open(os.path.join(CSRC, src), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def measured_traffic(k, j, wg, ring=0):
-    """HBM bytes per recurrence launch from the committed FETCH_SIZE / WRITE_SIZE
-    counters, if they were taken on this kernel source and launch shape."""
-    import hashlib
+    """HBM bytes per launch (k = 0: per run by cash flows, its kernels together)
+    from the committed counters, if they were taken on these kernel sources and
+    this launch shape."""
+    by_flows = k == 0
     try:
-        with open(TRAFFIC_FILE) as f:
+        with open(TRAFFIC[by_flows][0]) as f:
             t = json.load(f)
-        h = hashlib.sha256()
-        for src in KERNEL_SOURCES:
-            with open(src, "rb") as f:
-                h.update(f.read())
-        sha = h.hexdigest()
+        sha = source_sha(by_flows)
     except OSError:
         return None
     launch = dict(t.get("launch", {}))
     launch.setdefault("curve_ring", 0)
-    if t.get("source_sha256") != sha or launch != {"block_k": k, "block_j": j, "wg_per_cu": wg,
-                                                   "curve_ring": ring}:
+    if t.get("source_sha256") != sha or (not by_flows and launch != {"block_k": k, "block_j": j, "wg_per_cu": wg,
+                                                                     "curve_ring": ring}):
         return None
     return float(t["traffic_bytes_per_launch"])
 
@@ -344,6 +354,7 @@ def node_means_leg(rr, synth, sync, steps=10):
         res = {}
         for name, fn in (("all_scenarios", f_all), ("mean_curve", f_mean), ("surrogate", f_sur)):
             fn()
+            fn()   # (captured)
             sync()
             res[name] = 1e3 * timed_steps(fn, steps, sync) / steps
         exact = ex["stats"].cpu().numpy()[:, 0]
@@ -394,8 +405,10 @@ def representative_leg(rr, synth, sync, steps=5):
                 "ms_per_step": ms, "kernel_ms": kms,
                 "kernel_tflops": achieved, "kernel_frac_fp64_peak": achieved / FP64_PEAK_TFLOPS if chains else None,
                 "kernel_issue_frac": ops * b.n_scen / (kms * 1e-3) / FP64_ISSUE_PEAK if chains else None,
-                "valuations_per_s": live * b.n_scen / (e / steps),
-                "valuation_steps_per_s": vsteps * b.n_scen / (e / steps),
+                # totals by summed cash flows form no reserve per policy and scenario
+                "valuations_per_s": live * b.n_scen / (e / steps) if chains else None,
+                "valuation_steps_per_s": vsteps * b.n_scen / (e / steps) if chains else None,
+                "scenario_totals_per_s": b.n_scen / (e / steps), "policies_in_a_total": live,
                 "escalating": int((pf.escalation > 0).sum()), "annual": int(pf.annual.sum()),
                 "launch": {"block_k": ctx.get_option(rr.OPT_LAST_K),
                            "block_j": ctx.get_option(rr.OPT_LAST_J),
@@ -506,7 +519,7 @@ def main():
         ctx.reserve_recurrence(0, 1, 0, b.n_scen, 12, out)
 
     t0 = time.perf_counter()
-    step()                       # first call: autotune + plan + graph capture
+    step()                       # first call: launched directly (by the recurrence kernel: plan, autotune)
     sync()
     first_call_s = time.perf_counter() - t0
     for _ in range(args.warmup):
@@ -545,7 +558,9 @@ def main():
         ctx.close()
         return
 
-    # Second timed region: HIP events around every recurrence kernel launch.
+    # Second timed region: HIP events around every run's kernels (without the
+    # totals pass and the statistic of the recurrence kernel's runs, and without
+    # the statistic of runs by cash flows).
     ctx.set_option(rr.OPT_KERNEL_TIMING, 1)
     ctx.kernel_times()
     elapsed_direct = timed_steps(step, args.steps, sync)
@@ -564,7 +579,7 @@ def main():
     traffic = measured_traffic(k_opt, j_opt, wg_opt, ring_opt)
 
     result = {
-        "metric": "policy x scenario reserve valuations/s (exact FP64 backward recurrence)",
+        "metric": "policy x scenario reserve valuations/s (exact FP64)",
         "value": value,
         "unit": "valuations/s",
         "n_gpus": 1,
@@ -598,7 +613,7 @@ def main():
         "launch": {"block_k": k_opt, "block_j": j_opt, "wg_per_cu": wg_opt,
                    "curve_ring": ctx.get_option(rr.OPT_LAST_RING),
                    "windows": ctx.get_option(rr.OPT_LAST_WINDOWS),
-                   "autotuned": args.block_k == 0},
+                   "by_cash_flows": by_flows, "autotuned": args.block_k == 0 and not by_flows},
     }
 
     exact_totals = out["totals"].cpu().numpy()[0]
@@ -632,7 +647,9 @@ def main():
         flops4 = sum(scenario_step_work(w4.portfolio, k, 12)[0] for k in range(w4.basis.n_nodes))
         flops4 *= w4.basis.n_scen
         chains4 = ctx.get_option(rr.OPT_LAST_K) > 0   # else summed cash flows: other work
-        sec["C4_nested_60_nodes"] = {"valuations_per_s": live4 * w4.basis.n_scen / (e4 / 10),
+        sec["C4_nested_60_nodes"] = {"valuations_per_s": live4 * w4.basis.n_scen / (e4 / 10) if chains4 else None,
+                                     "node_scenario_totals_per_s":
+                                     w4.basis.n_nodes * w4.basis.n_scen / (e4 / 10),
                                      "ms_per_step": 1e3 * e4 / 10,
                                      "live_valuations": live4 * w4.basis.n_scen,
                                      "nominal_valuations": w4.portfolio.n * w4.basis.n_nodes * w4.basis.n_scen,

@@ -248,12 +248,16 @@ int rr_check_portfolio(const rr_portfolio *p, int32_t n_steps, int32_t n_ages,
  * wavefront reads consecutive scenarios of one month).  Replaces any
  * previous basis.  A loaded portfolio that the new basis does not cover
  * (terms, ages or table indices) is dropped: rr_reserve_recurrence then
- * returns RR_ESTATE until a portfolio is uploaded again. */
+ * returns RR_ESTATE until a portfolio is uploaded again.  Beside the curves the
+ * library keeps their discount products D_t = v_0 ... v_{t-1} (8 bytes per curve
+ * value) where no product can leave the FP64 range (steps x the largest |log v|
+ * at most 600) and they are at most an eighth of the free device memory. */
 int rr_basis_upload(rr_ctx *ctx, const rr_basis *b);
 
 /* Copy, check, sort (by state model, payment pattern, remaining term
  * descending, age) and tile the portfolio (Sec. 3.8.2's per-policy inputs; the
- * paper balances uneven terms with a dynamic schedule, Sec. 5.1.1). */
+ * paper balances uneven terms with a dynamic schedule, Sec. 5.1.1).  After an
+ * upload that failed for want of memory there is no portfolio (RR_ESTATE). */
 int rr_portfolio_upload(rr_ctx *ctx, const rr_portfolio *p);
 
 /*
@@ -328,6 +332,19 @@ int rr_path_size(rr_ctx *ctx, int32_t node, int32_t node_step_m, int64_t *n_out)
  * term (Sec. 4.1.1-4.2.1) down to t = 0 (Sec. 3.8.2), plus the requested
  * reductions.  Asynchronous on the context's stream.  RR_ESTATE without a
  * basis and a portfolio; RR_ERANGE if path_cap is too small.
+ *
+ * The reserve at t = 0 is linear in the discount products, r_0 = sum_t f_t D_t
+ * with f_t the cash flow expected at t (Eq. (3.5)).  Runs of totals and
+ * statistics only, and state-0 reserves of two scenarios or more where the
+ * products are kept and the policies are not too many for the scenarios, form
+ * the flows once and go by that sum; all others, and every run with a launch
+ * option away from its default, by the recurrence kernel.  Results of the two
+ * agree to rounding, not bit for bit, so neither do a run and its parts where
+ * their numbers of scenarios lead to different ways.  Within one way nothing
+ * else changes a reserve: every launch shape and queue mode of the recurrence
+ * kernel gives the same bits, and so does every split by scenarios of a run by
+ * cash flows.  Such a run keeps up to 256 MiB of device memory in the context;
+ * where it is not to be had the recurrence kernel is taken.
  */
 int rr_reserve_recurrence(rr_ctx *ctx, const rr_run *run, const rr_outputs *out);
 
@@ -336,9 +353,9 @@ int rr_reserve_recurrence(rr_ctx *ctx, const rr_run *run, const rr_outputs *out)
  * capture, serving loops that must not call hipMalloc, harnesses that forbid
  * it): rr_reserve_recurrence with the same run, outputs and results, except
  * that it allocates nothing.  Its work lists, queue counters and partial
- * totals live in one static device array of 64 MiB per GPU, which every call
- * on that GPU shares (from any context) and which is held until the process
- * ends.  Consequences:
+ * totals, or its cash flows (a batch of nodes or policies at a time), live in
+ * one static device array of 64 MiB per GPU, which every call on that GPU shares
+ * (from any context) and which is held until the process ends.  Consequences:
  *   - a run whose scratch exceeds 64 MiB is RR_ERANGE (the partial totals take
  *     8 bytes x nodes x tiles of 64 policies x scenarios when totals or
  *     statistics are requested: e.g. 10,000 policies x 60 nodes x 500
@@ -349,18 +366,26 @@ int rr_reserve_recurrence(rr_ctx *ctx, const rr_run *run, const rr_outputs *out)
  *   - no autotuning (it builds and uploads candidate plans): the launch shape
  *     is the pinned options, else the shape an earlier rr_reserve_recurrence
  *     call chose for this run shape, else K = 16, J = 2, one workgroup per CU;
- *   - no graph replay and no kernel timing; the work lists are copied from
- *     host memory the context keeps on every call (a few tens of KB).
+ *   - no graph replay and no kernel timing; the work lists of the recurrence
+ *     kernel are copied from host memory the context keeps on every call (a few
+ *     tens of KB).
  * The basis and portfolio uploads still allocate: call them beforehand.
  */
 int rr_reserve_recurrence_noalloc(rr_ctx *ctx, const rr_run *run, const rr_outputs *out);
 
-/* Options (rr_set_option). */
+/* Options (rr_set_option).  K, J, workgroups, queues, ring and curve share are the
+ * recurrence kernel's: with any of them away from its default a run takes that
+ * kernel, with all at their defaults it may go by cash flows
+ * (rr_reserve_recurrence), and then the read-only K, J, workgroups, ring and
+ * windows of the last launch are 0. */
 #define RR_OPT_BLOCK_K      1   /* scenarios per lane: 0 = autotune, or 1,2,4,8,16,32 */
 #define RR_OPT_WG_PER_CU    2   /* persistent workgroups per CU: 0 = autotune, 1..8 */
-#define RR_OPT_USE_GRAPH    3   /* 1 = replay captured hipGraphs (default), 0 = direct launches */
-#define RR_OPT_KERNEL_TIMING 4  /* 1 = record HIP events around each recurrence kernel
-                                   (and each fused surrogate inference kernel) */
+#define RR_OPT_USE_GRAPH    3   /* 1 = replay captured hipGraphs (default): a run is captured on
+                                   its second call and replayed after that; 0 = direct launches */
+#define RR_OPT_KERNEL_TIMING 4  /* 1 = record HIP events around each recurrence kernel, around
+                                   the kernels of each run by cash flows together (flows,
+                                   product, totals; without the statistic), and around each
+                                   fused surrogate inference kernel */
 #define RR_OPT_XCD_QUEUES   5   /* 1 = per-XCD work queues with stealing (default), 0 = one queue */
 #define RR_OPT_LAST_K       6   /* read-only: scenarios per lane of the last launch */
 #define RR_OPT_LAST_WG      7   /* read-only: workgroups per CU of the last launch */
@@ -390,8 +415,9 @@ int rr_reserve_recurrence_noalloc(rr_ctx *ctx, const rr_run *run, const rr_outpu
 int rr_set_option(rr_ctx *ctx, int32_t option, int64_t value);
 int rr_get_option(rr_ctx *ctx, int32_t option, int64_t *value);
 
-/* Durations (ms) of the recurrence kernels launched since the previous call,
- * recorded when RR_OPT_KERNEL_TIMING is on; waits for them to finish. */
+/* Durations (ms) of the recurrence kernels (or of the kernels of runs by cash
+ * flows, one duration a run) launched since the previous call, recorded when
+ * RR_OPT_KERNEL_TIMING is on; waits for them to finish. */
 int rr_kernel_times(rr_ctx *ctx, double *ms, int32_t cap, int32_t *count);
 
 /* ------------------------------------------------------------------------

@@ -1731,10 +1731,12 @@ static bool flow_room(rr_ctx *c, size_t doubles)
 
 // Whether a captured run has a second branch: the totals and the statistic of a
 // large run beside the product, which leaves half of a CU's wavefront slots
-// free: 10,000 policies x 1,000 scenarios 0.178 -> 0.165 ms.  A graph with a fork
-// and a join starts some 15 us later than a plain sequence, which is more than
-// the branch saves a small run: 1,002 x 9 0.053 with the branch, 0.038 without;
-// 340 x 16 0.048 / 0.033; 10,000 x 200 (31,400 tiles x scenarios) 0.096 without.
+// free.  A graph with a fork and a join starts some 15 us later than a plain
+// sequence, which is more than the branch saves a small run: 1,002 x 9 0.053 with
+// the branch, 0.038 without; 340 x 16 0.048 / 0.033.  At the line 10,000 x 254
+// (39,878 tiles x scenarios) takes 0.087 without, x 256 0.085 with it; beyond,
+// against the same launches made directly: 30,000 x 1,000 0.359 -> 0.350, 4,001
+// of every product x 2 x 333 0.253 -> 0.246, 10,000 x 1,000 0.152 -> 0.150.
 constexpr long long kBranchTiles = 40000;   // tiles x scenarios
 
 static bool two_branches(const rr_ctx *c, const rr_run *run)

@@ -443,7 +443,7 @@ __global__ void __launch_bounds__(64) k_disc_products(const double *__restrict__
 // XCDs had written (100 policies, one scenario: 30 us, side by side 17).
 // Bound by the one read of the products.  Read a row a thread after a chain per
 // scenario had written them, 10,000 policies' node means at 60 nodes x 500
-// scenarios took 0.372 ms, now 0.113.
+// scenarios took 0.372 ms, now 0.101.
 constexpr int MEAN_MONTHS = 16, MEAN_WAVES = 4;
 
 __global__ void __launch_bounds__(64 * MEAN_WAVES)
