@@ -137,7 +137,7 @@ def cpu_model() -> str:
 
 def cpu_share() -> int:
     """Threads for the CPU leg: the CPU share this process is given
-    (OMP_NUM_THREADS, as a GPU machine sets it per GPU), else every core."""
+    (OMP_NUM_THREADS, where it is set per GPU), else every core."""
     val = os.environ.get("OMP_NUM_THREADS", "").strip()
     if val.isdigit() and int(val) > 0:
         return int(val)
