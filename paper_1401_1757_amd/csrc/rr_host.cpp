@@ -800,9 +800,13 @@ extern "C" int rr_curves_generate_vasicek(rr_ctx *c, const rr_vasicek *vs)
     int rc;
     if ((rc = vasicek_params(c, vs, c->n_nodes, c->n_scen, c->n_steps, c->scen_pad, &P, &r0))) return rc;
     ++c->curve_gen;   // cached per-scenario decisions (the surrogate's range flags) are stale
+    const double present = c->curve_log_step;
     c->curve_log_step = vasicek_log_step(P, r0);
     double *D = discount_room(c);
-    if ((rc = enqueue_vasicek(c, P, r0, c->v.p, 1, nullptr, D))) return rc;
+    if ((rc = enqueue_vasicek(c, P, r0, c->v.p, 1, nullptr, D))) {
+        c->curve_log_step = std::max(present, c->curve_log_step);   // the curves may be either's
+        return rc;
+    }
     c->has_disc = D && safe_products(c);
     return RR_OK;
 }

@@ -280,3 +280,26 @@ def test_a_portfolio_that_found_no_room_is_not_valued(double):
         assert rc == rr.RR_ENOMEM and c.run(1, 70, rr.OUT_R0) == rr.RR_ESTATE and log() == ""
     assert rc == 0 and extra > 0
     """)
+
+
+def test_a_failed_regeneration_keeps_the_present_curves_bound(double):
+    run(double, """
+    q, pf = book(300, 160)
+    c = Ctx()
+    v = np.full((1, 70, 160), 1e-27)
+    keep = []
+    c.ok(lib.rr_basis_upload(c.h, ctypes.byref(rr.basis_struct(q, v, None, keep))))
+    c.portfolio(pf)
+    c.ok(c.run(1, 70, rr.OUT_TOTALS, noalloc=True))
+    assert "k_recurrence" in log()
+    hd.hd_set_memory(hd.hd_used())
+    assert lib.rr_curves_generate_vasicek(c.h, ctypes.byref(c.vas(1, keep, SAFE))) == rr.RR_ENOMEM
+    log()
+    c.ok(c.run(1, 70, rr.OUT_TOTALS, noalloc=True))
+    assert "k_recurrence" in log()
+    hd.hd_set_memory(1 << 36)
+    c.regenerate(**SAFE)
+    log()
+    c.ok(c.run(1, 70, rr.OUT_TOTALS, noalloc=True))
+    assert "k_flow_totals" in log()
+    """)
