@@ -234,9 +234,11 @@ int fail(rr_ctx *c, int code, const char *fmt, ...);
 #define HIPCHK(ctx, expr)                                                                     \
     do {                                                                                      \
         hipError_t e__ = (expr);                                                              \
-        if (e__ != hipSuccess)                                                                \
+        if (e__ != hipSuccess) {                                                              \
+            (void)hipGetLastError(); /* reported here, not by the next launch's check */      \
             return rr::host::fail(ctx, e__ == hipErrorOutOfMemory ? RR_ENOMEM : RR_EDEVICE,   \
                                   "%s: %s", #expr, hipGetErrorString(e__));                   \
+        }                                                                                     \
     } while (0)
 
 template <typename T>

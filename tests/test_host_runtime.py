@@ -303,3 +303,26 @@ def test_a_failed_regeneration_keeps_the_present_curves_bound(double):
     c.ok(c.run(1, 70, rr.OUT_TOTALS, noalloc=True))
     assert "k_flow_totals" in log()
     """)
+
+
+def test_a_failed_call_is_reported_once(double):
+    """The launches' check of the runtime's last error does not find the error that
+    an earlier call has reported already."""
+    run(double, """
+    q, pf = book(300, 60)
+    c = Ctx()
+    c.generate(q, 70, 60, **SAFE)
+    c.portfolio(pf)
+    c.ok(c.run(1, 70, rr.OUT_R0 | rr.OUT_TOTALS))
+    hd.hd_set_memory(hd.hd_used())
+    big = rr.Basis(q.shape[0], q.shape[1], np.ascontiguousarray(q).ctypes.data, 1, 4000, 60, None, None, rr.HOST, 0.0)
+    v = np.ones((1, 4000, 60))
+    big.v = v.ctypes.data
+    other = Ctx.__new__(Ctx)
+    other.h = ctypes.c_void_p()
+    hd.hd_set_memory(hd.hd_used() + 100000)
+    assert lib.rr_create(ctypes.byref(other.h), 0, STREAM) == 0
+    assert lib.rr_basis_upload(other.h, ctypes.byref(big)) == rr.RR_ENOMEM
+    c.ok(c.run(1, 70, rr.OUT_R0 | rr.OUT_TOTALS, at=2))
+    c.ok(c.run(1, 70, rr.OUT_TOTALS, noalloc=True))
+    """)
