@@ -1310,6 +1310,12 @@ extern "C" int rr_markov_upload(rr_ctx *c, const rr_markov *m)
                 if (std::fabs(sum - 1.0) > 1e-12)
                     return fail(c, RR_EINVAL, "markov: model %d age %d row %d sums to %.17g", md, a, i, sum);
             }
+    // A portfolio with RR_MARKOV policies holds the old benefits: drop it (and
+    // before the old models go, should there be no room for the new ones).
+    bool has_mk = false;
+    for (int i = 0; i < c->n_user; ++i) has_mk |= c->h_product[i] == RR_MARKOV;
+    if (c->has_pf && has_mk) c->has_pf = false;
+    c->has_markov = false;
     if (MP == 4) {   // the transposed copy behind the matrices
         const size_t n = wp.size();
         wp.resize(2 * n);
@@ -1327,10 +1333,6 @@ extern "C" int rr_markov_upload(rr_ctx *c, const rr_markov *m)
     c->mk_states = M;
     c->mk_ages = m->n_ages;
     c->has_markov = true;
-    // A portfolio with RR_MARKOV policies holds the old benefits: drop it.
-    bool has_mk = false;
-    for (int i = 0; i < c->n_user; ++i) has_mk |= c->h_product[i] == RR_MARKOV;
-    if (c->has_pf && has_mk) c->has_pf = false;
     drop_graphs(c);
     c->plans.clear();
     c->tuned.clear();

@@ -326,3 +326,28 @@ def test_a_failed_call_is_reported_once(double):
     c.ok(c.run(1, 70, rr.OUT_R0 | rr.OUT_TOTALS, at=2))
     c.ok(c.run(1, 70, rr.OUT_TOTALS, noalloc=True))
     """)
+
+
+def test_markov_models_that_found_no_room_leave_no_portfolio_on_them(double):
+    run(double, """
+    q, pf = book(300, 60, products=(0,))
+    c = Ctx()
+    c.generate(q, 70, 60, **SAFE)
+    w, ben = synth.phi_models(q.shape[1])
+
+    def markov(w, ben):
+        keep = [np.ascontiguousarray(w), np.ascontiguousarray(ben)]
+        m = rr.Markov(w.shape[0], w.shape[2], w.shape[1], keep[0].ctypes.data, keep[1].ctypes.data, rr.HOST)
+        return lib.rr_markov_upload(c.h, ctypes.byref(m))
+
+    c.ok(markov(w, ben))
+    c.portfolio(synth.with_markov_policies(np.random.default_rng(1), pf, (w, ben), 0.5))
+    c.ok(c.run(1, 70, rr.OUT_R0))
+    hd.hd_set_memory(hd.hd_used())
+    log()
+    assert markov(np.concatenate([w] * 40), np.concatenate([ben] * 40)) == rr.RR_ENOMEM
+    assert c.run(1, 70, rr.OUT_R0) == rr.RR_ESTATE and log() == ""
+    hd.hd_set_memory(1 << 36)
+    c.portfolio(pf)
+    c.ok(c.run(1, 70, rr.OUT_R0))
+    """)
