@@ -447,13 +447,18 @@ extern "C" const char *rr_last_error(const rr_ctx *c) { return c ? c->err.c_str(
 extern "C" int rr_set_stream(rr_ctx *c, uint64_t stream)
 {
     if (!c) return RR_EINVAL;
-    // (while the caller captures the new stream, nothing may be done on another)
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (stream && !c->graphs.empty() &&
-        hipStreamIsCapturing((hipStream_t)(uintptr_t)stream, &status) != hipSuccess)
-        status = hipStreamCaptureStatusActive;
-    drop_graphs(c, status != hipStreamCaptureStatusNone);
-    c->stream = (hipStream_t)(uintptr_t)stream;
+    const hipStream_t next = (hipStream_t)(uintptr_t)stream;
+    auto capturing = [](hipStream_t q) {   // (the null stream cannot be captured)
+        hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+        if (q && hipStreamIsCapturing(q, &status) != hipSuccess) {
+            (void)hipGetLastError();
+            return true;
+        }
+        return status != hipStreamCaptureStatusNone;
+    };
+    // (while the caller captures, nothing else may be done on a stream)
+    if (!c->graphs.empty()) drop_graphs(c, capturing(next) || capturing(c->stream));
+    c->stream = next;
     return RR_OK;
 }
 

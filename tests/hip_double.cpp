@@ -256,6 +256,7 @@ hipError_t hipEventDestroy(hipEvent_t e)
 }
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
 {
+    not_in_capture("hipEventRecord");
     ((Event *)e)->captured_on = g_streams[s].capturing ? g_streams[s].origin : nullptr;
     ((Event *)e)->ticket = g_ticket;
     return hipSuccess;

@@ -351,3 +351,27 @@ def test_markov_models_that_found_no_room_leave_no_portfolio_on_them(double):
     c.portfolio(pf)
     c.ok(c.run(1, 70, rr.OUT_R0))
     """)
+
+
+@pytest.mark.parametrize("captured", ["STREAM", "STREAM + 0x100"])
+def test_another_stream_while_the_caller_captures(double, captured):
+    """Changing to a stream that the caller is capturing, or away from one, drops
+    the captured runs without an operation on any stream."""
+    run(double, f"""
+    q, pf = book(300, 60)
+    c = Ctx()
+    c.generate(q, 70, 60, **SAFE)
+    c.portfolio(pf)
+    for rep in range(2):
+        c.ok(c.run(1, 70, rr.OUT_R0 | rr.OUT_TOTALS))
+    assert hd.hd_live_execs() == 1
+    waits = hd.hd_waits()
+    hd.hd_set_capturing({captured}, 1)
+    c.ok(lib.rr_set_stream(c.h, STREAM + 0x100))
+    assert hd.hd_waits() == waits and not hd.hd_faults(), hd.hd_faults()
+    hd.hd_set_capturing({captured}, 0)
+    for rep in range(3):
+        c.ok(c.run(1, 70, rr.OUT_R0 | rr.OUT_TOTALS))
+    lib.rr_destroy(c.h)
+    assert hd.hd_live_execs() == 0 and not hd.hd_faults(), hd.hd_faults()
+    """)
